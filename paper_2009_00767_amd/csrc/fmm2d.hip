@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "device_common.h"
+#include "near2d.h"
 
 namespace sffmm {
 
@@ -594,60 +595,6 @@ void launch_l2p2d(const FmmArgs& a, bool leaf_local, hipStream_t st) {
 // a wave's source loads are broadcasts of a few addresses.  Pairs with r = 0
 // (the target itself, coincident points) contribute nothing.
 // ---------------------------------------------------------------------------
-// one source: pairs with r = 0 (the target itself, coincident points) add nothing
-__device__ __forceinline__ void pair2_f64(double x, double y, double sx, double sy, double q,
-                                          double& phi, double& ex, double& ey) {
-  const double dx = x - sx, dy = y - sy;
-  const double r2 = dx * dx + dy * dy;
-  if (r2 == 0.0) return;
-  phi += q * 0.5 * log(r2);
-  const double w = q / r2;
-  ex -= w * dx;
-  ey -= w * dy;
-}
-
-// lsh = 2 (L - d) when the launch works at level d = lt.L of an adaptive tree
-// of depth L: leaf keys and leaf offsets are those of level d, and only the
-// targets whose leaf lies at level d are taken.
-__global__ __launch_bounds__(256) void k_p2p2d_f64(FmmArgs a, int lsh) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= a.n) return;
-  const LevelTable& lt = a.lt;
-  if (a.depth && a.depth[j] != lt.L) return;
-  const uint32_t key = a.keys[j] >> lsh;
-  const uint32_t sysbits = key & ~local2(0xFFFFFFFFu, lt.L);
-  const int lx = (int)compact2(local2(key, lt.L)), ly = (int)compact2(local2(key, lt.L) >> 1);
-  const int nl = 1 << lt.L;
-  const double x = a.xs[j], y = a.ys[j];
-  double phi = 0.0, ex = 0.0, ey = 0.0;
-  for (int ny = ly - 1; ny <= ly + 1; ++ny) {
-    if (ny < 0 || ny >= nl) continue;
-    for (int nx = lx - 1; nx <= lx + 1; ++nx) {
-      if (nx < 0 || nx >= nl) continue;
-      const uint32_t nk = sysbits | spread2(nx) | (spread2(ny) << 1);
-      const int32_t i0 = a.leaf_start[(int64_t)nk << lsh], i1 = a.leaf_start[(int64_t)(nk + 1) << lsh];
-      // sources four at a time, their loads issued together (the sums keep
-      // the source order)
-      int32_t i = i0;
-      for (; i + 4 <= i1; i += 4) {
-        double sx[4], sy[4], sq[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          sx[u] = a.xs[i + u];
-          sy[u] = a.ys[i + u];
-          sq[u] = a.qs[i + u];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) pair2_f64(x, y, sx[u], sy[u], sq[u], phi, ex, ey);
-      }
-      for (; i < i1; ++i) pair2_f64(x, y, a.xs[i], a.ys[i], a.qs[i], phi, ex, ey);
-    }
-  }
-  a.near_pot[j] = phi;
-  a.near_ex[j] = ex;
-  a.near_ey[j] = ey;
-}
-
 // FP32 pair terms from leaf-local coordinates (leaf-centre offsets are
 // multiples of s_L, exact in FP32); log2 and reciprocal on the hardware
 // transcendental unit; running sums flushed to FP64 every 32 sources.
@@ -674,8 +621,6 @@ constexpr float kP2pEps = 0x1p-96f;
 // kernel, which reads sources from global memory leaf by leaf (dense clusters,
 // where leaves are large: there a wave mostly lies in one leaf and reads its
 // sources with scalar loads).
-constexpr int kP2pHalo = 6;  // 4 x 4 tile + one leaf on each side
-constexpr int kP2pHaloLeaves = kP2pHalo * kP2pHalo;
 constexpr int kP2pThreads = 320;
 constexpr int kP2pPad = 8;  // zero records after the stage: a span's last batch may read past it
 constexpr int kTileBatch = 4;  // LDS records loaded together per target (batches of 8 spilled)
@@ -693,22 +638,6 @@ __device__ __forceinline__ void pair_f32_h(const float4& t, const float4& s, flo
   fy -= w * dy;
 }
 
-// Workgroup order of the near-field kernels: chunks of kXcdChunk consecutive
-// workgroups (consecutive sorted targets or tiles) go to one XCD, the chunks dealt over
-// the 8 XCDs in the order the hardware deals workgroups, so that the waves that
-// share a neighbourhood mostly read its sources through one XCD's L2.  The
-// grid is a multiple of 8 kXcdChunk workgroups (direct_grid) and the map is a
-// permutation of it.
-constexpr int kXcdChunk = 8;
-__device__ __forceinline__ int64_t xcd_chunk_remap(int64_t bid) {
-  const int64_t x = bid & 7, i = bid >> 3;
-  return ((i / kXcdChunk) * 8 + x) * kXcdChunk + (i % kXcdChunk);
-}
-static dim3 direct_grid(int64_t n) {
-  const int64_t per = 8 * kXcdChunk;
-  return dim3((unsigned)(((n + 255) / 256 + per - 1) / per * per));
-}
-
 // Eight waves per SIMD (64 registers): a few spills at the row level cost less
 // than the lower occupancy without them (measured beside the moments chain).
 __global__ __launch_bounds__(kP2pThreads, 8) void k_p2p2d_f32_tile(FmmArgs a, int cap) {
@@ -716,48 +645,19 @@ __global__ __launch_bounds__(kP2pThreads, 8) void k_p2p2d_f32_tile(FmmArgs a, in
   __shared__ int32_t hstart[kP2pHaloLeaves];
   __shared__ int32_t hoff[kP2pHaloLeaves + 1];
   const LevelTable& lt = a.lt;
-  const int L = lt.L, nl = 1 << L, tid = threadIdx.x;
+  const int L = lt.L, tid = threadIdx.x;
   const int64_t tl = xcd_chunk_remap(blockIdx.x);
   if (tl >= ((int64_t)lt.nsys << (2 * (lt.L - 2)))) return;  // grid padding (workgroup-uniform)
   const uint32_t tile = (uint32_t)tl;
   const uint32_t k0 = tile << 4;  // first leaf key of the tile (system bits included)
-  const uint32_t sysbits = k0 & ~local2(0xFFFFFFFFu, L);
   const uint32_t tm = local2(k0, L);
   const int bx0 = (int)compact2(tm), by0 = (int)compact2(tm >> 1);
-  int cnt = 0;
-  if (tid < kP2pHaloLeaves) {
-    const int x = bx0 - 1 + tid % kP2pHalo, y = by0 - 1 + tid / kP2pHalo;
-    int32_t s0 = 0;
-    if (x >= 0 && x < nl && y >= 0 && y < nl) {
-      const uint32_t k = sysbits | spread2((uint32_t)x) | (spread2((uint32_t)y) << 1);
-      s0 = a.leaf_start[k];
-      cnt = a.leaf_start[k + 1] - s0;
-    }
-    hstart[tid] = s0;
-  }
-  if (tid < 64) {  // offsets of the halo leaves: an inclusive scan across wave 0
-    int v = cnt;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int u = __shfl_up(v, d, 64);
-      if (tid >= d) v += u;
-    }
-    if (tid < kP2pHaloLeaves) hoff[tid + 1] = v;
-    if (tid == 0) hoff[0] = 0;
-  }
-  __syncthreads();
+  tile_halo(lt, a.leaf_start, tile, hstart, hoff);
   const int total = hoff[kP2pHaloLeaves];
   if (tid == 0) a.p2p_over[tile] = total > cap ? 1 : 0;
   if (total > cap) return;  // workgroup-uniform
   for (int e = tid; e < total; e += kP2pThreads) {
-    int lo = 0, hi = kP2pHaloLeaves - 1;  // the last halo leaf starting at or before e
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (hoff[mid] <= e)
-        lo = mid;
-      else
-        hi = mid - 1;
-    }
+    const int lo = halo_leaf(hoff, e);
     float4 v = a.pts[hstart[lo] + (e - hoff[lo])];
     v.w = (float)(lo % kP2pHalo);
     src[e] = v;
@@ -894,7 +794,7 @@ __device__ __forceinline__ void p2p_leaf_f32(const float4* __restrict__ pts, int
   }
 }
 
-// lsh as in k_p2p2d_f64 (adaptive depth: pts rebased to the level-d box centres).
+// lsh: see walk_near2d (adaptive depth: only the targets of depth lt.L).
 __global__ __launch_bounds__(256) void k_p2p2d_f32(FmmArgs a, int tiled,
                                                   const float4* __restrict__ pts,
                                                   const int32_t* __restrict__ leaf_start, int lsh) {
@@ -904,107 +804,16 @@ __global__ __launch_bounds__(256) void k_p2p2d_f32(FmmArgs a, int tiled,
   if (a.depth && a.depth[j] != lt.L) return;
   const uint32_t key = a.keys[j] >> lsh;
   if (tiled && !a.p2p_over[key >> 4]) return;  // done by the tile kernel
-  const int nl = 1 << lt.L;
   const float sL = (float)lt.s[lt.L];
   const float4 t = pts[j];
   double phi = 0.0, ex = 0.0, ey = 0.0;
-  const uint32_t lmask = local2(0xFFFFFFFFu, lt.L);
-  const int lx = (int)compact2(key & lmask), ly = (int)compact2((key & lmask) >> 1);
-  // The wave's distinct leaves (its targets are consecutive in sorted order, so
-  // dense leaves give one or two): when there are at most four, of one system,
-  // whose neighbourhoods fit in a 4 x 4-leaf box, and the sources of that box
-  // are at most 1.2 x those of the largest single neighbourhood (a wave in one
-  // leaf always), the wave walks the box with uniform leaf ranges and sources
-  // (scalar loads), each lane taking the leaves next to its own; its leaves
-  // come in the order of its own 3 x 3 walk, so the sums are the same as with
-  // the per-lane walk below, which reads sources with vector loads.
-  uint64_t todo = __ballot(true);
-  int nd = 0, bx0 = 0, bx1 = -1, by0 = 0, by1 = -1;
-  int dx0 = 0, dy0 = 0, dx1 = 0, dy1 = 0, dx2 = 0, dy2 = 0, dx3 = 0, dy3 = 0;
-  uint32_t sys0 = 0;
-  bool shared = true;
-  while (todo != 0 && shared) {
-    const uint32_t kk = __builtin_amdgcn_readlane(key, __ffsll((unsigned long long)todo) - 1);
-    todo &= ~__ballot(key == kk);
-    const int kx = (int)compact2(kk & lmask), ky = (int)compact2((kk & lmask) >> 1);
-    const uint32_t ks = kk & ~lmask;
-    if (nd == 0) {
-      sys0 = ks;
-      bx0 = kx - 1;
-      bx1 = kx + 1;
-      by0 = ky - 1;
-      by1 = ky + 1;
-    } else {
-      bx0 = min(bx0, kx - 1);
-      bx1 = max(bx1, kx + 1);
-      by0 = min(by0, ky - 1);
-      by1 = max(by1, ky + 1);
-    }
-    if (nd == 0) {
-      dx0 = kx;
-      dy0 = ky;
-    } else if (nd == 1) {
-      dx1 = kx;
-      dy1 = ky;
-    } else if (nd == 2) {
-      dx2 = kx;
-      dy2 = ky;
-    } else {
-      dx3 = kx;
-      dy3 = ky;
-    }
-    ++nd;
-    shared = nd <= 4 && ks == sys0 && (bx1 - bx0 + 1) * (by1 - by0 + 1) <= 16;
-  }
-  if (shared && nd > 1) {
-    int usum = 0, o0 = 0, o1 = 0, o2 = 0, o3 = 0;
-    for (int ny = max(by0, 0); ny <= min(by1, nl - 1); ++ny)
-      for (int nx = max(bx0, 0); nx <= min(bx1, nl - 1); ++nx) {
-        const uint32_t nk = sys0 | spread2(nx) | (spread2(ny) << 1);
-        const int c = leaf_start[(int64_t)(nk + 1) << lsh] - leaf_start[(int64_t)nk << lsh];
-        usum += c;
-        if (abs(nx - dx0) <= 1 && abs(ny - dy0) <= 1) o0 += c;
-        if (abs(nx - dx1) <= 1 && abs(ny - dy1) <= 1) o1 += c;
-        if (nd > 2 && abs(nx - dx2) <= 1 && abs(ny - dy2) <= 1) o2 += c;
-        if (nd > 3 && abs(nx - dx3) <= 1 && abs(ny - dy3) <= 1) o3 += c;
-      }
-    shared = 5 * usum <= 6 * max(max(o0, o1), max(o2, o3));
-  }
-  if (shared) {
-    for (int ny = max(by0, 0); ny <= min(by1, nl - 1); ++ny) {
-      const float oy = (float)(ly - ny) * sL;
-      for (int nx = max(bx0, 0); nx <= min(bx1, nl - 1); ++nx) {
-        const uint32_t nk = sys0 | spread2(nx) | (spread2(ny) << 1);
-        const int32_t i0 = leaf_start[(int64_t)nk << lsh], i1 = leaf_start[(int64_t)(nk + 1) << lsh];
-        if (abs(nx - lx) <= 1 && abs(ny - ly) <= 1)
-          p2p_leaf_f32(pts, i0, i1, t, (float)(lx - nx) * sL, oy, phi, ex, ey);
-      }
-    }
-  } else {
-    const uint32_t sysbits = key & ~lmask;
-    for (int ny = ly - 1; ny <= ly + 1; ++ny) {
-      if (ny < 0 || ny >= nl) continue;
-      const float oy = (float)(ly - ny) * sL;
-      for (int nx = lx - 1; nx <= lx + 1; ++nx) {
-        if (nx < 0 || nx >= nl) continue;
-        const uint32_t nk = sysbits | spread2(nx) | (spread2(ny) << 1);
-        p2p_leaf_f32(pts, leaf_start[(int64_t)nk << lsh], leaf_start[(int64_t)(nk + 1) << lsh], t,
-                     (float)(lx - nx) * sL, oy, phi, ex, ey);
-      }
-    }
-  }
+  walk_near2d(lt, key, leaf_start, lsh, [&](int32_t i0, int32_t i1, int dx, int dy) {
+    p2p_leaf_f32(pts, i0, i1, t, (float)dx * sL, (float)dy * sL, phi, ex, ey);
+  });
   phi -= (double)t.z * (double)__builtin_amdgcn_logf(kP2pEps);  // the target's own term
   a.near_pot[j] = phi * 0.34657359027997264;  // (ln 2) / 2: log r = log2(r^2) ln2 / 2
   a.near_ex[j] = ex;
   a.near_ey[j] = ey;
-}
-
-// LDS records staged per tile: 1.5 x the mean halo occupancy, in [512, 2048].
-int p2p2d_tile_cap(const LevelTable& lt, int64_t n) {
-  const double leaves = (double)((int64_t)lt.nsys << (2 * lt.L));
-  const double want = 1.5 * kP2pHaloLeaves * (double)n / leaves;
-  const int cap = ((int)std::min(want, 2048.0) + 127) / 128 * 128;
-  return std::max(512, std::min(2048, cap));
 }
 
 // ---------------------------------------------------------------------------
@@ -1136,39 +945,27 @@ __global__ __launch_bounds__(256) void k_p2p2d_f32_shallow(FmmArgs a) {
 
 void launch_p2p2d(const FmmArgs& a, bool leaf_local, hipStream_t st) {
   if (a.n <= 0) return;
-  const dim3 grid((unsigned)((a.n + 255) / 256));
-  if (a.depth) {
-    // the uniform near field of depth d for the targets whose depth is d (the
-    // others leave at once): FP64, one launch per level; FP32, the direct
-    // kernel for depth L and one launch for every shallower depth
-    if (leaf_local) {
-      hipLaunchKernelGGL(k_p2p2d_f32, direct_grid(a.n), dim3(256), 0, st, a, 0, a.pts,
-                         a.leaf_start, 0);
-      if (a.lt.L > a.lt.kmin) hipLaunchKernelGGL(k_p2p2d_f32_shallow, grid, dim3(256), 0, st, a);
-    } else {
-      for (int d = a.lt.kmin; d <= a.lt.L; ++d) {
-        FmmArgs b = a;
-        b.lt.L = d;
-        hipLaunchKernelGGL(k_p2p2d_f64, grid, dim3(256), 0, st, b, 2 * (a.lt.L - d));
-      }
-    }
+  if (!leaf_local) {
+    launch_p2p2d_f64(a, st);
     return;
   }
-  if (leaf_local) {
-    const int tiled = a.lt.L >= 2 && a.p2p_over ? 1 : 0;
-    if (tiled) {
-      const int64_t tiles = (int64_t)a.lt.nsys << (2 * (a.lt.L - 2));
-      const int cap = p2p2d_tile_cap(a.lt, a.n);
-      const int64_t per = 8 * kXcdChunk;
-      hipLaunchKernelGGL(k_p2p2d_f32_tile, dim3((unsigned)((tiles + per - 1) / per * per)),
-                         dim3(kP2pThreads),
-                         (size_t)(cap + kP2pPad) * sizeof(float4), st, a, cap);
-    }
-    hipLaunchKernelGGL(k_p2p2d_f32, direct_grid(a.n), dim3(256), 0, st, a, tiled, a.pts,
-                       a.leaf_start, 0);
-  } else {
-    hipLaunchKernelGGL(k_p2p2d_f64, grid, dim3(256), 0, st, a, 0);
+  const dim3 direct = chunked_grid((a.n + 255) / 256);
+  if (a.depth) {
+    // the direct kernel for depth L and one launch for every shallower depth
+    hipLaunchKernelGGL(k_p2p2d_f32, direct, dim3(256), 0, st, a, 0, a.pts, a.leaf_start, 0);
+    if (a.lt.L > a.lt.kmin)
+      hipLaunchKernelGGL(k_p2p2d_f32_shallow, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0,
+                         st, a);
+    return;
   }
+  const int tiled = a.lt.L >= 2 && a.p2p_over ? 1 : 0;
+  if (tiled) {
+    const int64_t tiles = (int64_t)a.lt.nsys << (2 * (a.lt.L - 2));
+    const int cap = p2p2d_tile_cap(a.lt, a.n, 2048);
+    hipLaunchKernelGGL(k_p2p2d_f32_tile, chunked_grid(tiles), dim3(kP2pThreads),
+                       (size_t)(cap + kP2pPad) * sizeof(float4), st, a, cap);
+  }
+  hipLaunchKernelGGL(k_p2p2d_f32, direct, dim3(256), 0, st, a, tiled, a.pts, a.leaf_start, 0);
 }
 
 }  // namespace sffmm

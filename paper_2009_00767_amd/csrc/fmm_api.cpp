@@ -414,15 +414,15 @@ int fmm_plan(const fmm_options* opt, fmm_plan_t* out) {
   if (pl->f32) {
     rc |= dalloc(pl, &pl->pts, N);
     rc |= dalloc(pl, &pl->pts_alt, N);
-    // one flag per 4 x 4-leaf tile of the deepest tree (of every system)
-    if (dim == 2 && pl->lcap >= 2)
-      rc |= dalloc(pl, &pl->p2p_over, (size_t)nsysmax << (2 * (pl->lcap - 2)));
   } else {
     rc |= dalloc(pl, &pl->xs, N);
     rc |= dalloc(pl, &pl->ys, N);
     if (dim == 3) rc |= dalloc(pl, &pl->zs, N);
     rc |= dalloc(pl, &pl->qs, N);
   }
+  // one flag per 4 x 4-leaf tile of the deepest tree (of every system)
+  if (dim == 2 && pl->lcap >= 2)
+    rc |= dalloc(pl, &pl->p2p_over, (size_t)nsysmax << (2 * (pl->lcap - 2)));
   rc |= dalloc(pl, &pl->mom64, (size_t)(pl->nbox64 * pl->cs));
   rc |= dalloc(pl, &pl->loc64, (size_t)(pl->nbox64 * pl->cs));
   rc |= dalloc(pl, &pl->mom32, (size_t)(pl->nbox32 * pl->cs));

@@ -172,7 +172,7 @@ struct FmmArgs {
   double* near_ey;
   double* near_ez;
   double* m2l_part;      // 3D M2L: partial sums of the split small levels (m2l3d_partial_entries)
-  uint8_t* p2p_over;     // 2D FP32 near field: per 4 x 4-leaf tile, halo too large to stage
+  uint8_t* p2p_over;     // 2D near field: per 4 x 4-leaf tile, halo too large to stage
   double* pot;           // caller output (input order)
   double* field;         // caller output or NULL
   const BatchIo* io;     // batched graphs: the outputs come from this record instead

@@ -1,0 +1,324 @@
+// p2p2d_f64.hip -- the FP64 near field of the 2D log kernel (E-2 of Section
+// 2.1), in sorted order (the local evaluation adds the far field and scatters
+// back to input order).  Sources of a target: its leaf and the adjacent ones;
+// pairs with r = 0 (the target itself, coincident points) contribute nothing.
+//
+// What bounds it: vector issue.  A pair needs log r^2 and 1 / r^2 in FP64;
+// with the library's log and a correctly rounded division it took about 117
+// issue slots.  Here it takes about 30: the reciprocal is the hardware
+// estimate with one third-order step, and the logarithm comes from a table in
+// LDS.  Measured (MI355X): 1.8e9 pairs of a 500,009-particle mixture (level 8,
+// dense leaves, direct form) 4.5 -> 1.45 ms, 1.27e12 pairs/s; 2^20 uniform
+// particles at level 8 (tile form, beside the moments) 0.90 -> 0.35 ms; 4096
+// particles at level 4 (sixteen lanes a target instead of one: 64 waves had
+// left the chip idle) 63 -> 12 us.
+#include "near2d.h"
+
+namespace sffmm {
+
+namespace {
+
+// log2 of a normal r2 > 0 is the exponent plus log2 of the mantissa m in [1/2,
+// 1), which is T_i + log2(1 + u) with u = m c_i - 1, c_i the reciprocal of the
+// middle of m's interval of width 2^-8 and T_i = -log2 c_i.  |u| <= 2^-8, so
+// the series of log2(1 + u) ends after u^6 (the next term is below 3e-18).
+constexpr int kLogBits = 7;
+constexpr int kLogTable = 1 << kLogBits;
+__device__ __forceinline__ void fill_log_table(double2* tab) {
+  for (int i = threadIdx.x; i < kLogTable; i += blockDim.x) {
+    const double c = 1.0 / (0.5 + ((double)i + 0.5) * (0.5 / kLogTable));
+    tab[i] = make_double2(c, -log2(c));
+  }
+}
+
+// Running sums of a target: log2(r^2) in two parts (the exponents' share is
+// kept apart, so that neither part rounds at the other's magnitude), and the field.
+struct NearSum {
+  double fr = 0.0, ex2 = 0.0, ex = 0.0, ey = 0.0;
+};
+
+// Below thr (0 < r2 < 2^-900, or any r2 of a box too large for the reciprocal)
+// a pair takes the library's functions.
+__device__ __forceinline__ double near_threshold(double side) {
+  return side < 0x1p400 ? 0x1p-900 : __builtin_inf();
+}
+
+// U sources at once: the tests for r = 0 and for r^2 out of range cost one
+// compare a pair; what they guard is left out unless some lane needs it.
+template <int U>
+__device__ __forceinline__ void pairs2_f64(double x, double y, const double (&sx)[U],
+                                           const double (&sy)[U], double (&q)[U], double thr,
+                                           const double2* tab, NearSum& a) {
+  double dx[U], dy[U], r2[U];
+  bool odd = false;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    dx[u] = x - sx[u];
+    dy[u] = y - sy[u];
+    r2[u] = fma(dx[u], dx[u], dy[u] * dy[u]);
+    odd = odd || !(r2[u] >= thr);
+  }
+  if (__any(odd)) {
+    bool far_off = false;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool zero = r2[u] == 0.0;
+      r2[u] = zero ? 1.0 : r2[u];
+      q[u] = zero ? 0.0 : q[u];
+      far_off = far_off || (!zero && !(r2[u] >= thr));
+    }
+    if (__any(far_off)) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        a.fr += q[u] * log2(r2[u]);
+        const double w = q[u] / r2[u];
+        a.ex -= w * dx[u];
+        a.ey -= w * dy[u];
+      }
+      return;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const uint32_t hi = (uint32_t)__double2hiint(r2[u]);
+    const double2 t = tab[(hi >> (20 - kLogBits)) & (kLogTable - 1)];
+    const double m = __hiloint2double((int)((hi & 0xFFFFFu) | 0x3FE00000u), __double2loint(r2[u]));
+    const double ef = (double)((int)(hi >> 20) - 1022);
+    double y0 = __builtin_amdgcn_rcp(r2[u]);  // relative error e at most about 2^-24
+    const double e = fma(-r2[u], y0, 1.0);
+    y0 = fma(y0, fma(e, e, e), y0);  // 1 / r2 = y0 / (1 - e) = y0 (1 + e + e^2 + ...)
+    const double w = q[u] * y0;
+    const double v = fma(m, t.x, -1.0);
+    double p = fma(v, -0.24044917348149390, 0.28853900817779268);  // (-1)^(k+1) / (k ln 2)
+    p = fma(p, v, -0.36067376022224085);
+    p = fma(p, v, 0.48089834696298780);
+    p = fma(p, v, -0.72134752044448170);
+    p = fma(p, v, 1.4426950408889634);
+    a.fr = fma(q[u], fma(p, v, t.y), a.fr);
+    a.ex2 = fma(q[u], ef, a.ex2);
+    a.ex = fma(-w, dx[u], a.ex);
+    a.ey = fma(-w, dy[u], a.ey);
+  }
+}
+
+__device__ __forceinline__ void store_near(const FmmArgs& a, int64_t j, const NearSum& s) {
+  a.near_pot[j] = (s.fr + s.ex2) * 0.34657359027997264;  // (ln 2) / 2: log r = log2(r^2) ln2 / 2
+  a.near_ex[j] = s.ex;
+  a.near_ey[j] = s.ey;
+}
+
+// Sources i0 + P k (k = 0, 1, ...) below i1 in batches of four; the last batch
+// repeats its first source with no charge.
+template <int P>
+__device__ __forceinline__ void range2_f64(const double* __restrict__ xs,
+                                           const double* __restrict__ ys,
+                                           const double* __restrict__ qs, int32_t i0, int32_t i1,
+                                           double x, double y, double thr, const double2* tab,
+                                           NearSum& s) {
+  int32_t i = i0;
+  for (; i + 3 * P < i1; i += 4 * P) {
+    double sx[4], sy[4], q[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      sx[u] = xs[i + u * P];
+      sy[u] = ys[i + u * P];
+      q[u] = qs[i + u * P];
+    }
+    pairs2_f64<4>(x, y, sx, sy, q, thr, tab, s);
+  }
+  if (i < i1) {
+    double sx[4], sy[4], q[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool in = i + u * P < i1;
+      const int32_t iu = in ? i + u * P : i;
+      sx[u] = xs[iu];
+      sy[u] = ys[iu];
+      q[u] = in ? qs[iu] : 0.0;
+    }
+    pairs2_f64<4>(x, y, sx, sy, q, thr, tab, s);
+  }
+}
+
+// Direct form.  P = 1: one thread per sorted target (walk_near2d; dense leaves
+// share their sources as scalar loads).  P > 1 (few targets for the chip): P
+// neighbouring lanes share a target, lane r taking every P-th source of the
+// leaves' sources in a row, and their sums meet in a butterfly.
+// lsh = 2 (L - d) when the launch works at level d = lt.L of an adaptive tree
+// of depth L: leaf keys and leaf offsets are those of level d, and only the
+// targets whose leaf lies at level d are taken.
+// over: only the targets of tiles the tile kernel left.
+template <int P>
+__global__ __launch_bounds__(256) void k_p2p2d_f64(FmmArgs a, int over,
+                                                   const double* __restrict__ xs,
+                                                   const double* __restrict__ ys,
+                                                   const double* __restrict__ qs,
+                                                   const int32_t* __restrict__ leaf_start,
+                                                   int lsh) {
+  __shared__ double2 tab[kLogTable];
+  const int64_t t = xcd_chunk_remap(blockIdx.x) * 256 + threadIdx.x;
+  const int64_t j = t / P;
+  const LevelTable& lt = a.lt;
+  bool mine = j < a.n && (!a.depth || a.depth[j] == lt.L);
+  const uint32_t key = mine ? a.keys[j] >> lsh : 0u;
+  if (over) mine = mine && a.p2p_over[key >> 4];
+  if (!__syncthreads_or(mine)) return;
+  fill_log_table(tab);
+  __syncthreads();
+  if (!mine) return;
+  const double thr = near_threshold(lt.side);
+  const double x = xs[j], y = ys[j];
+  NearSum s;
+  if constexpr (P == 1) {
+    walk_near2d(lt, key, leaf_start, lsh, [&](int32_t i0, int32_t i1, int, int) {
+      range2_f64<1>(xs, ys, qs, i0, i1, x, y, thr, tab, s);
+    });
+  } else {
+    const uint32_t lmask = local2(0xFFFFFFFFu, lt.L), sysbits = key & ~lmask;
+    const int lx = (int)compact2(key & lmask), ly = (int)compact2((key & lmask) >> 1);
+    const int nl = 1 << lt.L;
+    int32_t i0[9], i1[9];
+#pragma unroll
+    for (int b = 0; b < 9; ++b) {  // every range up front: the loads overlap
+      const int nx = lx - 1 + b % 3, ny = ly - 1 + b / 3;
+      const bool in = nx >= 0 && nx < nl && ny >= 0 && ny < nl;
+      const int64_t nk = in ? (int64_t)(sysbits | spread2(nx) | (spread2(ny) << 1)) : 0;
+      i0[b] = in ? leaf_start[nk << lsh] : 0;
+      i1[b] = in ? leaf_start[(nk + 1) << lsh] : 0;
+    }
+    int32_t off = (int32_t)(t % P);  // this lane's first source of the next leaf
+#pragma unroll
+    for (int b = 0; b < 9; ++b) {
+      const int32_t len = i1[b] - i0[b];
+      range2_f64<P>(xs, ys, qs, i0[b] + off, i1[b], x, y, thr, tab, s);
+      const int32_t left = len - off;  // sources from this lane's first one on
+      off = left > 0 ? (P - left % P) % P : -left;
+    }
+#pragma unroll
+    for (int d = 1; d < P; d <<= 1) {
+      s.fr += __shfl_xor(s.fr, d, 64);
+      s.ex2 += __shfl_xor(s.ex2, d, 64);
+      s.ex += __shfl_xor(s.ex, d, 64);
+      s.ey += __shfl_xor(s.ey, d, 64);
+    }
+    if (t % P != 0) return;
+  }
+  store_near(a, j, s);
+}
+
+// Tile form: a workgroup stages the sources of a 4 x 4-leaf tile's 6 x 6-leaf
+// halo in LDS, halo rows contiguous, so that a target's nine leaves are three
+// spans.  P lanes share a target (its spans' sources dealt round): a wave then
+// holds 64 / P targets of one or two leaves, whose spans hardly differ in
+// length.  Tiles whose halo exceeds the stage are flagged and left to the
+// direct kernel.
+constexpr int kTile64P = 4;
+constexpr int kTile64Cap = 1536;  // records of 24 bytes
+constexpr int kTile64Pad = 4 * kTile64P;
+
+__global__ __launch_bounds__(256) void k_p2p2d_f64_tile(FmmArgs a, int cap) {
+  constexpr int P = kTile64P;
+  extern __shared__ double2 sxy[];  // cap + pad positions, then as many charges
+  __shared__ double2 tab[kLogTable];
+  __shared__ int32_t hstart[kP2pHaloLeaves];
+  __shared__ int32_t hoff[kP2pHaloLeaves + 1];
+  double* sq = reinterpret_cast<double*>(sxy + cap + kTile64Pad);
+  const LevelTable& lt = a.lt;
+  const int L = lt.L, tid = threadIdx.x;
+  const int64_t tl = xcd_chunk_remap(blockIdx.x);
+  if (tl >= ((int64_t)lt.nsys << (2 * (L - 2)))) return;  // grid padding (workgroup-uniform)
+  const uint32_t tile = (uint32_t)tl, k0 = tile << 4;
+  const uint32_t tm = local2(k0, L);
+  const int bx0 = (int)compact2(tm), by0 = (int)compact2(tm >> 1);
+  fill_log_table(tab);
+  tile_halo(lt, a.leaf_start, tile, hstart, hoff);
+  const int total = hoff[kP2pHaloLeaves];
+  if (tid == 0) a.p2p_over[tile] = total > cap ? 1 : 0;
+  if (total > cap) return;  // workgroup-uniform
+  for (int e = tid; e < total; e += 256) {
+    const int h = halo_leaf(hoff, e);
+    const int32_t i = hstart[h] + (e - hoff[h]);
+    sxy[e] = make_double2(a.xs[i], a.ys[i]);
+    sq[e] = a.qs[i];
+  }
+  if (tid < kTile64Pad) {
+    sxy[total + tid] = make_double2(0.0, 0.0);
+    sq[total + tid] = 0.0;
+  }
+  __syncthreads();
+  const int32_t t0 = a.leaf_start[k0], t1 = a.leaf_start[k0 + 16];
+  const double thr = near_threshold(lt.side);
+  const int part = tid % P;
+  for (int32_t j = t0 + tid / P; j < t1; j += 256 / P) {
+    const uint32_t key = local2(a.keys[j], L);
+    const int tx = (int)compact2(key) - bx0, ty = (int)compact2(key >> 1) - by0;
+    const double x = a.xs[j], y = a.ys[j];
+    NearSum s;
+#pragma unroll 1
+    for (int dy = 0; dy < 3; ++dy) {
+      const int h = (ty + dy) * kP2pHalo + tx;  // halo leaves h, h + 1, h + 2
+      const int c1 = hoff[h + 3];
+      // (reads past the span stay below total + pad; they carry no charge)
+      for (int c = hoff[h] + part; c < c1; c += 4 * P) {
+        double sx[4], sy[4], q[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const double2 p = sxy[c + u * P];
+          sx[u] = p.x;
+          sy[u] = p.y;
+          q[u] = c + u * P < c1 ? sq[c + u * P] : 0.0;
+        }
+        pairs2_f64<4>(x, y, sx, sy, q, thr, tab, s);
+      }
+    }
+#pragma unroll
+    for (int d = 1; d < P; d <<= 1) {
+      s.fr += __shfl_xor(s.fr, d, 64);
+      s.ex2 += __shfl_xor(s.ex2, d, 64);
+      s.ex += __shfl_xor(s.ex, d, 64);
+      s.ey += __shfl_xor(s.ey, d, 64);
+    }
+    if (part == 0) store_near(a, j, s);
+  }
+}
+
+template <int P>
+void direct_f64(const FmmArgs& a, int over, int lsh, hipStream_t st) {
+  hipLaunchKernelGGL(k_p2p2d_f64<P>, chunked_grid((a.n * P + 255) / 256), dim3(256), 0, st, a, over,
+                     a.xs, a.ys, a.qs, a.leaf_start, lsh);
+}
+
+}  // namespace
+
+void launch_p2p2d_f64(const FmmArgs& a, hipStream_t st) {
+  if (a.n <= 0) return;
+  if (a.depth) {
+    // the uniform near field of depth d for the targets whose depth is d (the
+    // others leave at once), one launch per level
+    for (int d = a.lt.kmin; d <= a.lt.L; ++d) {
+      FmmArgs b = a;
+      b.lt.L = d;
+      direct_f64<1>(b, 0, 2 * (a.lt.L - d), st);
+    }
+    return;
+  }
+  // Tiles from 1024 of them on (four workgroups a CU).  Below that the chip
+  // wants more threads than targets: sixteen lanes a target up to 2^14 targets
+  // and four up to 2^16 give it at least one wave a SIMD (4096 targets: 63 us
+  // with one lane, 12 with sixteen; 20,011: 76 and 18).
+  const int64_t tiles = a.lt.L >= 2 && a.p2p_over ? (int64_t)a.lt.nsys << (2 * (a.lt.L - 2)) : 0;
+  if (tiles >= 1024) {
+    const int cap = p2p2d_tile_cap(a.lt, a.n, kTile64Cap);
+    hipLaunchKernelGGL(k_p2p2d_f64_tile, chunked_grid(tiles), dim3(256),
+                       (size_t)(cap + kTile64Pad) * 3 * sizeof(double), st, a, cap);
+    direct_f64<1>(a, 1, 0, st);
+  } else if (a.n * 16 <= (1 << 18)) {
+    direct_f64<16>(a, 0, 0, st);
+  } else if (a.n * 4 <= (1 << 18)) {
+    direct_f64<4>(a, 0, 0, st);
+  } else {
+    direct_f64<1>(a, 0, 0, st);
+  }
+}
+
+}  // namespace sffmm
