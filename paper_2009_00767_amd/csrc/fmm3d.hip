@@ -399,43 +399,56 @@ void launch_l2p3d(const FmmArgs& a, bool leaf_local, hipStream_t st) {
 // r = 0 (the target itself, coincident points) contribute nothing.
 // phi += q / r,  field += q (x_t - x_s) / r^3.
 // ---------------------------------------------------------------------------
-// 1 / sqrt(x) for normal x > 0: the hardware estimate refined by two
-// Newton-Raphson steps for f(y) = 1/y^2 - x, y <- y + y (1 - x y^2) / 2; each
-// step squares the relative error, which ends within a few units in the last
-// place (instead of a correctly rounded square root and division).
-__device__ __forceinline__ double rsqrt_nr(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const double e = fma(-x * y, y, 1.0);
-    y = fma(0.5 * y, e, y);
-  }
-  return y;
+// 1 / sqrt(x) for normal x > 0: the hardware estimate y (relative error at most
+// 2^-24.2, measured) times the series of (1 - e)^(-1/2), e = 1 - x y^2, up to
+// e^2; what is left, 5/16 e^3, lies far below an FP64 rounding.
+__device__ __forceinline__ double rsqrt_3rd(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-// One source.  r^2 is formed on a floor, fma(dx, dx, fma(dy, dy, fma(dz, dz,
-// 2^-400))), which keeps 1 / sqrt finite at r = 0, and the charge of a pair at
-// r = 0 is taken as zero by a select (a branch per pair costs more); for real
-// pairs the floor changes r^2 by 2^-400 / r^2.
+// One source.  APART: r is known not to vanish (apart3).  Else r^2 is formed on
+// a floor, fma(dx, dx, fma(dy, dy, fma(dz, dz, 2^-400))), which keeps 1 / sqrt
+// finite at r = 0, and the charge of a pair at r = 0 is taken as zero by a select
+// (a branch per pair costs more); for real pairs the floor changes r^2 by
+// 2^-400 / r^2.
+// Bound by vector issue: 22 instructions a pair with the select and 19 without
+// (26 with two Newton steps for the root), one of them, the estimate, four
+// times as long as the others.  With the even slices below, the paper's
+// 200k-particle level-3 run takes 1.83 -> 1.41 ms, at 1.2e12 pairs/s.
 constexpr double kP2p3Eps = 0x1p-400;
+template <bool APART>
 __device__ __forceinline__ void pair3_f64(double x, double y, double z, double sx, double sy,
                                           double sz, double sq, double& phi, double& ex,
                                           double& ey, double& ez) {
   const double dx = x - sx, dy = y - sy, dz = z - sz;
   const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, kP2p3Eps)));
-  const double rinv = rsqrt_nr(r2);
-  const double qr = (r2 > kP2p3Eps ? sq : 0.0) * rinv;
+  const double rinv = rsqrt_3rd(r2);
+  const double qr = (APART || r2 > kP2p3Eps ? sq : 0.0) * rinv;
   phi += qr;
   const double w = qr * rinv * rinv;
-  ex += w * dx;
-  ey += w * dy;
-  ez += w * dz;
+  ex = fma(w, dx, ex);
+  ey = fma(w, dy, ey);
+  ez = fma(w, dz, ez);
+}
+
+// Whether this target keeps apart from every source outside its leaf: it lies
+// 2^-40 of the box side inside its leaf's faces (leaf coordinates round at about
+// 2^-52 of it), and the square of that distance lies above the floor.
+__device__ __forceinline__ bool apart3(const LevelTable& lt, int lx, int ly, int lz, double x,
+                                       double y, double z) {
+  const double m = 0x1p-40 * lt.side, s = lt.s[lt.L];
+  const double rx = x - (lt.origin[0] + s * lx), ry = y - (lt.origin[1] + s * ly),
+               rz = z - (lt.origin[2] + s * lz);
+  return m > 0x1p-150 && rx > m && ry > m && rz > m && s - rx > m && s - ry > m && s - rz > m;
 }
 
 // PARTS > 1 (few particles for the chip): PARTS waves per 64 targets (a
-// workgroup of 64 PARTS threads), wave w walking the in-domain neighbour leaves
-// w, w + PARTS, ... of the 27; the partial sums meet in LDS and are added in
-// wave order.  PARTS = 1: 256 targets per workgroup.
+// workgroup of 64 PARTS threads), wave w walking its share of the sources (FP64:
+// a slice of every leaf, walk_near3; FP32: the in-domain neighbour leaves w, w +
+// PARTS, ... of the 27); the partial sums meet in LDS and are added in wave
+// order.  PARTS = 1: 256 targets per workgroup.
 template <int PARTS>
 constexpr int p2p3_threads() {
   return PARTS == 1 ? 256 : 64 * PARTS;
@@ -484,9 +497,11 @@ __device__ __forceinline__ void p2p3_range_f64(const FmmArgs& a, int32_t i0, int
       sq[u] = a.qs[i + u];
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) pair3_f64(x, y, z, sx[u], sy[u], sz[u], sq[u], phi, ex, ey, ez);
+    for (int u = 0; u < 4; ++u)
+      pair3_f64<false>(x, y, z, sx[u], sy[u], sz[u], sq[u], phi, ex, ey, ez);
   }
-  for (; i < i1; ++i) pair3_f64(x, y, z, a.xs[i], a.ys[i], a.zs[i], a.qs[i], phi, ex, ey, ez);
+  for (; i < i1; ++i)
+    pair3_f64<false>(x, y, z, a.xs[i], a.ys[i], a.zs[i], a.qs[i], phi, ex, ey, ez);
 }
 
 // Orders the LDS accesses of one wave whose lanes read what other lanes wrote:
@@ -502,6 +517,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 // stage (x, y in the first 64 slots, z, q in the next 64), and every lane reads
 // them back from there (one address for the whole wave), instead of four 8-byte
 // vector loads per source and pair.  The order of the sums is unchanged.
+template <bool APART>
 __device__ __forceinline__ void p2p3_range_f64_staged(const FmmArgs& a, int32_t i0, int32_t i1,
                                                       double x, double y, double z,
                                                       double2* stage, int lane, double& phi,
@@ -527,13 +543,36 @@ __device__ __forceinline__ void p2p3_range_f64_staged(const FmmArgs& a, int32_t 
       }
 #pragma unroll
       for (int w = 0; w < 4; ++w)
-        pair3_f64(x, y, z, su[w].x, su[w].y, sv[w].x, sv[w].y, phi, ex, ey, ez);
+        pair3_f64<APART>(x, y, z, su[w].x, su[w].y, sv[w].x, sv[w].y, phi, ex, ey, ez);
     }
     for (; s < m; ++s) {
       const double2 su = stage[s], sv = stage[64 + s];
-      pair3_f64(x, y, z, su.x, su.y, sv.x, sv.y, phi, ex, ey, ez);
+      pair3_f64<APART>(x, y, z, su.x, su.y, sv.x, sv.y, phi, ex, ey, ez);
     }
   }
+}
+
+// Calls f(i0, i1, own) for this part's slice of the sorted range of each in-domain
+// leaf of the 27 around leaf `key` (own: that leaf itself).  Every part takes
+// 1 / PARTS of every leaf, cut at multiples of four sources: the parts of 64
+// targets end together (with whole leaves dealt out, 27 over eight parts, some
+// had four and some three: 1.54 -> 1.41 ms on the paper's 200k-particle run).
+template <int PARTS, class F>
+__device__ __forceinline__ void walk_near3(const FmmArgs& a, uint32_t key, int part, F&& f) {
+  const int lx = (int)compact3(key), ly = (int)compact3(key >> 1), lz = (int)compact3(key >> 2);
+  const int nl = 1 << a.lt.L;
+  for (int nz = max(lz - 1, 0); nz <= min(lz + 1, nl - 1); ++nz)
+    for (int ny = max(ly - 1, 0); ny <= min(ly + 1, nl - 1); ++ny)
+      for (int nx = max(lx - 1, 0); nx <= min(lx + 1, nl - 1); ++nx) {
+        const uint32_t nk = spread3(nx) | (spread3(ny) << 1) | (spread3(nz) << 2);
+        int32_t i0 = a.leaf_start[nk], i1 = a.leaf_start[nk + 1];
+        if (PARTS > 1) {
+          const int64_t len = i1 - i0;
+          if (part < PARTS - 1) i1 = i0 + ((int32_t)(len * (part + 1) / PARTS) & ~3);
+          i0 += (int32_t)(len * part / PARTS) & ~3;
+        }
+        f(i0, i1, nk == key);
+      }
 }
 
 // A wave whose 64 targets lie in one leaf walks the sources through its LDS stage.
@@ -552,26 +591,22 @@ __global__ __launch_bounds__(p2p3_threads<PARTS>()) void k_p2p3d_f64(FmmArgs a) 
   const int lane = threadIdx.x & 63;
   double phi = 0.0, ex = 0.0, ey = 0.0, ez = 0.0;
   if (live) {
-    const int L = a.lt.L;
-    const int lx = (int)compact3(key), ly = (int)compact3(key >> 1), lz = (int)compact3(key >> 2);
-    const int nl = 1 << L;
     const double x = a.xs[j], y = a.ys[j], z = a.zs[j];
-    int nbr = 0;
-    for (int nz = lz - 1; nz <= lz + 1; ++nz) {
-      if (nz < 0 || nz >= nl) continue;
-      for (int ny = ly - 1; ny <= ly + 1; ++ny) {
-        if (ny < 0 || ny >= nl) continue;
-        for (int nx = lx - 1; nx <= lx + 1; ++nx) {
-          if (nx < 0 || nx >= nl) continue;
-          if (PARTS > 1 && nbr++ % PARTS != part) continue;
-          const uint32_t nk = spread3(nx) | (spread3(ny) << 1) | (spread3(nz) << 2);
-          const int32_t i0 = a.leaf_start[nk], i1 = a.leaf_start[nk + 1];
-          if (uni)
-            p2p3_range_f64_staged(a, i0, i1, x, y, z, wstage, lane, phi, ex, ey, ez);
-          else
-            p2p3_range_f64(a, i0, i1, x, y, z, phi, ex, ey, ez);
-        }
-      }
+    if (uni) {
+      // the leaf in a scalar register: ranges, bounds and branches stay scalar
+      const bool apart = __all(apart3(a.lt, (int)compact3(k0), (int)compact3(k0 >> 1),
+                                     (int)compact3(k0 >> 2), x, y, z));
+      walk_near3<PARTS>(a, k0, __builtin_amdgcn_readfirstlane(part),
+                        [&](int32_t i0, int32_t i1, bool own) {
+        if (apart && !own)
+          p2p3_range_f64_staged<true>(a, i0, i1, x, y, z, wstage, lane, phi, ex, ey, ez);
+        else
+          p2p3_range_f64_staged<false>(a, i0, i1, x, y, z, wstage, lane, phi, ex, ey, ez);
+      });
+    } else {
+      walk_near3<PARTS>(a, key, part, [&](int32_t i0, int32_t i1, bool) {
+        p2p3_range_f64(a, i0, i1, x, y, z, phi, ex, ey, ez);
+      });
     }
   }
   p2p3d_finish<PARTS>(a, j, live, phi, ex, ey, ez);
