@@ -1303,13 +1303,15 @@ int fmm_mlp_forward(const float* w, const float* x, int64_t m, float* y, void* s
 }
 
 namespace {
+std::mutex g_mlp_mu;  // the order network's partial-sum array of every device
+
 struct MlpScratch {
   float* part = nullptr;
   double* part_loss = nullptr;
   int alloc(int64_t m) {
-    const int64_t nw = (mlp_grad_waves(m) + 3) / 4 * 4 + 4;
-    if (hipMalloc(&part, sizeof(float) * (size_t)nw * FMM_MLP_NPARAM) != hipSuccess ||
-        hipMalloc(&part_loss, sizeof(double) * (size_t)nw) != hipSuccess) {
+    const size_t nb = (size_t)std::max<int64_t>(mlp_grad_blocks(m), 1);
+    if (hipMalloc(&part, sizeof(float) * nb * FMM_MLP_NPARAM) != hipSuccess ||
+        hipMalloc(&part_loss, sizeof(double) * nb) != hipSuccess) {
       (void)hipGetLastError();
       return FMM_ERR_NOMEM;
     }
@@ -1326,12 +1328,16 @@ struct MlpScratch {
 int fmm_mlp_loss_grad(const float* w, const float* x, const float* t, int64_t m, float* grad,
                       float* loss, void* stream) {
   if (m < 0 || !w || !grad || (m > 0 && (!x || !t))) return FMM_ERR_INVALID_ARG;
+  // The partial sums live in the device's own array while this call holds the
+  // lock (it ends with the stream idle); a call that comes meanwhile, from
+  // another thread, allocates its own (two allocations and frees cost about 45 us).
   MlpScratch sc;
-  if (sc.alloc(m) != FMM_OK) return FMM_ERR_NOMEM;
+  std::unique_lock<std::mutex> own(g_mlp_mu, std::try_to_lock);
+  if (!own.owns_lock() && sc.alloc(m) != FMM_OK) return FMM_ERR_NOMEM;
   hipStream_t st = static_cast<hipStream_t>(stream);
   launch_mlp_grad(w, x, t, m, sc.part, sc.part_loss, grad, loss, st);
-  if (hipGetLastError() != hipSuccess) return FMM_ERR_DEVICE;
-  return hipStreamSynchronize(st) == hipSuccess ? FMM_OK : FMM_ERR_DEVICE;
+  const bool launched = hipGetLastError() == hipSuccess;
+  return hipStreamSynchronize(st) == hipSuccess && launched ? FMM_OK : FMM_ERR_DEVICE;
 }
 
 int fmm_mlp_adam_step(float* w, const float* grad, float* m1, float* m2, int32_t step, float lr,

@@ -253,9 +253,11 @@ void launch_batch_begin(BatchIo* io, const double* pos, const double* q, double*
                         double* field, const int64_t* off, const int32_t* levels,
                         const int64_t* prep_off, const int32_t* prep_info, int nsys, int lmax,
                         int32_t* flag, int32_t tag, hipStream_t st);
-int64_t mlp_grad_waves(int64_t m);
+// workgroups (partial gradients) of a batch of m samples: at most 256
+int64_t mlp_grad_blocks(int64_t m);
 void launch_mlp_forward(const float* w, const float* x, int64_t m, float* y, hipStream_t st);
-// part: [round_up(mlp_grad_waves(m), 4)][FMM_MLP_NPARAM], part_loss the same count
+// part: [mlp_grad_blocks(m)][FMM_MLP_NPARAM], part_loss the same count; part NULL:
+// the device's own array of that size, which serves one gradient at a time
 void launch_mlp_grad(const float* w, const float* x, const float* t, int64_t m, float* part,
                      double* part_loss, float* grad, float* loss, hipStream_t st);
 void launch_mlp_adam(float* w, const float* g, float* m1, float* m2, int step, float lr,

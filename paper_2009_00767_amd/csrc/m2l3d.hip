@@ -239,6 +239,24 @@ __global__ __launch_bounds__(64 * NW) void k_m2l3d_mfma(FmmArgs a, M2l3Tiles tt,
       for (int m = 0; m < MB; ++m) SFFMM_LOADA(q, tzm[m], av[m], a0[m]);
     }
     const T* Wl = cur;
+#ifdef V_NBIN
+    if constexpr (true) {
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          const T wv = Wl[((size_t)nb * (KS + 1) + s) * 64 + lane];
+#pragma unroll
+          for (int m = 0; m < MB; ++m) acc[m][nb] = Mfma16x<T>::op(av[m][s], wv, (s == 0 && !kF64) ? acc_t{0,0,0,0} : acc[m][nb]);
+        }
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const T wv = Wl[((size_t)nb * (KS + 1) + KS) * 64 + lane];
+#pragma unroll
+        for (int m = 0; m < MB; ++m) acc[m][nb] = Mfma16x<T>::op(g == 0 ? a0[m] : (T)0, wv, acc[m][nb]);
+      }
+    } else
+#endif
     if constexpr (KS == 32) {
       // one layer per wave and one wave per SIMD: the NB output blocks in the
       // inner loop, so consecutive products go to independent accumulators
@@ -284,7 +302,9 @@ __global__ __launch_bounds__(64 * NW) void k_m2l3d_mfma(FmmArgs a, M2l3Tiles tt,
         for (int nb = 0; nb < NB; ++nb) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) sum[m][nb][r] += (double)acc[m][nb][r];
+#ifndef V_NBIN
           acc[m][nb] = acc_t{0, 0, 0, 0};
+#endif
         }
     }
     if constexpr (!kDB) __syncthreads();  // every wave done with the one buffer
