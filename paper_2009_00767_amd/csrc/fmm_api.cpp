@@ -612,7 +612,8 @@ struct TreeRun {
   int64_t leaf0 = 0;            // first leaf_start entry
   int64_t box64 = 0, box32 = 0; // first box in the FP64 / FP32 coefficient arrays
   int64_t part64 = 0, part32 = 0;
-  bool leaves_done = false;     // the sort already wrote the leaf offsets
+  bool sorted = false;          // the sort already wrote the leaf offsets (and in FP64 mode the
+                                // sorted coordinates)
 };
 
 // Enqueues everything after the sort for one tree: leaf offsets, gather, then
@@ -627,10 +628,10 @@ void enqueue_tree(fmm_plan_s* pl, const TreeRun& t, const uint32_t* skeys, const
   const int64_t nleaf = (int64_t)lt.nsys << (pl->dim * lt.L);
   const uint32_t* keys = skeys + t.p0;
   const int32_t* pm = perm + t.p0;
-  if (!t.leaves_done) launch_leaf_bounds(keys, t.n, nleaf, pl->leaf_start + t.leaf0, st);
+  if (!t.sorted) launch_leaf_bounds(keys, t.n, nleaf, pl->leaf_start + t.leaf0, st);
   // FP32 modes: the sorted leaf-local records came with the sort (spts);
   // FP64 mode gathers the sorted coordinates and charges
-  if (!pl->f32)
+  if (!pl->f32 && !t.sorted)
     launch_gather_f64(pl->dim, pos, q, pm, t.n, pl->xs + t.p0, pl->ys + t.p0,
                       pl->zs ? pl->zs + t.p0 : nullptr, pl->qs + t.p0, st, io);
   if (ev && (pl->ev_mask >> 1 & 1)) (void)hipEventRecord(ev[1], st);
@@ -971,18 +972,23 @@ int fmm_eval(fmm_plan_t pl, int64_t n, const double* pos, const double* q, doubl
   if (timing && (pl->ev_mask & 1)) (void)hipEventRecord(ev[0], st);
 
   const int bits = pl->dim * pl->L;
-  const bool two_digit = pl->radix_parts && radix_two_digit(n, bits);
-  launch_bin(pl->dim, pos, n, pl->lt, pl->keys, pl->vals, pl->flag, pl->tag, pl->hist, st, q,
-             pl->f32 ? pl->pts : nullptr, two_digit ? 8 : 0);
+  const bool one = sort_in_one(n, bits);
+  const bool two_digit = !one && pl->radix_parts && radix_two_digit(n, bits);
   int which = 0;
-  if (two_digit)
-    radix_sort_two_digit(pl->keys, pl->vals, pl->keys_alt, pl->vals_alt, n, bits, pl->hist,
-                         pl->radix_tot, pl->leaf_start, (int64_t)1 << bits, pl->radix_parts, st,
-                         pl->f32 ? pl->pts : nullptr, pl->f32 ? pl->pts_alt : nullptr);
-  else
-    which = radix_sort(pl->keys, pl->vals, pl->keys_alt, pl->vals_alt, n, bits, pl->hist,
-                       pl->radix_tot, st, true, pl->f32 ? pl->pts : nullptr,
-                       pl->f32 ? pl->pts_alt : nullptr);
+  if (one) {
+    launch_sort_one(pl->dim, pos, q, n, pl->lt, bits, pl->keys, pl->vals, pl->flag, pl->tag,
+                    pl->leaf_start, pl->pts, pl->xs, pl->ys, pl->zs, pl->qs, st);
+  } else {
+    launch_bin(pl->dim, pos, n, pl->lt, pl->keys, pl->vals, pl->flag, pl->tag, pl->hist, st, q,
+               pl->pts, two_digit ? bits - 8 : 0);
+    if (two_digit)
+      radix_sort_two_digit(pl->keys, pl->vals, pl->keys_alt, pl->vals_alt, n, bits, pl->hist,
+                           pl->radix_tot, pl->leaf_start, pl->radix_parts, st, pl->pts,
+                           pl->pts_alt, pl->dim, pos, q, pl->xs, pl->ys, pl->zs, pl->qs);
+    else
+      which = radix_sort(pl->keys, pl->vals, pl->keys_alt, pl->vals_alt, n, bits, pl->hist,
+                         pl->radix_tot, st, true, pl->pts, pl->pts_alt);
+  }
   const float4* spts = pl->f32 ? (which ? pl->pts_alt : pl->pts) : nullptr;
   const uint32_t* skeys = which ? pl->keys_alt : pl->keys;
   const int32_t* perm = which ? pl->vals_alt : pl->vals;
@@ -1004,7 +1010,7 @@ int fmm_eval(fmm_plan_t pl, int64_t n, const double* pos, const double* q, doubl
   TreeRun t;
   t.lt = pl->lt;
   t.n = n;
-  t.leaves_done = two_digit;
+  t.sorted = one || two_digit;
   enqueue_tree(pl, t, skeys, perm, pos, q, pot, field, st, ev, spts);
   if (timing) {
     pl->ring_batched[pl->ring_next] = false;

@@ -104,18 +104,27 @@ int radix_sort(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_
                bool first_hist_done = false, float4* recs = nullptr, float4* recs_alt = nullptr);
 size_t radix_hist_entries(int64_t maxn);
 // Keys of 9..16 bits whose mean high-digit bucket fits the LDS stage: a first
-// pass by the high digit key >> 8 (its tile histograms in hist, from
-// launch_bin with hist_shift = 8), then a stable sort of each bucket by the low 8 bits
-// that also writes leaf_start[0..nleaf] (single system, nleaf = 2^bits).  The
-// result is in keys / vals / recs, the same order as radix_sort's.
+// pass by the high 8 bits, key >> (bits - 8) (their tile histograms in hist,
+// from launch_bin with hist_shift = bits - 8), then a stable sort of each bucket
+// by the bits below that also writes leaf_start[0..2^bits] (single system).
+// The result is in keys / vals / recs, the same order as radix_sort's.
 // parts: radix_two_digit_parts() ints of scratch (digit counts of the parts of
 // buckets beyond the LDS stage).
+// xs .. qs (FP64 mode, else NULL): the sorted coordinates and charges.
 bool radix_two_digit(int64_t n, int bits);
 size_t radix_two_digit_parts();
 void radix_sort_two_digit(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt,
                           int64_t n, int bits, int32_t* hist, int32_t* tot, int32_t* leaf_start,
-                          int64_t nleaf, int32_t* parts, hipStream_t st, float4* recs,
-                          float4* recs_alt);
+                          int32_t* parts, hipStream_t st, float4* recs, float4* recs_alt, int dim,
+                          const double* pos, const double* q, double* xs, double* ys, double* zs,
+                          double* qs);
+// Few particles and keys of few bits: binning, sort, leaf offsets and the
+// sorted records (rec) or coordinates and charges (xs .. qs) in one launch.
+bool sort_in_one(int64_t n, int bits);
+void launch_sort_one(int dim, const double* pos, const double* q, int64_t n, const LevelTable& lt,
+                     int bits, uint32_t* keys, int32_t* vals, int32_t* flag, int32_t tag,
+                     int32_t* leaf_start, float4* rec, double* xs, double* ys, double* zs,
+                     double* qs, hipStream_t st);
 // leaf_start[l] = first sorted position with key >= l, l in [0, nleaf].
 void launch_leaf_bounds(const uint32_t* sorted_keys, int64_t n, int64_t nleaf, int32_t* leaf_start,
                         hipStream_t st);

@@ -222,7 +222,8 @@ extern "C" int fmm_eval_noalloc(const fmm_options* opt, int64_t n, const double*
   int32_t* vals_alt = c.take<int32_t>(n);
   int32_t* hist = c.take<int32_t>(radix_hist_entries(n));
   int32_t* tot = c.take<int32_t>(256);
-  const bool two_digit = bits > 8 && bits <= 16 && radix_two_digit(n, bits);
+  const bool one = sort_in_one(n, bits);
+  const bool two_digit = !one && radix_two_digit(n, bits);
   int32_t* parts = two_digit ? c.take<int32_t>(radix_two_digit_parts()) : nullptr;
   int32_t* leaf_start = c.take<int32_t>(nleaf + 1);
   int32_t* flag = c.take<int32_t>(4);
@@ -265,19 +266,25 @@ extern "C" int fmm_eval_noalloc(const fmm_options* opt, int64_t n, const double*
   launch_fill_i32(reinterpret_cast<int32_t*>(loc32), 0, nbox32 * cs, st);
   hipLaunchKernelGGL(k_build_ops2d, dim3(49), dim3(256), 0, st, ly, p, op64, op32, opl64, opl32);
   const int32_t tag = 1;
-  launch_bin(2, pos, n, lt, keys, vals, flag, tag, hist, st, q, f32 ? pts : nullptr,
-             two_digit ? 8 : 0);
   int which = 0;
-  if (two_digit)
-    radix_sort_two_digit(keys, vals, keys_alt, vals_alt, n, bits, hist, tot, leaf_start, nleaf,
-                         parts, st, f32 ? pts : nullptr, f32 ? pts_alt : nullptr);
-  else
-    which = radix_sort(keys, vals, keys_alt, vals_alt, n, bits, hist, tot, st, true,
-                       f32 ? pts : nullptr, f32 ? pts_alt : nullptr);
+  if (one) {
+    launch_sort_one(2, pos, q, n, lt, bits, keys, vals, flag, tag, leaf_start, pts, xs, ys, nullptr,
+                    qs, st);
+  } else {
+    launch_bin(2, pos, n, lt, keys, vals, flag, tag, hist, st, q, pts, two_digit ? bits - 8 : 0);
+    if (two_digit)
+      radix_sort_two_digit(keys, vals, keys_alt, vals_alt, n, bits, hist, tot, leaf_start, parts,
+                           st, pts, pts_alt, 2, pos, q, xs, ys, nullptr, qs);
+    else
+      which = radix_sort(keys, vals, keys_alt, vals_alt, n, bits, hist, tot, st, true, pts,
+                         pts_alt);
+  }
   const uint32_t* skeys = which ? keys_alt : keys;
   const int32_t* perm = which ? vals_alt : vals;
-  if (!two_digit) launch_leaf_bounds(skeys, n, nleaf, leaf_start, st);
-  if (!f32) launch_gather_f64(2, pos, q, perm, n, xs, ys, nullptr, qs, st);
+  if (!one && !two_digit) {
+    launch_leaf_bounds(skeys, n, nleaf, leaf_start, st);
+    if (!f32) launch_gather_f64(2, pos, q, perm, n, xs, ys, nullptr, qs, st);
+  }
 
   FmmArgs a{};
   a.lt = lt;

@@ -359,24 +359,48 @@ int radix_sort(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_
 }
 
 // ---------------------------------------------------------------------------
-// Keys of 9..16 bits: two digits.  The first pass scatters by the high digit
-// (key >> 8; the binning counted it), which leaves each high digit's elements
-// in one contiguous bucket, in input order; then each bucket is sorted stably
-// by the low 8 bits and the leaf offsets of its 256 keys are written from the
-// same counts, which replaces the second pass's count, scan and scatter and
-// the leaf-offset search.  Two launches share the buckets.  The first has one
-// workgroup per bucket: a bucket that fits the LDS stage is placed there at
-// its final order and written out in one coalesced sweep; for a larger one
-// (clustered inputs) it counts the digits of each of the bucket's
-// kBucketSplit parts into a table.  In the second, the kBucketSplit
-// workgroups of such a bucket each place one part, their digit offsets taken
-// from the table, straight to the final places (the workgroups of the other
-// buckets leave at once).  Inside a workgroup every wave takes a contiguous
-// piece: after one count of each wave's digits and one scan, the waves rank
-// and place their pieces 64 keys at a time with no further barrier (a wave's
-// running digit offsets in LDS, read and advanced in program order).
-constexpr int kBucketCap = 5120;  // elements of a bucket the LDS stage holds
-constexpr int kBucketSplit = 8;   // parts of a bucket beyond the stage
+// Keys of 9..16 bits: two digits.  The first pass scatters by the high 8 bits
+// (key >> lb, lb the bits below; the binning counted them), which leaves each
+// high digit's elements in one contiguous bucket, in input order; then each
+// bucket is sorted stably by its low lb bits and the leaf offsets of its 2^lb
+// keys are written from the same counts, which replaces the second pass's
+// count, scan and scatter and the leaf-offset search.  Two launches share the
+// buckets.  The first has one workgroup per bucket: a bucket that fits the LDS
+// stage is placed there at its final order and written out in one coalesced
+// sweep; for a larger one (clustered inputs) it counts the digits of each of
+// the bucket's kBucketSplit parts into a table.  In the second (left out when n
+// itself fits a stage), the kBucketSplit workgroups of such a bucket each place
+// one part, their digit offsets taken from the table, straight to the final
+// places (the workgroups of the other buckets leave at once).  Inside a
+// workgroup every wave takes a contiguous piece: after one count of each wave's
+// digits and one scan, the waves rank and place their pieces 64 keys at a time
+// with no further barrier (a wave's running digit offsets in LDS, read and
+// advanced in program order).  In FP64 mode the sorted coordinates and charges
+// are gathered in the same sweep.
+constexpr int kBucketCap = 5120;       // elements of a bucket the LDS stage holds
+constexpr int kBucketCapSmall = 1280;  // the same for small n (four waves a bucket)
+constexpr int kBucketSplit = 8;        // parts of a bucket beyond the stage
+
+// Sorted FP64 coordinates and charges of the particle of sorted place `dst`.
+struct GatherOut {
+  const double* pos;
+  const double* q;
+  double* xs;  // NULL: no gather
+  double* ys;
+  double* zs;  // NULL: two dimensions
+  double* qs;
+};
+__device__ __forceinline__ void gather_one(const GatherOut& g, int64_t dst, int32_t i) {
+  if (g.zs) {
+    g.xs[dst] = g.pos[3 * (int64_t)i];
+    g.ys[dst] = g.pos[3 * (int64_t)i + 1];
+    g.zs[dst] = g.pos[3 * (int64_t)i + 2];
+  } else {
+    g.xs[dst] = g.pos[2 * (int64_t)i];
+    g.ys[dst] = g.pos[2 * (int64_t)i + 1];
+  }
+  g.qs[dst] = g.q[i];
+}
 
 // First place and size of bucket b from the digit totals (every thread of the
 // workgroup calls it; one block scan).
@@ -399,17 +423,19 @@ __device__ __forceinline__ int bucket_part_size(int m) {
   return (m + kBucketSplit - 1) / kBucketSplit;
 }
 
-template <int NT, bool STAGED>
+// CAP: the stage of the launch with STAGED set.
+template <int NT, bool STAGED, int CAP>
 __global__ __launch_bounds__(NT) void k_bucket_sort(
     const uint32_t* __restrict__ kin, const int32_t* __restrict__ vin,
     const float4* __restrict__ pin, uint32_t* __restrict__ kout, int32_t* __restrict__ vout,
-    float4* __restrict__ pout, int64_t n, const int32_t* __restrict__ tot,
-    int32_t* __restrict__ leaf_start, int64_t nleaf, int32_t* __restrict__ parts) {
+    float4* __restrict__ pout, int64_t n, int lb, const int32_t* __restrict__ tot,
+    int32_t* __restrict__ leaf_start, int64_t nleaf, int32_t* __restrict__ parts, GatherOut go) {
   static_assert(NT >= 256, "one thread per digit");
   constexpr int NW = NT / 64;
   // chunks of 64 keys a wave holds at once: a staged bucket's whole piece, so
   // that its keys, values and records are loaded once, up front
-  constexpr int G = STAGED ? (kBucketCap / NW + 63) / 64 : 4;
+  constexpr int G = STAGED ? (CAP / NW + 63) / 64 : 4;
+  const uint32_t low = (1u << lb) - 1u;
   extern __shared__ __align__(16) unsigned char bsmem[];  // STAGED: keys, values [, records]
   __shared__ int32_t wcnt[NW][256];
   __shared__ int32_t pre[256], all_cnt[256];
@@ -422,7 +448,7 @@ __global__ __launch_bounds__(NT) void k_bucket_sort(
   bucket_range<NT>(tot, n, b, wt, &s_b0, &s_m);
   const int64_t b0 = s_b0;
   const int m = s_m;
-  const bool fits = m <= kBucketCap;
+  const bool fits = m <= CAP;
   if (!STAGED && fits) return;  // sorted by the first launch (workgroup-uniform)
   const int per = bucket_part_size(m);
   if (STAGED && !fits) {
@@ -440,7 +466,7 @@ __global__ __launch_bounds__(NT) void k_bucket_sort(
         }
 #pragma unroll
         for (int c = 0; c < G; ++c)
-          if (g0 + 64 * c < phi) count_digits(all_cnt, k2[c] & 255u, g0 + 64 * c + lane < phi);
+          if (g0 + 64 * c < phi) count_digits(all_cnt, k2[c] & low, g0 + 64 * c + lane < phi);
       }
       __syncthreads();
       if (t < 256) parts[((int64_t)b * kBucketSplit + s) * 256 + t] = all_cnt[t];
@@ -485,7 +511,7 @@ __global__ __launch_bounds__(NT) void k_bucket_sort(
   if (STAGED) {
 #pragma unroll
     for (int c = 0; c < G; ++c)
-      if (wlo + 64 * c + lane < whi) atomicAdd(&wcnt[wave][kk[c] & 255u], 1);
+      if (wlo + 64 * c + lane < whi) atomicAdd(&wcnt[wave][kk[c] & low], 1);
   } else {
     for (int g0 = wlo; g0 < whi; g0 += 64 * G) {
 #pragma unroll
@@ -495,7 +521,7 @@ __global__ __launch_bounds__(NT) void k_bucket_sort(
       }
 #pragma unroll
       for (int c = 0; c < G; ++c)
-        if (g0 + 64 * c < whi) count_digits(wcnt[wave], kk[c] & 255u, g0 + 64 * c + lane < whi);
+        if (g0 + 64 * c < whi) count_digits(wcnt[wave], kk[c] & low, g0 + 64 * c + lane < whi);
     }
   }
   __syncthreads();
@@ -512,8 +538,8 @@ __global__ __launch_bounds__(NT) void k_bucket_sort(
     int32_t all;
     const int32_t ex = block_exclusive_scan<NT>(c, wt, &all);
     if (t < 256) {
-      const int64_t leaf = ((int64_t)b << 8) | t;
-      if (part == 0 && leaf < nleaf) leaf_start[leaf] = (int32_t)(b0 + ex);
+      const int64_t leaf = ((int64_t)b << lb) | t;
+      if (part == 0 && (uint32_t)t <= low) leaf_start[leaf] = (int32_t)(b0 + ex);
       // each wave's first place for digit t inside the bucket
       int32_t o = ex + pre[t];
 #pragma unroll
@@ -527,8 +553,8 @@ __global__ __launch_bounds__(NT) void k_bucket_sort(
   }
   __syncthreads();
   uint32_t* skey = reinterpret_cast<uint32_t*>(bsmem);
-  int32_t* sval = reinterpret_cast<int32_t*>(skey + kBucketCap);
-  float4* srec = reinterpret_cast<float4*>(sval + kBucketCap);
+  int32_t* sval = reinterpret_cast<int32_t*>(skey + CAP);
+  float4* srec = reinterpret_cast<float4*>(sval + CAP);
   const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   for (int g0 = wlo; g0 < whi; g0 += 64 * G) {  // wave-uniform (STAGED: once)
     if (!STAGED) {
@@ -545,7 +571,7 @@ __global__ __launch_bounds__(NT) void k_bucket_sort(
     for (int c = 0; c < G; ++c) {
       if (g0 + 64 * c >= whi) break;  // wave-uniform
       const bool valid = g0 + 64 * c + lane < whi;
-      const uint32_t d = kk[c] & 255u;
+      const uint32_t d = kk[c] & low;
       const uint64_t mk = digit_match(d, valid);
       const int rank = __popcll(mk & lt_mask);
       const int32_t base = valid ? wcnt[wave][d] : 0;
@@ -560,6 +586,7 @@ __global__ __launch_bounds__(NT) void k_bucket_sort(
           kout[b0 + lp] = kk[c];
           vout[b0 + lp] = vv[c];
           if (pin) pout[b0 + lp] = rr[c];
+          if (go.xs) gather_one(go, b0 + lp, vv[c]);
         }
       }
     }
@@ -570,38 +597,199 @@ __global__ __launch_bounds__(NT) void k_bucket_sort(
       kout[b0 + i] = skey[i];
       vout[b0 + i] = sval[i];
       if (pin) pout[b0 + i] = srec[i];
+      if (go.xs) gather_one(go, b0 + i, sval[i]);
     }
   }
 }
 
 bool radix_two_digit(int64_t n, int bits) {
   if (bits <= 8 || bits > 16 || n <= 0) return false;
-  const int64_t buckets = (int64_t)1 << (bits - 8);
-  return n <= buckets * (kBucketCap * 9 / 10);  // the mean bucket well inside the stage
+  return n <= 256 * (kBucketCap * 9 / 10);  // the mean bucket well inside the stage
 }
 
 size_t radix_two_digit_parts() { return (size_t)256 * kBucketSplit * 256; }
 
+template <int NT, int CAP>
+static void bucket_sorts(uint32_t* keys, int32_t* vals, const uint32_t* keys_alt,
+                         const int32_t* vals_alt, int64_t n, int lb, const int32_t* tot,
+                         int32_t* leaf_start, int64_t nleaf, int32_t* parts, hipStream_t st,
+                         float4* recs, const float4* recs_alt, const GatherOut& go) {
+  const size_t lds = (size_t)CAP * (sizeof(uint32_t) + sizeof(int32_t) +
+                                    (recs ? sizeof(float4) : 0));
+  if (lds > 65536)
+    (void)hipFuncSetAttribute((const void*)k_bucket_sort<NT, true, CAP>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((k_bucket_sort<NT, true, CAP>), dim3(256), dim3(NT), lds, st, keys_alt,
+                     vals_alt, recs_alt, keys, vals, recs, n, lb, tot, leaf_start, nleaf, parts,
+                     go);
+  if (n > CAP)  // (else no bucket outgrows the stage)
+    hipLaunchKernelGGL((k_bucket_sort<512, false, CAP>), dim3(256 * kBucketSplit), dim3(512), 0,
+                       st, keys_alt, vals_alt, recs_alt, keys, vals, recs, n, lb, tot, leaf_start,
+                       nleaf, parts, go);
+}
+
+// Four waves a bucket while the mean bucket lies well inside their stage (20,011
+// keys of 10 bits are 78 a bucket), sixteen above.
 void radix_sort_two_digit(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt,
                           int64_t n, int bits, int32_t* hist, int32_t* tot, int32_t* leaf_start,
-                          int64_t nleaf, int32_t* parts, hipStream_t st, float4* recs,
-                          float4* recs_alt) {
+                          int32_t* parts, hipStream_t st, float4* recs, float4* recs_alt, int dim,
+                          const double* pos, const double* q, double* xs, double* ys, double* zs,
+                          double* qs) {
   const int64_t ntiles = (n + kRadixTile - 1) / kRadixTile;
   const size_t lds = recs ? sizeof(float4) * kRadixTile : 0;
+  const int lb = bits - 8;
+  const int64_t nleaf = (int64_t)1 << bits;
+  const GatherOut go{pos, q, xs, ys, dim == 3 ? zs : nullptr, qs};
   hipLaunchKernelGGL(k_scan_rows, dim3(256), dim3(256), 0, st, hist, ntiles, tot);
   hipLaunchKernelGGL(k_rs_scatter, dim3(ntiles), dim3(kScatterThreads), lds, st, keys, vals,
-                     keys_alt, vals_alt, n, 8, hist, tot, ntiles, recs, recs_alt);
-  const size_t blds = (size_t)kBucketCap * (sizeof(uint32_t) + sizeof(int32_t) +
-                                            (recs ? sizeof(float4) : 0));
-  if (blds > 65536)
-    (void)hipFuncSetAttribute((const void*)k_bucket_sort<1024, true>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)blds);
-  const unsigned buckets = 1u << (bits - 8);
-  hipLaunchKernelGGL((k_bucket_sort<1024, true>), dim3(buckets), dim3(1024), blds, st, keys_alt,
-                     vals_alt, recs_alt, keys, vals, recs, n, tot, leaf_start, nleaf, parts);
-  hipLaunchKernelGGL((k_bucket_sort<512, false>), dim3(buckets * kBucketSplit), dim3(512), 0, st,
-                     keys_alt, vals_alt, recs_alt, keys, vals, recs, n, tot, leaf_start, nleaf,
-                     parts);
+                     keys_alt, vals_alt, n, lb, hist, tot, ntiles, recs, recs_alt);
+  if (n <= 256 * (kBucketCapSmall * 9 / 10))
+    bucket_sorts<256, kBucketCapSmall>(keys, vals, keys_alt, vals_alt, n, lb, tot, leaf_start,
+                                       nleaf, parts, st, recs, recs_alt, go);
+  else
+    bucket_sorts<1024, kBucketCap>(keys, vals, keys_alt, vals_alt, n, lb, tot, leaf_start, nleaf,
+                                   parts, st, recs, recs_alt, go);
+}
+
+// ---------------------------------------------------------------------------
+// Few particles: everything before the near field and the moments in one
+// workgroup of 16 waves: leaf keys, a stable counting sort in LDS by one or two
+// 8-bit digits (each wave ranks a contiguous piece, as above), leaf offsets,
+// and the sorted records (FP32 modes) or coordinates and charges (FP64).  One
+// launch instead of five or six: they are bound by latency, not by work.
+// ---------------------------------------------------------------------------
+constexpr int kOneThreads = 1024, kOneWaves = kOneThreads / 64;
+constexpr int kOneMax = 8192;   // particles
+constexpr int kOneBits = 12;    // key bits
+
+template <int D, int PER>  // PER: particles per thread
+__global__ __launch_bounds__(kOneThreads) void k_sort_one(
+    const double* __restrict__ pos, const double* __restrict__ q, int n, LevelTable lt, int bits,
+    uint32_t* __restrict__ keys, int32_t* __restrict__ vals, int32_t* flag, int32_t tag,
+    int32_t* __restrict__ leaf_start, float4* __restrict__ rec, GatherOut go) {
+  __shared__ uint16_t skey[PER * kOneThreads], sval[PER * kOneThreads];
+  __shared__ int32_t wcnt[kOneWaves][256];
+  __shared__ int32_t wt[kOneWaves];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  // this wave's piece [p0, p0 + 64 PER), 64 at a time
+  const int p0 = wave * 64 * PER;
+  uint32_t kk[PER];
+  int32_t vv[PER];
+#pragma unroll
+  for (int c = 0; c < PER; ++c) {
+    const int e = p0 + 64 * c + lane;
+    vv[c] = e;
+    kk[c] = 0;
+    if (e < n) {
+      bool bad;
+      kk[c] = bin_key<D>(pos, e, lt, bad);
+      if (bad) flag[0] = tag;  // every writer stores the same value
+    }
+  }
+  for (int sh = 0; sh < bits; sh += 8) {  // (bits = 0: one leaf, nothing to sort)
+    if (sh > 0) {
+#pragma unroll
+      for (int c = 0; c < PER; ++c) {
+        const int e = p0 + 64 * c + lane;
+        kk[c] = e < n ? skey[e] : 0u;
+        vv[c] = e < n ? sval[e] : 0;
+      }
+    }
+    for (int i = t; i < kOneWaves * 256; i += kOneThreads) (&wcnt[0][0])[i] = 0;
+    __syncthreads();
+    uint64_t mks[PER];
+#pragma unroll
+    for (int c = 0; c < PER; ++c) {
+      const bool valid = p0 + 64 * c + lane < n;
+      const uint32_t d = (kk[c] >> sh) & 255u;
+      mks[c] = digit_match(d, valid);
+      if (valid && __popcll(mks[c] & lt_mask) == 0) atomicAdd(&wcnt[wave][d], __popcll(mks[c]));
+    }
+    __syncthreads();
+    int32_t cnt = 0;
+    if (t < 256)
+#pragma unroll
+      for (int w = 0; w < kOneWaves; ++w) cnt += wcnt[w][t];
+    int32_t all;
+    int32_t o = block_exclusive_scan<kOneThreads>(cnt, wt, &all);
+    if (t < 256) {
+#pragma unroll
+      for (int w = 0; w < kOneWaves; ++w) {
+        const int32_t x = wcnt[w][t];
+        wcnt[w][t] = o;
+        o += x;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < PER; ++c) {
+      if (p0 + 64 * c >= n) break;  // wave-uniform
+      const bool valid = p0 + 64 * c + lane < n;
+      const uint32_t d = (kk[c] >> sh) & 255u;
+      const int rank = __popcll(mks[c] & lt_mask);
+      const int32_t base = valid ? wcnt[wave][d] : 0;
+      if (valid && rank == 0) wcnt[wave][d] = base + __popcll(mks[c]);  // after every lane's read
+      if (valid) {
+        skey[base + rank] = (uint16_t)kk[c];
+        sval[base + rank] = (uint16_t)vv[c];
+      }
+    }
+    __syncthreads();
+  }
+  if (bits == 0) {
+#pragma unroll
+    for (int c = 0; c < PER; ++c) {
+      skey[p0 + 64 * c + lane] = 0;
+      sval[p0 + 64 * c + lane] = (uint16_t)(p0 + 64 * c + lane);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int c = 0; c < PER; ++c) {
+    const int e = t + kOneThreads * c;
+    if (e >= n) break;
+    const uint32_t key = skey[e];
+    const int32_t i = sval[e];
+    keys[e] = key;
+    vals[e] = i;
+    if (rec) rec[e] = leaf_record<D>(pos, q, i, key, lt.origin, lt.s[lt.L]);
+    if (go.xs) gather_one(go, e, i);
+  }
+  for (int l = t; l <= (1 << bits); l += kOneThreads) {  // first place with key >= l
+    int lo = 0, hi = n;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if ((int)skey[mid] < l)
+        lo = mid + 1;
+      else
+        hi = mid;
+    }
+    leaf_start[l] = lo;
+  }
+}
+
+bool sort_in_one(int64_t n, int bits) { return n <= kOneMax && bits <= kOneBits; }
+
+void launch_sort_one(int dim, const double* pos, const double* q, int64_t n, const LevelTable& lt,
+                     int bits, uint32_t* keys, int32_t* vals, int32_t* flag, int32_t tag,
+                     int32_t* leaf_start, float4* rec, double* xs, double* ys, double* zs,
+                     double* qs, hipStream_t st) {
+  const GatherOut go{pos, q, xs, ys, dim == 3 ? zs : nullptr, qs};
+  const dim3 one(1), nt(kOneThreads);
+#define SFFMM_ONE(DIM, PER)                                                                     \
+  hipLaunchKernelGGL((k_sort_one<DIM, PER>), one, nt, 0, st, pos, q, (int)n, lt, bits, keys,    \
+                     vals, flag, tag, leaf_start, rec, go)
+  if (dim == 2) {
+    if (n <= 2 * kOneThreads) SFFMM_ONE(2, 2);
+    else if (n <= 4 * kOneThreads) SFFMM_ONE(2, 4);
+    else SFFMM_ONE(2, 8);
+  } else {
+    if (n <= 2 * kOneThreads) SFFMM_ONE(3, 2);
+    else if (n <= 4 * kOneThreads) SFFMM_ONE(3, 4);
+    else SFFMM_ONE(3, 8);
+  }
+#undef SFFMM_ONE
 }
 
 // leaf_start[l] = lower_bound(sorted_keys, l), l = 0..nleaf.  (A binary
