@@ -51,18 +51,21 @@ __device__ __forceinline__ T leaf_to_box(uint32_t leaf, int sh) {
   return (T)r + (T)0.5 - (T)(1u << sh) * (T)0.5;
 }
 
-// P2M work plan: per level, G lanes per box (a power of two <= 64 giving each
-// lane about 16 particles) and S waves (slices) per box when it holds far more
-// than a wave's share.  Level thread ranges start on wave boundaries.
+// P2M work plan: per level, G = 2^lgG lanes per box (at most 64) and S = 2^lgS
+// waves (slices) per box when it holds far more than a wave's share.  Level
+// thread ranges start on wave boundaries.  (Powers of two kept as shifts: the
+// 64-bit divisions by G and S took more instructions than a lane's particles.)
 struct P2mPlan {
   int klo, khi;
-  int32_t G[kMaxLevels2D + 1];
-  int32_t S[kMaxLevels2D + 1];
+  int32_t lgG[kMaxLevels2D + 1];
+  int32_t lgS[kMaxLevels2D + 1];
   int64_t thr_off[kMaxLevels2D + 2];
   int64_t part_off[kMaxLevels2D + 1];
 };
 
-inline P2mPlan make_p2m_plan(int dim, int klo, int khi, int64_t n, int nsys = 1) {
+// Each lane takes about `per` particles (16; where a lane's sum may be split,
+// fewer: p2m_lane_particles), a box of at most 1.5 per a single lane.
+inline P2mPlan make_p2m_plan(int dim, int klo, int khi, int64_t n, int nsys = 1, int per = 16) {
   P2mPlan pl{};
   pl.klo = klo;
   pl.khi = khi;
@@ -70,21 +73,76 @@ inline P2mPlan make_p2m_plan(int dim, int klo, int khi, int64_t n, int nsys = 1)
   for (int k = klo; k <= khi; ++k) {
     const int64_t nb = (int64_t)nsys << (dim * k);
     const int64_t avg = n / nb;
-    int64_t G = 1, S = 1;
-    if (avg > 24) {
-      while (G < 64 && G * 16 < avg) G *= 2;
+    int lg = 0, ls = 0;
+    if (2 * avg > 3 * per) {
+      while (lg < 6 && ((int64_t)per << lg) < avg) ++lg;
       if (avg > 2048)
-        while (S < 1024 && S * 1024 < avg) S *= 2;
+        while (ls < 10 && ((int64_t)1024 << ls) < avg) ++ls;
     }
-    pl.G[k] = (int32_t)G;
-    pl.S[k] = (int32_t)S;
+    pl.lgG[k] = lg;
+    pl.lgS[k] = ls;
     pl.thr_off[k] = t;
     pl.part_off[k] = po;
-    t += (nb * G * S + 63) / 64 * 64;
-    if (S > 1) po += nb * S;
+    t += ((nb << (lg + ls)) + 63) / 64 * 64;
+    if (ls > 0) po += nb << ls;
   }
   pl.thr_off[khi + 1] = t;
   return pl;
+}
+
+// Particles per lane: FP32 sums keep 16, which their rounding follows; FP64 sums
+// take 8 from 2^19 particles on and 4 below, where the waves of a level would
+// not fill the chip and a launch lasts as long as one lane's chain (whole
+// evaluation of 4096 particles: 67 us with 16, 61 with 8, 60 with 4; of 2^20:
+// 547, 545 and 555).
+inline int p2m_lane_particles(bool f64, int64_t n) {
+  return !f64 ? 16 : n >= ((int64_t)1 << 19) ? 8 : 4;
+}
+
+// The work item of thread t of level k: box b, slice j, lane r of its group, and
+// (inside the box range) its particles lo + r, lo + r + G, ... below hi.
+struct P2mItem {
+  int64_t b;
+  int j, r;
+};
+__device__ __forceinline__ P2mItem p2m_item_of(const P2mPlan& pl, int k, int64_t t) {
+  const int64_t local = t - pl.thr_off[k];
+  const int lg = pl.lgG[k], ls = pl.lgS[k];
+  return P2mItem{local >> (lg + ls), (int)(local >> lg) & ((1 << ls) - 1),
+                 (int)local & ((1 << lg) - 1)};
+}
+__device__ __forceinline__ void p2m_slice(const P2mPlan& pl, int k, int j, int32_t s0, int32_t s1,
+                                          int32_t& lo, int32_t& hi) {
+  const int64_t len = s1 - s0;
+  lo = s0 + (int32_t)(len * j >> pl.lgS[k]);
+  hi = s0 + (int32_t)(len * (j + 1) >> pl.lgS[k]);
+}
+
+// Sums v[0..N) over the 2^lg lanes of each group (neighbouring lanes, lg uniform
+// over the wave) and hands every value to one lane: store(i, sum) on the lane
+// that ends up with value i.  Step d (lanes d apart) keeps half of the values a
+// lane holds and sends the other half, so that N values cost N exchanges and
+// not N per step, and a row is written by all lanes of its group.  The sums are
+// those of a butterfly over d = 1, 2, 4, ..., bit for bit.
+template <int N, int STEP = 0, int NV, typename T, class F>
+__device__ __forceinline__ void group_sum(T (&v)[NV], int lg, F&& store, int base = 0,
+                                          int lim = N) {
+  if constexpr (STEP < 6) {
+    if (lg > STEP) {
+      constexpr int H = (N + 1) / 2;
+      const bool up = (threadIdx.x >> STEP) & 1;
+#pragma unroll
+      for (int i = 0; i < H; ++i) {
+        const T lo = v[i], hi = H + i < N ? v[H + i] : (T)0;
+        v[i] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, 1 << STEP, 64);
+      }
+      group_sum<H, STEP + 1>(v, lg, store, up ? base + H : base, up ? lim : min(lim, base + H));
+      return;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (base + i < lim) store(base + i, v[i]);
 }
 
 inline size_t p2m_partial_rows(int dim, int klo, int khi, int64_t maxn, int nsys = 1) {
@@ -92,7 +150,7 @@ inline size_t p2m_partial_rows(int dim, int klo, int khi, int64_t maxn, int nsys
   const P2mPlan pl = make_p2m_plan(dim, klo, khi, maxn, nsys);
   int64_t rows = 0;
   for (int k = klo; k <= khi; ++k)
-    if (pl.S[k] > 1) rows += ((int64_t)nsys << (dim * k)) * pl.S[k];
+    if (pl.lgS[k] > 0) rows += ((int64_t)nsys << (dim * k)) << pl.lgS[k];
   return (size_t)rows;
 }
 

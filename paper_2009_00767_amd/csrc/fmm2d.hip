@@ -91,25 +91,33 @@ __device__ __forceinline__ void with_order_bucket(int p, F&& f) {
   f(std::integral_constant<int, PB>());
 }
 
+struct NegInverse {  // -1 / m
+  double v[kMaxOrder2D + 1];
+  constexpr NegInverse() : v() {
+    for (int m = 1; m <= kMaxOrder2D; ++m) v[m] = -1.0 / m;
+  }
+};
+static __constant__ const NegInverse kNegInverse;
+
 // Moments of one (box, slice, lane) work item up to order PK (>= p): powers
 // of w above p are formed too and dropped at the store, where every moment
 // above p is written as zero.
 template <typename T, int PB, int PK, bool LL>
 __device__ __forceinline__ void p2m_item(const FmmArgs& a, const P2mPlan& pl, int k, int p,
-                                         bool valid, int64_t b, int j, int r, int G, int S) {
+                                         bool valid, const P2mItem& it) {
   const LevelTable& lt = a.lt;
-  const int sh = lt.L - k;
-  T re[PK + 1], im[PK + 1];
+  const int sh = lt.L - k, G = 1 << pl.lgG[k];
+  const int64_t b = it.b;
+  T v[2 * PK + 1];  // re / im of orders 1..PK, then order 0
 #pragma unroll
-  for (int m = 0; m <= PK; ++m) re[m] = im[m] = (T)0;
+  for (int i = 0; i <= 2 * PK; ++i) v[i] = (T)0;
   // adaptive depth: only the moments some interaction list reads, those of
   // boxes whose parent has an open box in its 3 x 3 (every box at kmin)
   if (valid && a.adapt_open && k > lt.kmin)
     valid = (a.adapt_open[adapt_open_off(k - 1) + (b >> 2)] & 2) != 0;
   if (valid) {
-    const int64_t s0 = a.leaf_start[b << (2 * sh)], s1 = a.leaf_start[(b + 1) << (2 * sh)];
-    const int64_t len = s1 - s0;
-    const int64_t lo = s0 + len * j / S, hi = s0 + len * (j + 1) / S;
+    int32_t lo, hi;
+    p2m_slice(pl, k, it.j, a.leaf_start[b << (2 * sh)], a.leaf_start[(b + 1) << (2 * sh)], lo, hi);
     const T is = (T)lt.inv_s[k];
     T cx = 0, cy = 0, sL = (T)lt.s[lt.L];
     if (!LL) {
@@ -120,16 +128,16 @@ __device__ __forceinline__ void p2m_item(const FmmArgs& a, const P2mPlan& pl, in
     // the next particle's inputs are loaded while this one is accumulated
     float4 npt = make_float4(0.f, 0.f, 0.f, 0.f);
     double nx = 0, ny = 0, nq = 0;
-    if (lo + r < hi) {
+    if (lo + it.r < hi) {
       if (LL) {
-        npt = a.pts[lo + r];
+        npt = a.pts[lo + it.r];
       } else {
-        nx = a.xs[lo + r];
-        ny = a.ys[lo + r];
-        nq = a.qs[lo + r];
+        nx = a.xs[lo + it.r];
+        ny = a.ys[lo + it.r];
+        nq = a.qs[lo + it.r];
       }
     }
-    for (int64_t i = lo + r; i < hi; i += G) {
+    for (int32_t i = lo + it.r; i < hi; i += G) {
       T q, wr, wi;
       const float4 pt = npt;
       const double px = nx, py = ny, pq = nq;
@@ -154,44 +162,36 @@ __device__ __forceinline__ void p2m_item(const FmmArgs& a, const P2mPlan& pl, in
         wr = ((T)px - cx) * is;
         wi = ((T)py - cy) * is;
       }
-      re[0] += q;
+      v[2 * PK] += q;
       T pr = q * wr, pi = q * wi;  // q w^m
 #pragma unroll
       for (int m = 1; m <= PK; ++m) {
-        re[m] += pr;
-        im[m] += pi;
+        v[2 * (m - 1)] += pr;
+        v[2 * (m - 1) + 1] += pi;
         const T nr = pr * wr - pi * wi;
         pi = pr * wi + pi * wr;
         pr = nr;
       }
     }
   }
-  for (int d = 1; d < G; d <<= 1) {
-#pragma unroll
-    for (int m = 0; m <= PK; ++m) {
-      re[m] += __shfl_xor(re[m], d, 64);
-      im[m] += __shfl_xor(im[m], d, 64);
-    }
-  }
-  if (!valid || r != 0) return;
-  const int cs = a.cs;
+  const int S = 1 << pl.lgS[k], cs = a.cs;
   T* out;
   if (S == 1)
     out = (sizeof(T) == 8 ? (T*)a.mom64 : (T*)a.mom32) + (lt.off[k] + b) * cs;
   else
-    out = (sizeof(T) == 8 ? (T*)a.part64 : (T*)a.part32) + (pl.part_off[k] + b * S + j) * cs;
-#pragma unroll
-  for (int m = 1; m <= PB; ++m) {
-    T vr = (T)0, vi = (T)0;
-    if (m <= PK) {
-      const T f = (T)(-1.0 / (double)m);
-      vr = m <= p ? re[m] * f : (T)0;
-      vi = m <= p ? im[m] * f : (T)0;
+    out = (sizeof(T) == 8 ? (T*)a.part64 : (T*)a.part32) + (pl.part_off[k] + b * S + it.j) * cs;
+  group_sum<2 * PK + 1>(v, pl.lgG[k], [&](int i, T x) {
+    if (!valid) return;
+    if (i < 2 * PK) {
+      const int m = i / 2 + 1;
+      out[i] = m <= p ? x * (T)kNegInverse.v[m] : (T)0;
+    } else {
+      out[2 * PB] = x;
     }
-    out[2 * (m - 1)] = vr;
-    out[2 * (m - 1) + 1] = vi;
-  }
-  out[2 * PB] = re[0];
+  });
+  if (!valid || it.r != 0) return;
+#pragma unroll
+  for (int i = 2 * PK; i < 2 * PB; ++i) out[i] = (T)0;
   out[2 * PB + 1] = (T)0;
 }
 
@@ -202,16 +202,12 @@ __global__ __launch_bounds__(256) void k_p2m2d(FmmArgs a, P2mPlan pl) {
   const LevelTable& lt = a.lt;
   int k = pl.klo;
   while (k < pl.khi && t >= pl.thr_off[k + 1]) ++k;
-  const int G = pl.G[k], S = pl.S[k];
-  const int64_t local = t - pl.thr_off[k];
-  const int64_t nb = (int64_t)lt.nsys << (2 * k);
-  const int64_t b = local / (G * S);
-  const bool valid = b < nb;
-  const int rem = (int)(local - b * G * S);
-  const int j = rem / G, r = rem - (rem / G) * G;
-  const int p = FULL ? PB : a.ord[k];  // this level's order (waves never straddle levels)
+  k = __builtin_amdgcn_readfirstlane(k);  // (waves never straddle levels)
+  const P2mItem it = p2m_item_of(pl, k, t);
+  const bool valid = it.b < (int64_t)lt.nsys << (2 * k);
+  const int p = FULL ? PB : a.ord[k];  // this level's order
   with_order_bucket<PB, FULL>(p, [&](auto pk) {
-    p2m_item<T, PB, decltype(pk)::value, LL>(a, pl, k, p, valid, b, j, r, G, S);
+    p2m_item<T, PB, decltype(pk)::value, LL>(a, pl, k, p, valid, it);
   });
 }
 
@@ -237,7 +233,7 @@ __global__ __launch_bounds__(256) void k_p2m_slices(FmmArgs a, P2mPlan pl, Slice
   const int64_t item = wv - jb.off[i];
   const int64_t b = item / nc;
   const int c = (int)(item - b * nc);
-  const int S = pl.S[k];
+  const int S = 1 << pl.lgS[k];
   const T* part = sizeof(T) == 8 ? (const T*)a.part64 : (const T*)a.part32;
   T* mom = sizeof(T) == 8 ? (T*)a.mom64 : (T*)a.mom32;
   const T* src = part + (pl.part_off[k] + b * S) * a.cs + c;
@@ -250,7 +246,8 @@ __global__ __launch_bounds__(256) void k_p2m_slices(FmmArgs a, P2mPlan pl, Slice
 
 template <int PB>
 static void p2m_dispatch(const FmmArgs& a, bool ll, bool f64, hipStream_t st) {
-  const P2mPlan pl = make_p2m_plan(2, a.klo, a.khi, a.n, a.lt.nsys);
+  const P2mPlan pl = make_p2m_plan(2, a.klo, a.khi, a.n, a.lt.nsys,
+                                   p2m_lane_particles(f64, a.n));
   const int64_t thr = pl.thr_off[a.khi + 1];
   const dim3 grid((unsigned)((thr + 255) / 256));
   const bool full = a.ord_full != 0;
@@ -272,7 +269,7 @@ static void p2m_dispatch(const FmmArgs& a, bool ll, bool f64, hipStream_t st) {
   SliceJob jb{};
   int64_t waves = 0;
   for (int k = a.klo; k <= a.khi; ++k)
-    if (pl.S[k] > 1) {
+    if (pl.lgS[k] > 0) {
       jb.lev[jb.n] = k;
       jb.off[jb.n] = waves;
       ++jb.n;

@@ -85,22 +85,19 @@ __global__ __launch_bounds__(256) void k_p2m3d(FmmArgs a, P2mPlan pl) {
   const LevelTable& lt = a.lt;
   int k = pl.klo;
   while (k < pl.khi && t >= pl.thr_off[k + 1]) ++k;
-  const int G = pl.G[k], S = pl.S[k];
-  const int64_t local = t - pl.thr_off[k];
-  const int64_t nb = (int64_t)1 << (3 * k);
-  const int64_t b = local / (G * S);
-  const bool valid = b < nb;
-  const int rem = (int)(local - b * G * S);
-  const int j = rem / G, r = rem - (rem / G) * G;
+  k = __builtin_amdgcn_readfirstlane(k);  // (waves never straddle levels)
+  const P2mItem it = p2m_item_of(pl, k, t);
+  const int64_t b = it.b;
+  const int G = 1 << pl.lgG[k], S = 1 << pl.lgS[k], j = it.j, r = it.r;
+  const bool valid = b < (int64_t)1 << (3 * k);
   const int sh = lt.L - k;
   const int p = a.p;
   T acc[NR];
 #pragma unroll
   for (int i = 0; i < NR; ++i) acc[i] = (T)0;
   if (valid) {
-    const int64_t s0 = a.leaf_start[b << (3 * sh)], s1 = a.leaf_start[(b + 1) << (3 * sh)];
-    const int64_t len = s1 - s0;
-    const int64_t lo = s0 + len * j / S, hi = s0 + len * (j + 1) / S;
+    int32_t lo, hi;
+    p2m_slice(pl, k, j, a.leaf_start[b << (3 * sh)], a.leaf_start[(b + 1) << (3 * sh)], lo, hi);
     const T is = (T)lt.inv_s[k], sL = (T)lt.s[lt.L];
     T cx = 0, cy = 0, cz = 0;
     if (!LL) {
@@ -109,7 +106,7 @@ __global__ __launch_bounds__(256) void k_p2m3d(FmmArgs a, P2mPlan pl) {
       cy = (T)(lt.origin[1] + lt.s[k] * ((double)compact3(ub >> 1) + 0.5));
       cz = (T)(lt.origin[2] + lt.s[k] * ((double)compact3(ub >> 2) + 0.5));
     }
-    for (int64_t i = lo + r; i < hi; i += G) {
+    for (int32_t i = lo + r; i < hi; i += G) {
       T q, wx, wy, wz;
       if (LL) {
         const float4 pt = a.pts[i];
@@ -135,19 +132,15 @@ __global__ __launch_bounds__(256) void k_p2m3d(FmmArgs a, P2mPlan pl) {
       }
     }
   }
-  for (int d = 1; d < G; d <<= 1) {
-#pragma unroll
-    for (int i = 0; i < NR; ++i) acc[i] += __shfl_xor(acc[i], d, 64);
-  }
-  if (!valid || r != 0) return;
   const int cs = a.cs;
   T* out;
   if (S == 1)
     out = (sizeof(T) == 8 ? (T*)a.mom64 : (T*)a.mom32) + (lt.off[k] + b) * cs;
   else
     out = (sizeof(T) == 8 ? (T*)a.part64 : (T*)a.part32) + (pl.part_off[k] + b * S + j) * cs;
-#pragma unroll
-  for (int i = 0; i < NR; ++i) out[i] = acc[i];
+  group_sum<NR>(acc, pl.lgG[k], [&](int i, T x) {
+    if (valid) out[i] = x;
+  });
 }
 
 template <typename T>
@@ -157,7 +150,7 @@ __global__ void k_p2m3d_slices(FmmArgs a, P2mPlan pl, int k, int nc) {
   if (g >= nb * nc) return;
   const int64_t b = g / nc;
   const int c = (int)(g - b * nc);
-  const int S = pl.S[k];
+  const int S = 1 << pl.lgS[k];
   const T* part = sizeof(T) == 8 ? (const T*)a.part64 : (const T*)a.part32;
   T* mom = sizeof(T) == 8 ? (T*)a.mom64 : (T*)a.mom32;
   const T* src = part + (pl.part_off[k] + b * S) * a.cs + c;
@@ -168,7 +161,7 @@ __global__ void k_p2m3d_slices(FmmArgs a, P2mPlan pl, int k, int nc) {
 
 template <int PB, int BASIS = 0>
 static void p2m3d_dispatch(const FmmArgs& a, bool ll, bool f64, hipStream_t st) {
-  const P2mPlan pl = make_p2m_plan(3, a.klo, a.khi, a.n);
+  const P2mPlan pl = make_p2m_plan(3, a.klo, a.khi, a.n, 1, p2m_lane_particles(f64, a.n));
   const int64_t thr = pl.thr_off[a.khi + 1];
   const dim3 grid((unsigned)((thr + 255) / 256));
   if (f64) {
@@ -181,7 +174,7 @@ static void p2m3d_dispatch(const FmmArgs& a, bool ll, bool f64, hipStream_t st) 
   }
   constexpr int NR = BASIS ? 64 : (PB + 1) * (PB + 1);
   for (int k = a.klo; k <= a.khi; ++k)
-    if (pl.S[k] > 1) {
+    if (pl.lgS[k] > 0) {
       const int64_t cnt = ((int64_t)1 << (3 * k)) * NR;
       if (f64)
         hipLaunchKernelGGL(k_p2m3d_slices<double>, dim3((cnt + 255) / 256), dim3(256), 0, st, a,

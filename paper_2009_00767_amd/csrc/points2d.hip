@@ -139,28 +139,25 @@ __global__ __launch_bounds__(256) void k_p2m2d_points(FmmArgs a, P2mPlan pl, Pts
   const LevelTable& lt = a.lt;
   int k = pl.klo;
   while (k < pl.khi && t >= pl.thr_off[k + 1]) ++k;
-  const int G = pl.G[k], S = pl.S[k];
-  const int64_t local = t - pl.thr_off[k];
-  const int64_t nb = (int64_t)1 << (2 * k);
-  const int64_t b = local / (G * S);
-  const bool valid = b < nb;
-  const int rem = (int)(local - b * G * S);
-  const int j = rem / G, r = rem - (rem / G) * G;
+  k = __builtin_amdgcn_readfirstlane(k);  // (waves never straddle levels)
+  const P2mItem it = p2m_item_of(pl, k, t);
+  const int64_t b = it.b;
+  const int G = 1 << pl.lgG[k], S = 1 << pl.lgS[k], j = it.j, r = it.r;
+  const bool valid = b < (int64_t)1 << (2 * k);
   const int sh = lt.L - k;
   T acc[D];
 #pragma unroll
   for (int i = 0; i < D; ++i) acc[i] = (T)0;
   if (valid) {
-    const int64_t s0 = a.leaf_start[b << (2 * sh)], s1 = a.leaf_start[(b + 1) << (2 * sh)];
-    const int64_t len = s1 - s0;
-    const int64_t lo = s0 + len * j / S, hi = s0 + len * (j + 1) / S;
+    int32_t lo, hi;
+    p2m_slice(pl, k, j, a.leaf_start[b << (2 * sh)], a.leaf_start[(b + 1) << (2 * sh)], lo, hi);
     const T is = (T)lt.inv_s[k], sL = (T)lt.s[lt.L];
     T cx = 0, cy = 0;
     if (!LL) {
       cx = (T)(lt.origin[0] + lt.s[k] * ((double)compact2((uint32_t)b) + 0.5));
       cy = (T)(lt.origin[1] + lt.s[k] * ((double)compact2((uint32_t)b >> 1) + 0.5));
     }
-    for (int64_t i = lo + r; i < hi; i += G) {
+    for (int32_t i = lo + r; i < hi; i += G) {
       T q, wx, wy;
       if (LL) {
         const float4 pt = a.pts[i];
@@ -184,19 +181,15 @@ __global__ __launch_bounds__(256) void k_p2m2d_points(FmmArgs a, P2mPlan pl, Pts
       }
     }
   }
-  for (int dd = 1; dd < G; dd <<= 1) {
-#pragma unroll
-    for (int i = 0; i < D; ++i) acc[i] += __shfl_xor(acc[i], dd, 64);
-  }
-  if (!valid || r != 0) return;
   const int cs = a.cs;
   T* out;
   if (S == 1)
     out = (sizeof(T) == 8 ? (T*)a.mom64 : (T*)a.mom32) + (lt.off[k] + b) * cs;
   else
     out = (sizeof(T) == 8 ? (T*)a.part64 : (T*)a.part32) + (pl.part_off[k] + b * S + j) * cs;
-#pragma unroll
-  for (int i = 0; i < D; ++i) out[i] = acc[i];
+  group_sum<D>(acc, pl.lgG[k], [&](int i, T x) {
+    if (valid) out[i] = x;
+  });
 }
 
 // Slice partials of level k added up: one wave per (box, point), lane l taking
@@ -209,7 +202,7 @@ __global__ __launch_bounds__(256) void k_points2d_slices(FmmArgs a, P2mPlan pl, 
   if (wv >= nb * d) return;  // whole waves
   const int64_t b = wv / d;
   const int c = (int)(wv - b * d);
-  const int S = pl.S[k];
+  const int S = 1 << pl.lgS[k];
   const T* part = sizeof(T) == 8 ? (const T*)a.part64 : (const T*)a.part32;
   T* mom = sizeof(T) == 8 ? (T*)a.mom64 : (T*)a.mom32;
   const T* src = part + (pl.part_off[k] + b * S) * a.cs + c;
@@ -402,7 +395,7 @@ __global__ __launch_bounds__(256) void k_l2p2d_points(FmmArgs a, PtsNodes nd) {
 template <int N>
 void p2m_points_n(const FmmArgs& a, bool ll, bool f64, hipStream_t st) {
   const PtsNodes nd = make_nodes(a.basis, N);
-  const P2mPlan pl = make_p2m_plan(2, a.klo, a.khi, a.n);
+  const P2mPlan pl = make_p2m_plan(2, a.klo, a.khi, a.n, 1, p2m_lane_particles(f64, a.n));
   const int64_t thr = pl.thr_off[a.khi + 1];
   const dim3 grid((unsigned)((thr + 255) / 256));
   if (f64) {
@@ -414,7 +407,7 @@ void p2m_points_n(const FmmArgs& a, bool ll, bool f64, hipStream_t st) {
     hipLaunchKernelGGL((k_p2m2d_points<float, N, true>), grid, dim3(256), 0, st, a, pl, nd);
   }
   for (int k = a.klo; k <= a.khi; ++k)
-    if (pl.S[k] > 1) {
+    if (pl.lgS[k] > 0) {
       const int64_t waves = ((int64_t)1 << (2 * k)) * (N * N);
       const dim3 sg((unsigned)((waves * 64 + 255) / 256));
       if (f64)

@@ -68,13 +68,11 @@ __global__ __launch_bounds__(256) void k_p2m3d_pts(FmmArgs a, P2mPlan pl, PtsNod
   const LevelTable& lt = a.lt;
   int k = pl.klo;
   while (k < pl.khi && t >= pl.thr_off[k + 1]) ++k;
-  const int G = pl.G[k], S = pl.S[k];
-  const int64_t local = t - pl.thr_off[k];
-  const int64_t nb = (int64_t)1 << (3 * k);
-  const int64_t b = local / (G * S);
-  const bool valid = b < nb;
-  const int rem = (int)(local - b * G * S);
-  const int j = rem / G, r = rem - (rem / G) * G;
+  k = __builtin_amdgcn_readfirstlane(k);  // (waves never straddle levels)
+  const P2mItem it = p2m_item_of(pl, k, t);
+  const int64_t b = it.b;
+  const int G = 1 << pl.lgG[k], S = 1 << pl.lgS[k], j = it.j, r = it.r;
+  const bool valid = b < (int64_t)1 << (3 * k);
   const int sh = lt.L - k;
   // the weight of plane l: c_l prod_{m != l} (u - a_m)
   T al[N], cl = (T)0;
@@ -87,9 +85,8 @@ __global__ __launch_bounds__(256) void k_p2m3d_pts(FmmArgs a, P2mPlan pl, PtsNod
 #pragma unroll
   for (int i = 0; i < P; ++i) acc[i] = (T)0;
   if (valid) {
-    const int64_t s0 = a.leaf_start[b << (3 * sh)], s1 = a.leaf_start[(b + 1) << (3 * sh)];
-    const int64_t len = s1 - s0;
-    const int64_t lo = s0 + len * j / S, hi = s0 + len * (j + 1) / S;
+    int32_t lo, hi;
+    p2m_slice(pl, k, j, a.leaf_start[b << (3 * sh)], a.leaf_start[(b + 1) << (3 * sh)], lo, hi);
     const T is = (T)lt.inv_s[k], sL = (T)lt.s[lt.L];
     T cx = 0, cy = 0, cz = 0;
     if (!LL) {
@@ -98,7 +95,7 @@ __global__ __launch_bounds__(256) void k_p2m3d_pts(FmmArgs a, P2mPlan pl, PtsNod
       cy = (T)(lt.origin[1] + lt.s[k] * ((double)compact3(ub >> 1) + 0.5));
       cz = (T)(lt.origin[2] + lt.s[k] * ((double)compact3(ub >> 2) + 0.5));
     }
-    for (int64_t i = lo + r; i < hi; i += G) {
+    for (int32_t i = lo + r; i < hi; i += G) {
       T q, wx, wy, wz;
       if (LL) {
         const float4 pt = a.pts[i];
@@ -130,11 +127,6 @@ __global__ __launch_bounds__(256) void k_p2m3d_pts(FmmArgs a, P2mPlan pl, PtsNod
       }
     }
   }
-  for (int dd = 1; dd < G; dd <<= 1) {
-#pragma unroll
-    for (int i = 0; i < P; ++i) acc[i] += __shfl_xor(acc[i], dd, 64);
-  }
-  if (!valid || r != 0) return;
   const int cs = a.cs;
   T* out;
   if (S == 1)
@@ -142,8 +134,9 @@ __global__ __launch_bounds__(256) void k_p2m3d_pts(FmmArgs a, P2mPlan pl, PtsNod
   else
     out = (sizeof(T) == 8 ? (T*)a.part64 : (T*)a.part32) + (pl.part_off[k] + b * S + j) * cs;
   out += P * l;
-#pragma unroll
-  for (int i = 0; i < P; ++i) out[i] = acc[i];
+  group_sum<P>(acc, pl.lgG[k], [&](int i, T x) {
+    if (valid) out[i] = x;
+  });
 }
 
 // the S slice rows of each level-k box added in slice order
@@ -154,7 +147,7 @@ __global__ void k_p2m3d_pts_slices(FmmArgs a, P2mPlan pl, int k, int nc) {
   if (g >= nb * nc) return;
   const int64_t b = g / nc;
   const int c = (int)(g - b * nc);
-  const int S = pl.S[k];
+  const int S = 1 << pl.lgS[k];
   const T* src = (sizeof(T) == 8 ? (const T*)a.part64 : (const T*)a.part32) +
                  (pl.part_off[k] + b * S) * a.cs + c;
   T acc = 0;
@@ -264,7 +257,7 @@ __global__ __launch_bounds__(256) void k_l2p3d_pts(FmmArgs a, PtsNodes nd) {
 template <int N>
 void p2m3_pts(const FmmArgs& a, bool ll, bool f64, hipStream_t st) {
   const PtsNodes nd = make_nodes(a.basis, N);
-  const P2mPlan pl = make_p2m_plan(3, a.klo, a.khi, a.n);
+  const P2mPlan pl = make_p2m_plan(3, a.klo, a.khi, a.n, 1, p2m_lane_particles(f64, a.n));
   const int64_t thr = pl.thr_off[a.khi + 1];  // a multiple of 64
   const dim3 grid((unsigned)((N * thr + 255) / 256));
   if (f64) {
@@ -276,7 +269,7 @@ void p2m3_pts(const FmmArgs& a, bool ll, bool f64, hipStream_t st) {
     hipLaunchKernelGGL((k_p2m3d_pts<float, N, true>), grid, dim3(256), 0, st, a, pl, nd, thr);
   }
   for (int k = a.klo; k <= a.khi; ++k)
-    if (pl.S[k] > 1) {
+    if (pl.lgS[k] > 0) {
       const int64_t cnt = ((int64_t)1 << (3 * k)) * (N * N * N);
       const dim3 sg((unsigned)((cnt + 255) / 256));
       if (f64)
