@@ -653,12 +653,11 @@ __global__ __launch_bounds__(kP2pThreads, 8) void k_p2p2d_f32_tile(FmmArgs a, in
   const int total = hoff[kP2pHaloLeaves];
   if (tid == 0) a.p2p_over[tile] = total > cap ? 1 : 0;
   if (total > cap) return;  // workgroup-uniform
-  for (int e = tid; e < total; e += kP2pThreads) {
-    const int lo = halo_leaf(hoff, e);
-    float4 v = a.pts[hstart[lo] + (e - hoff[lo])];
-    v.w = (float)(lo % kP2pHalo);
+  stage_halo(hstart, hoff, kP2pThreads, [&](int e, int32_t i, int col) {
+    float4 v = a.pts[i];
+    v.w = (float)col;
     src[e] = v;
-  }
+  });
   if (tid < kP2pPad) src[total + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
   __syncthreads();
   const int32_t t0 = a.leaf_start[k0], t1 = a.leaf_start[k0 + 16];

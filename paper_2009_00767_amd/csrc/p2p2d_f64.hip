@@ -43,48 +43,18 @@ __device__ __forceinline__ double near_threshold(double side) {
   return side < 0x1p400 ? 0x1p-900 : __builtin_inf();
 }
 
-// U sources at once: the tests for r = 0 and for r^2 out of range cost one
-// compare a pair; what they guard is left out unless some lane needs it.
+// The sums of U pairs at dx, dy, r2 (a normal number of FP64's range).
 template <int U>
-__device__ __forceinline__ void pairs2_f64(double x, double y, const double (&sx)[U],
-                                           const double (&sy)[U], double (&q)[U], double thr,
+__device__ __forceinline__ void add_pairs2(const double (&dx)[U], const double (&dy)[U],
+                                           const double (&r2)[U], const double (&q)[U],
                                            const double2* tab, NearSum& a) {
-  double dx[U], dy[U], r2[U];
-  bool odd = false;
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    dx[u] = x - sx[u];
-    dy[u] = y - sy[u];
-    r2[u] = fma(dx[u], dx[u], dy[u] * dy[u]);
-    odd = odd || !(r2[u] >= thr);
-  }
-  if (__any(odd)) {
-    bool far_off = false;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool zero = r2[u] == 0.0;
-      r2[u] = zero ? 1.0 : r2[u];
-      q[u] = zero ? 0.0 : q[u];
-      far_off = far_off || (!zero && !(r2[u] >= thr));
-    }
-    if (__any(far_off)) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        a.fr += q[u] * log2(r2[u]);
-        const double w = q[u] / r2[u];
-        a.ex -= w * dx[u];
-        a.ey -= w * dy[u];
-      }
-      return;
-    }
-  }
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const uint32_t hi = (uint32_t)__double2hiint(r2[u]);
     const double2 t = tab[(hi >> (20 - kLogBits)) & (kLogTable - 1)];
-    const double m = __hiloint2double((int)((hi & 0xFFFFFu) | 0x3FE00000u), __double2loint(r2[u]));
-    const double ef = (double)((int)(hi >> 20) - 1022);
-    double y0 = __builtin_amdgcn_rcp(r2[u]);  // relative error e at most about 2^-24
+    const double m = __builtin_amdgcn_frexp_mant(r2[u]);
+    const double ef = (double)__builtin_amdgcn_frexp_exp(r2[u]);
+    double y0 = __builtin_amdgcn_rcp(r2[u]);  // relative error e at most 2^-24.3 (measured)
     const double e = fma(-r2[u], y0, 1.0);
     y0 = fma(y0, fma(e, e, e), y0);  // 1 / r2 = y0 / (1 - e) = y0 (1 + e + e^2 + ...)
     const double w = q[u] * y0;
@@ -99,6 +69,57 @@ __device__ __forceinline__ void pairs2_f64(double x, double y, const double (&sx
     a.ex = fma(-w, dx[u], a.ex);
     a.ey = fma(-w, dy[u], a.ey);
   }
+}
+
+// U sources at once.  Whether some lane has a pair at r = 0 or below thr is one
+// compare a pair (its mask is joined in scalar registers); the batch then takes
+// a path of its own, so that the others carry nothing of it.
+template <int U>
+__device__ __forceinline__ void pairs2_f64(double x, double y, const double (&sx)[U],
+                                           const double (&sy)[U], const double (&q)[U],
+                                           double thr, const double2* tab, NearSum& a) {
+  double dx[U], dy[U], r2[U];
+  uint64_t odd = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    dx[u] = x - sx[u];
+    dy[u] = y - sy[u];
+    r2[u] = fma(dx[u], dx[u], dy[u] * dy[u]);
+    odd |= __ballot(!(r2[u] >= thr));
+  }
+  if (odd != 0) {
+    double r[U], c[U];
+    uint64_t tiny = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool zero = r2[u] == 0.0;
+      r[u] = zero ? 1.0 : r2[u];
+      c[u] = zero ? 0.0 : q[u];
+      tiny |= __ballot(!(r2[u] >= thr) && !zero);
+    }
+    if (tiny != 0) {
+#pragma unroll 1
+      for (int u = 0; u < U; ++u) {
+        double ru = r[0], cu = c[0], du = dx[0], eu = dy[0];
+#pragma unroll
+        for (int v = 1; v < U; ++v)
+          if (u == v) {
+            ru = r[v];
+            cu = c[v];
+            du = dx[v];
+            eu = dy[v];
+          }
+        a.fr += cu * log2(ru);
+        const double w = cu / ru;
+        a.ex -= w * du;
+        a.ey -= w * eu;
+      }
+      return;
+    }
+    add_pairs2<U>(dx, dy, r, c, tab, a);
+    return;
+  }
+  add_pairs2<U>(dx, dy, r2, q, tab, a);
 }
 
 __device__ __forceinline__ void store_near(const FmmArgs& a, int64_t j, const NearSum& s) {
@@ -208,21 +229,21 @@ __global__ __launch_bounds__(256) void k_p2p2d_f64(FmmArgs a, int over,
 
 // Tile form: a workgroup stages the sources of a 4 x 4-leaf tile's 6 x 6-leaf
 // halo in LDS, halo rows contiguous, so that a target's nine leaves are three
-// spans.  P lanes share a target (its spans' sources dealt round): a wave then
-// holds 64 / P targets of one or two leaves, whose spans hardly differ in
-// length.  Tiles whose halo exceeds the stage are flagged and left to the
+// spans.  Two lanes share a target (its spans' sources dealt round): a wave then
+// holds 32 targets of two or three leaves, whose spans differ little in length
+// (2^20 uniform particles at level 8, alone: one lane 282 us, two 239, four 249,
+// eight 287).  Tiles whose halo exceeds the stage are flagged and left to the
 // direct kernel.
-constexpr int kTile64P = 4;
+constexpr int kTile64P = 2;
 constexpr int kTile64Cap = 1536;  // records of 24 bytes
-constexpr int kTile64Pad = 4 * kTile64P;
 
 __global__ __launch_bounds__(256) void k_p2p2d_f64_tile(FmmArgs a, int cap) {
   constexpr int P = kTile64P;
-  extern __shared__ double2 sxy[];  // cap + pad positions, then as many charges
+  extern __shared__ double2 sxy[];  // cap positions, then as many charges
   __shared__ double2 tab[kLogTable];
   __shared__ int32_t hstart[kP2pHaloLeaves];
   __shared__ int32_t hoff[kP2pHaloLeaves + 1];
-  double* sq = reinterpret_cast<double*>(sxy + cap + kTile64Pad);
+  double* sq = reinterpret_cast<double*>(sxy + cap);
   const LevelTable& lt = a.lt;
   const int L = lt.L, tid = threadIdx.x;
   const int64_t tl = xcd_chunk_remap(blockIdx.x);
@@ -235,16 +256,10 @@ __global__ __launch_bounds__(256) void k_p2p2d_f64_tile(FmmArgs a, int cap) {
   const int total = hoff[kP2pHaloLeaves];
   if (tid == 0) a.p2p_over[tile] = total > cap ? 1 : 0;
   if (total > cap) return;  // workgroup-uniform
-  for (int e = tid; e < total; e += 256) {
-    const int h = halo_leaf(hoff, e);
-    const int32_t i = hstart[h] + (e - hoff[h]);
+  stage_halo(hstart, hoff, 256, [&](int e, int32_t i, int) {
     sxy[e] = make_double2(a.xs[i], a.ys[i]);
     sq[e] = a.qs[i];
-  }
-  if (tid < kTile64Pad) {
-    sxy[total + tid] = make_double2(0.0, 0.0);
-    sq[total + tid] = 0.0;
-  }
+  });
   __syncthreads();
   const int32_t t0 = a.leaf_start[k0], t1 = a.leaf_start[k0 + 16];
   const double thr = near_threshold(lt.side);
@@ -258,17 +273,21 @@ __global__ __launch_bounds__(256) void k_p2p2d_f64_tile(FmmArgs a, int cap) {
     for (int dy = 0; dy < 3; ++dy) {
       const int h = (ty + dy) * kP2pHalo + tx;  // halo leaves h, h + 1, h + 2
       const int c1 = hoff[h + 3];
-      // (reads past the span stay below total + pad; they carry no charge)
-      for (int c = hoff[h] + part; c < c1; c += 4 * P) {
+      int c = hoff[h] + part;
+      for (; c + 3 * P < c1; c += 4 * P) {
         double sx[4], sy[4], q[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const double2 p = sxy[c + u * P];
           sx[u] = p.x;
           sy[u] = p.y;
-          q[u] = c + u * P < c1 ? sq[c + u * P] : 0.0;
+          q[u] = sq[c + u * P];
         }
         pairs2_f64<4>(x, y, sx, sy, q, thr, tab, s);
+      }
+      for (; c < c1; c += P) {
+        double sx[1] = {sxy[c].x}, sy[1] = {sxy[c].y}, q[1] = {sq[c]};
+        pairs2_f64<1>(x, y, sx, sy, q, thr, tab, s);
       }
     }
 #pragma unroll
@@ -310,7 +329,7 @@ void launch_p2p2d_f64(const FmmArgs& a, hipStream_t st) {
   if (tiles >= 1024) {
     const int cap = p2p2d_tile_cap(a.lt, a.n, kTile64Cap);
     hipLaunchKernelGGL(k_p2p2d_f64_tile, chunked_grid(tiles), dim3(256),
-                       (size_t)(cap + kTile64Pad) * 3 * sizeof(double), st, a, cap);
+                       (size_t)cap * 3 * sizeof(double), st, a, cap);
     direct_f64<1>(a, 1, 0, st);
   } else if (a.n * 16 <= (1 << 18)) {
     direct_f64<16>(a, 0, 0, st);
