@@ -350,8 +350,9 @@ int fmm_mlp_train(float* w, const float* x, const float* t, int64_t m, int32_t s
  * plan's precision and order and within the LDS, tiles dealt to the XCDs in
  * contiguous ranges if xcd_remap = 1.  3D: 4 tile_mb layers of 16 targets per
  * workgroup, tile_mb in {1, 2} (four waves of tile_mb layers) or, FP32 only, 4
- * (eight waves of two layers); each operator value read from LDS serves the
- * products of a wave's layers; xcd_remap = 1 only.  Anything else: FMM_ERR_INVALID_ARG.  Every
+ * (eight waves of two layers; FP64, tile_mb 1, levels from 5 on: eight waves of
+ * one layer); each operator value read from LDS serves the products of a wave's
+ * layers; xcd_remap = 1 only.  Anything else: FMM_ERR_INVALID_ARG.  Every
  * variant forms the same sums in the same order: results are bit-identical. */
 int fmm_set_m2l_variant(fmm_plan_t plan, int32_t tile_mb, int32_t xcd_remap);
 

@@ -482,7 +482,7 @@ int fmm_plan(const fmm_options* opt, fmm_plan_t* out) {
   rc |= dalloc(pl, &pl->near_ex, N);
   rc |= dalloc(pl, &pl->near_ey, N);
   if (dim == 3) rc |= dalloc(pl, &pl->near_ez, N);
-  if (dim == 3) rc |= dalloc(pl, &pl->m2l_part, m2l3d_partial_entries(pl->cs));
+  if (dim == 3) rc |= dalloc(pl, &pl->m2l_part, m2l3d_partial_entries(pl->cs, lt.L));
   if (rc) {
     free_plan(pl);
     return FMM_ERR_NOMEM;

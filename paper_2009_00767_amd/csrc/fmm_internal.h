@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "../../include/fmm.h"
 
 namespace sffmm {
@@ -218,10 +220,19 @@ size_t p2m3d_partial_entries(int klo, int khi, int64_t maxn, int cs);
 // 3D M2L; a.m2l_mb: 4 a.m2l_mb layers of 16 targets per workgroup.
 void launch_m2l3d(const FmmArgs& a, bool fp64, hipStream_t st);
 bool m2l3d_variant_ok(int mb, bool fp64);
-// Levels 2..kM2l3SplitLevel (8 tiles each) run their 189 offsets as kM2l3Split
-// chunks on as many workgroups; partial rows for the 64 + 512 boxes of those levels.
-constexpr int kM2l3Split = 27, kM2l3SplitLevel = 3, kM2l3SplitBoxes = 64 + 512;
-inline size_t m2l3d_partial_entries(int cs) { return (size_t)kM2l3Split * kM2l3SplitBoxes * cs; }
+// Levels 2..kM2l3SplitLevel run their 189 offsets in chunks (27 at levels 2 and 3,
+// 8 tiles each; 4 at level 4) on as many workgroups; partial rows of level k:
+// chunk c's boxes at m2l3_split_row(k) + c 8^k.
+constexpr int kM2l3SplitLevel = 4;
+constexpr int m2l3_split_of(int k) { return k <= 3 ? 27 : 4; }
+constexpr int64_t m2l3_split_row(int k) {
+  int64_t r = 0;
+  for (int j = 2; j < k; ++j) r += (int64_t)m2l3_split_of(j) << (3 * j);
+  return r;
+}
+inline size_t m2l3d_partial_entries(int cs, int levels) {
+  return (size_t)m2l3_split_row(std::min(levels, kM2l3SplitLevel) + 1) * cs;
+}
 void launch_l2p3d(const FmmArgs& a, bool leaf_local, hipStream_t st);
 void launch_p2p3d(const FmmArgs& a, bool leaf_local, hipStream_t st);
 

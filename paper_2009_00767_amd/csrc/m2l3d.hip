@@ -12,12 +12,22 @@
 // operator value read from LDS serving MB of them.  The operators stream from
 // beyond the L2 (the 3D pack outgrows an XCD's L2), so the more targets a
 // workgroup holds, the less operator traffic per target.
-// The operator of the next offset is prefetched into registers while the
-// current one is in use and double-buffered in LDS, in the lane-major order in
-// which the MFMA steps consume it (conflict-free LDS reads); source moments are
-// read straight from global memory (each is used by one target per offset).
+// The operator of the next offset is copied straight from global memory into
+// the other of two LDS buffers while the current one is in use (the FP64
+// operators of 125 point charges, which leave room for one buffer, pass through
+// registers), in the lane-major order in which the MFMA steps consume it
+// (conflict-free LDS reads).  Source moments are read straight from global
+// memory (each is used by one target per offset): the next offset's row takes
+// the registers of the current one part by part, as the steps finish with them.
 // The degree-0 input enters as one more MFMA step (K = 1, lane group 0); the
 // degree-0 output uses VALU fused multiply-adds.
+// Bound by the matrix cores and, near their peak, by the clock they run at.
+// Measured (FP32, order 8, 2^22 particles at level 7): 63.9 -> 52 ms; with operator
+// values read from LDS right before their use, and rows waited for at the head
+// of an offset, the cores were busy 0.64 of the time, now 0.81 of the time a CU
+// holds work.
+#include <type_traits>
+
 #include "device_common.h"
 #include "points3d.h"
 
@@ -46,6 +56,27 @@ struct Mfma16x<double> {
   }
 };
 
+// Copies 16 bytes a lane from global memory to LDS without passing through
+// registers: lane l's go to dst + 16 l (dst uniform over the wave).
+__device__ __forceinline__ void lds_copy16(const void* src, void* dst) {
+  __builtin_amdgcn_global_load_lds(
+      (const __attribute__((address_space(1))) void*)(uintptr_t)src,
+      (__attribute__((address_space(3))) void*)(uint32_t)(uintptr_t)dst, 16, 0, 0);
+}
+// Waits until at most `newer` (0, 2 or 4) of this wave's vector memory accesses are
+// outstanding; they return in order, so all but the `newer` issued last have
+// arrived.  Nothing is moved across it.
+__device__ __forceinline__ void lds_copy_wait(int newer) {
+  __builtin_amdgcn_sched_barrier(0);
+  if (newer == 4)
+    __builtin_amdgcn_s_waitcnt(0x0f74);
+  else if (newer == 2)
+    __builtin_amdgcn_s_waitcnt(0x0f72);
+  else
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // LDS of a workgroup: the operator slot double-buffered where two fit the
 // 160 KB of a CU, else one buffer (the 128 x 128 point-charge operators of
 // n = 5 in FP64), refilled between two barriers.
@@ -54,12 +85,16 @@ __host__ __device__ constexpr int m2l3_lds_slots() {
   return 2 * (64 * (NB * (KS + 1) + KS) + 4) * (int)sizeof(T) <= 160 * 1024 ? 2 : 1;
 }
 
+// The row of a source outside the grid (a select on the values would wait for
+// their loads where they are issued).
+static __device__ const double g_zero_row[128] = {0};
+
 struct M2l3Tiles {
   int klo, khi;
-  int64_t off[kMaxLevels3D + 2];  // first block of level k
+  int64_t off[kMaxLevels3D + 2];  // first block of level k (split launches: finest level first)
   int64_t nblocks;
   int nsplit[kMaxLevels3D + 2];     // offset chunks per tile at level k (1: no split)
-  int64_t pbase[kMaxLevels3D + 2];  // level k's first box row in the partial buffer
+  int64_t pbase[kMaxLevels3D + 2];  // level k's first row in the partial buffer
 };
 
 // Accumulator register r of lane group g holds output row 4g + r (FP32) or
@@ -70,7 +105,7 @@ __device__ __forceinline__ int crow3(int r, int g) {
 }
 
 template <typename T, int KS, int NB, int MB, int NW, bool SPLIT>
-__global__ __launch_bounds__(64 * NW) void k_m2l3d_mfma(FmmArgs a, M2l3Tiles tt, M2lLayout ly) {
+__global__ __launch_bounds__(64 * NW, sizeof(T) == 4 && KS < 32 ? 2 : 1) void k_m2l3d_mfma(FmmArgs a, M2l3Tiles tt, M2lLayout ly) {
   using acc_t = typename Mfma16x<T>::acc_t;
   using vec_t = typename Mfma16x<T>::vec_t;
   constexpr int VW = sizeof(vec_t) / sizeof(T);  // values per vector load
@@ -85,12 +120,16 @@ __global__ __launch_bounds__(64 * NW) void k_m2l3d_mfma(FmmArgs a, M2l3Tiles tt,
   T* wb0 = reinterpret_cast<T*>(smem_raw);
   T* wb1 = kDB ? wb0 + WLDS : wb0;
 
-  const int64_t blk = xcd_remap(blockIdx.x, tt.nblocks);
-  int k = tt.klo;
-  while (k < tt.khi && blk >= tt.off[k + 1]) ++k;
-  // small levels: ns workgroups per tile, each over its own chunk of the 189
-  // offsets, writing FP64 partial sums (added in chunk order by k_m2l3d_reduce)
-  const int ns = SPLIT ? kM2l3Split : 1;
+  // split levels, finest first: ns workgroups per tile, each over its own chunk
+  // of the 189 offsets, writing FP64 partial sums (added in chunk order by
+  // k_m2l3d_reduce)
+  const int64_t blk = SPLIT ? (int64_t)blockIdx.x : xcd_remap(blockIdx.x, tt.nblocks);
+  int k = SPLIT ? tt.khi : tt.klo;
+  if (SPLIT)
+    while (k > tt.klo && blk >= tt.off[k - 1]) --k;
+  else
+    while (k < tt.khi && blk >= tt.off[k + 1]) ++k;
+  const int ns = SPLIT ? tt.nsplit[k] : 1;
   const int chunk = SPLIT ? (int)((blk - tt.off[k]) % ns) : 0;
   const int64_t local = SPLIT ? (blk - tt.off[k]) / ns : blk - tt.off[k];
   const int n = 1 << k;
@@ -122,8 +161,9 @@ __global__ __launch_bounds__(64 * NW) void k_m2l3d_mfma(FmmArgs a, M2l3Tiles tt,
   T* loc = (kF64 ? (T*)a.loc64 : (T*)a.loc32) + a.lt.off[k] * cs;
   const T* ops = kF64 ? (const T*)a.opl64 : (const T*)a.opl32;
   const int i00 = ly.nr - 1;  // index of the degree-0 value
+  const int64_t zoff = reinterpret_cast<const T*>(g_zero_row) - mom;
 
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, g = lane >> 4;
   const int tx = tx0 + 2 * (i & 3) + px, ty = ty0 + 2 * (i >> 2) + py;
   int tzm[MB];  // the z of this lane's target in each of the wave's layers
@@ -136,11 +176,8 @@ __global__ __launch_bounds__(64 * NW) void k_m2l3d_mfma(FmmArgs a, M2l3Tiles tt,
   // read sources of the same x parity, three quarters of them the same boxes,
   // which the L2 still holds.
   auto xstep = [](int r) { return r < 3 ? 2 * r : 2 * r - 5; };
-  auto slot_of = [&](int q, int& dx, int& dy, int& dz) -> int {
-    dx = xlo + xstep(q % 6);
-    dy = ylo + (q / 6) % 6;
-    dz = zlo + q / 36;
-    return (dx + 3) + 7 * (dy + 3) + 49 * (dz + 3);
+  auto slot_of = [&](int q) -> int {
+    return (xlo + xstep(q % 6) + 3) + 7 * (ylo + (q / 6) % 6 + 3) + 49 * (zlo + q / 36 + 3);
   };
   auto adjacent = [&](int q, int xl, int yl, int zl) {
     const int dx = xl + xstep(q % 6), dy = yl + (q / 6) % 6, dz = zl + q / 36;
@@ -173,151 +210,171 @@ __global__ __launch_bounds__(64 * NW) void k_m2l3d_mfma(FmmArgs a, M2l3Tiles tt,
     }
   }
 
-  // W of offset q: global slot -> registers (fetch) -> LDS (store), lane-major as in memory
-#define SFFMM_FETCH(qq)                                                                      \
-  {                                                                                          \
-    int fx, fy, fz;                                                                          \
-    const vec_t* W = reinterpret_cast<const vec_t*>(ops + (size_t)slot_of(qq, fx, fy, fz) *  \
-                                                                 WGLB);                     \
-    _Pragma("unroll") for (int u = 0; u < PRE; ++u) {                                        \
-      const int e = tid + NT * u;                                                            \
-      pre[u] = W[e < NV ? e : NV - 1];                                                       \
-    }                                                                                        \
-  }
-#define SFFMM_STORE(buf)                                                                     \
-  {                                                                                          \
-    _Pragma("unroll") for (int u = 0; u < PRE; ++u) {                                        \
-      const int e = (tid + NT * u) * VW;                                                     \
-      if (e < WGLB) *reinterpret_cast<vec_t*>((buf) + e) = pre[u];                           \
-    }                                                                                        \
-  }
-  vec_t pre[PRE];
-  int q = SPLIT ? nth_q(chunk * 189 / ns) : next_q(-1);
-  SFFMM_FETCH(q);
-  SFFMM_STORE(wb0);
-  __syncthreads();
-  T* cur = wb0;
-  T* nxt = wb1;
-  // source row of offset qq for this lane's target in layer tz (zeros outside
-  // the grid); in FP64 the next offset's is loaded while the current one is
-  // contracted
-#define SFFMM_LOADA(qq, tz, AV, A0)                                                          \
-  {                                                                                          \
-    int ex, ey, ez;                                                                          \
-    (void)slot_of(qq, ex, ey, ez);                                                           \
-    const int sx = tx + ex, sy = ty + ey, sz = (tz) + ez;                                    \
-    const bool ok = sx >= 0 && sy >= 0 && sz >= 0 && sx < n && sy < n && sz < n && tx < n && \
-                    ty < n && (tz) < n;                                                      \
-    const T* A = mom + (ok ? (int64_t)(spread3(sx) | (spread3(sy) << 1) | (spread3(sz) << 2)) * cs : 0); \
-    if constexpr ((KS * sizeof(T)) % 16 == 0) {                                              \
-      const vec_t* Av = reinterpret_cast<const vec_t*>(A + g * KS);                          \
-      _Pragma("unroll") for (int u = 0; u < KS / VW; ++u) {                                  \
-        const vec_t v = Av[u];                                                               \
-        _Pragma("unroll") for (int c = 0; c < VW; ++c) AV[VW * u + c] = ok ? v[c] : (T)0;    \
-      }                                                                                      \
-    } else {                                                                                 \
-      _Pragma("unroll") for (int s = 0; s < KS; ++s) AV[s] = ok ? A[g * KS + s] : (T)0;      \
-    }                                                                                        \
-    A0 = ok ? A[i00] : (T)0;                                                                 \
-  }
-  // (FP64 with one layer only: in FP32, or with two layers, the registers of
-  // a second row cost more than the latency they hide; not for K = 128)
-  constexpr bool kPrefA = kF64 && MB == 1 && KS < 32;
-  T avn[KS], a0n = 0;
-  if (kPrefA) SFFMM_LOADA(q, tzm[0], avn, a0n);
-  while (q < q_stop) {
-    const int qn = next_q(q);
-    if (qn < q_stop) SFFMM_FETCH(qn);
-    T av[MB][KS], a0[MB];
-    if (kPrefA) {
+  // Operator of offset qq into LDS, lane-major as in memory (kDB: straight to
+  // LDS, no registers; else through registers, fetched early and stored late).
+  vec_t pre[kDB ? 1 : PRE];
+  auto fetch = [&](int qq, T* buf) {
+    const vec_t* W = reinterpret_cast<const vec_t*>(ops + (size_t)slot_of(qq) * WGLB);
 #pragma unroll
-      for (int s = 0; s < KS; ++s) av[0][s] = avn[s];
-      a0[0] = a0n;
-      if (qn < q_stop) SFFMM_LOADA(qn, tzm[0], avn, a0n);
-    } else {
-#pragma unroll
-      for (int m = 0; m < MB; ++m) SFFMM_LOADA(q, tzm[m], av[m], a0[m]);
-    }
-    const T* Wl = cur;
-#ifdef V_NBIN
-    if constexpr (true) {
-#pragma unroll
-      for (int s = 0; s < KS; ++s)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          const T wv = Wl[((size_t)nb * (KS + 1) + s) * 64 + lane];
-#pragma unroll
-          for (int m = 0; m < MB; ++m) acc[m][nb] = Mfma16x<T>::op(av[m][s], wv, (s == 0 && !kF64) ? acc_t{0,0,0,0} : acc[m][nb]);
-        }
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const T wv = Wl[((size_t)nb * (KS + 1) + KS) * 64 + lane];
-#pragma unroll
-        for (int m = 0; m < MB; ++m) acc[m][nb] = Mfma16x<T>::op(g == 0 ? a0[m] : (T)0, wv, acc[m][nb]);
-      }
-    } else
-#endif
-    if constexpr (KS == 32) {
-      // one layer per wave and one wave per SIMD: the NB output blocks in the
-      // inner loop, so consecutive products go to independent accumulators
-#pragma unroll
-      for (int s = 0; s < KS; ++s)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-          acc[0][nb] = Mfma16x<T>::op(av[0][s], Wl[((size_t)nb * (KS + 1) + s) * 64 + lane],
-                                      acc[0][nb]);
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)  // the degree-0 input step (K = 1, lane group 0)
-        acc[0][nb] = Mfma16x<T>::op(g == 0 ? a0[0] : (T)0,
-                                    Wl[((size_t)nb * (KS + 1) + KS) * 64 + lane], acc[0][nb]);
-    } else {
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const T* Wb = Wl + (size_t)nb * (KS + 1) * 64 + lane;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-          const T wv = Wb[s * 64];
-#pragma unroll
-          for (int m = 0; m < MB; ++m) acc[m][nb] = Mfma16x<T>::op(av[m][s], wv, acc[m][nb]);
-        }
-        const T wv = Wb[KS * 64];
-#pragma unroll
-        for (int m = 0; m < MB; ++m)  // the degree-0 input step (K = 1, lane group 0)
-          acc[m][nb] = Mfma16x<T>::op(g == 0 ? a0[m] : (T)0, wv, acc[m][nb]);
+    for (int u = 0; u < PRE; ++u) {
+      const int e0 = NT * u + 64 * w, e = e0 + lane;
+      if constexpr (kDB) {
+        if ((u + 1) * NT <= NV || e < NV) lds_copy16(W + e, buf + (size_t)e0 * VW);
+      } else {
+        pre[u] = W[e < NV ? e : NV - 1];
       }
     }
-    const T* R = Wl + (size_t)NB * (KS + 1) * 64;
+  };
+  // `newer`: loads issued after the copies that need not have arrived.
+  auto settle = [&](T* buf, int newer) {
+    if constexpr (kDB) {
+      lds_copy_wait(newer);
+    } else {
+#pragma unroll
+      for (int u = 0; u < PRE; ++u) {
+        const int e = (tid + NT * u) * VW;
+        if (e < WGLB) *reinterpret_cast<vec_t*>(buf + e) = pre[u];
+      }
+    }
+  };
+  // Source rows of offset qq for this lane's targets (the zero row outside the
+  // grid).  The y and z parts of the box index change every sixth offset only.
+  uint32_t yz[MB];
+  bool yzok[MB];
+  int qyz = -1;
+  auto find_rows = [&](int qq, const T* (&row)[MB]) {
+    if (qq / 6 != qyz) {  // (uniform)
+      qyz = qq / 6;
+      const int sy = ty + ylo + qyz % 6, dz = zlo + qyz / 6;
+#pragma unroll
+      for (int m = 0; m < MB; ++m) {
+        const int sz = tzm[m] + dz;
+        yzok[m] = sy >= 0 && sy < n && sz >= 0 && sz < n && tx < n && ty < n && tzm[m] < n;
+        yz[m] = (spread3((uint32_t)sy) << 1) | (spread3((uint32_t)sz) << 2);
+      }
+    }
+    const int sx = tx + xlo + xstep(qq % 6);
+    const bool xok = sx >= 0 && sx < n;
+    const uint32_t xs = spread3((uint32_t)sx);
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+      row[m] = mom + (xok && yzok[m] ? (int64_t)(xs | yz[m]) * cs : zoff);
+  };
+  // Values s0 .. s0 + RW - 1 of this lane's part of a row (one load).
+  constexpr int RW = (KS * sizeof(T)) % 16 == 0 ? VW : 1;
+  auto load_part = [&](const T* (&row)[MB], int s0, T (&av)[MB][KS]) {
 #pragma unroll
     for (int m = 0; m < MB; ++m) {
-      T b0o = 0;
+      if constexpr (RW == 1) {
+        av[m][s0] = row[m][g * KS + s0];
+      } else {
+        const vec_t v = *reinterpret_cast<const vec_t*>(row[m] + g * KS + s0);
 #pragma unroll
-      for (int s = 0; s < KS; ++s) b0o += R[s * 64 + lane] * av[m][s];
-      if (g == 0) b0o += R[KS * 64] * a0[m];  // degree 0 -> degree 0
-      b0p[m] += (double)b0o;
+        for (int c = 0; c < RW; ++c) av[m][s0 + c] = v[c];
+      }
     }
+  };
+  // The products of the rows av, a0 with the operator in Wl, step by step: the
+  // NB output blocks of a step follow each other, on independent accumulators,
+  // while the next step's operator values are on their way from LDS (left to
+  // itself the compiler read them just before their use and waited: 0.64 of
+  // the matrix cores' time).  RELOAD: a part of the rows is dead after its last
+  // step, and the next offset's takes its registers.
+  auto contract = [&](auto reload, const T* Wl, T (&av)[MB][KS], T (&a0)[MB],
+                      const T* (&row)[MB]) {
+    constexpr bool kReload = decltype(reload)::value;
+    constexpr acc_t zero = {0, 0, 0, 0};
+    const T* R = Wl + (size_t)NB * (KS + 1) * 64;
+    T wv[2][NB + 1];  // a step's operator values and its degree-0 output weight
+    auto read = [&](int s, T (&d)[NB + 1]) {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) d[nb] = Wl[(nb * (KS + 1) + s) * 64 + lane];
+      d[NB] = s < KS ? R[s * 64 + lane] : R[KS * 64];
+    };
+    T b0o[MB];
+#pragma unroll
+    for (int m = 0; m < MB; ++m) b0o[m] = (T)0;
+    read(0, wv[0]);
+#pragma unroll
+    for (int s = 0; s <= KS; ++s) {  // (step KS: the degree-0 input, K = 1, lane group 0)
+      if (s < KS) read(s + 1, wv[(s + 1) & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+          acc[m][nb] = Mfma16x<T>::op(s < KS ? av[m][s < KS ? s : 0] : g == 0 ? a0[m] : (T)0,
+                                      wv[s & 1][nb], s == 0 && !kF64 ? zero : acc[m][nb]);
+#pragma unroll
+      for (int m = 0; m < MB; ++m) {
+        if (s < KS)
+          b0o[m] = fma(wv[s & 1][NB], av[m][s < KS ? s : 0], b0o[m]);
+        else if (g == 0)
+          b0o[m] = fma(wv[s & 1][NB], a0[m], b0o[m]);  // degree 0 -> degree 0
+      }
+      if constexpr (kReload) {
+        if (s < KS && s % RW == RW - 1) load_part(row, s - RW + 1, av);
+        if (s == KS)
+#pragma unroll
+          for (int m = 0; m < MB; ++m) a0[m] = row[m][i00];
+      }
+    }
+#pragma unroll
+    for (int m = 0; m < MB; ++m) b0p[m] += (double)b0o[m];
     if constexpr (!kF64) {
 #pragma unroll
       for (int m = 0; m < MB; ++m)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
+        for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
           for (int r = 0; r < 4; ++r) sum[m][nb][r] += (double)acc[m][nb][r];
-#ifndef V_NBIN
-          acc[m][nb] = acc_t{0, 0, 0, 0};
-#endif
-        }
     }
-    if constexpr (!kDB) __syncthreads();  // every wave done with the one buffer
-    if (qn < q_stop) SFFMM_STORE(nxt);
-    __syncthreads();
-    T* t = cur;
-    cur = nxt;
-    nxt = t;
-    q = qn;
+  };
+
+  int q = SPLIT ? nth_q(chunk * 189 / ns) : next_q(-1);
+  const T* row[MB];
+  T av[MB][KS], a0[MB];
+  fetch(q, wb0);
+  find_rows(q, row);
+#pragma unroll
+  for (int s = 0; s < KS; s += RW) load_part(row, s, av);
+#pragma unroll
+  for (int m = 0; m < MB; ++m) a0[m] = row[m][i00];
+  settle(wb0, 0);
+  __syncthreads();
+  if constexpr (kDB) {
+    T* cur = wb0;
+    T* nxt = wb1;
+    for (;;) {
+      // past the last offset a repeat of it, never used: the same loads and
+      // copies are in flight on every path
+      const int qn = next_q(q);
+      const bool more = qn < q_stop;
+      fetch(more ? qn : q, nxt);
+      find_rows(more ? qn : q, row);
+      contract(std::true_type{}, cur, av, a0, row);
+      settle(nxt, 2 * MB);
+      __syncthreads();
+      if (!more) break;
+      T* t = cur;
+      cur = nxt;
+      nxt = t;
+      q = qn;
+    }
+  } else {
+    for (;;) {
+      const int qn = next_q(q);
+      const bool more = qn < q_stop;
+      fetch(more ? qn : q, wb0);
+      find_rows(more ? qn : q, row);
+      contract(std::true_type{}, wb0, av, a0, row);
+      if (!more) break;
+      __syncthreads();  // every wave done with the one buffer
+      settle(wb0, 0);
+      __syncthreads();
+      q = qn;
+    }
   }
-#undef SFFMM_FETCH
-#undef SFFMM_STORE
-#undef SFFMM_LOADA
   const int nout = ly.nr - 1;
 #pragma unroll
   for (int m = 0; m < MB; ++m) {
@@ -333,7 +390,7 @@ __global__ __launch_bounds__(64 * NW) void k_m2l3d_mfma(FmmArgs a, M2l3Tiles tt,
       if (gx < n && gy < n && tz < n) {
         const int64_t bx = (int64_t)(spread3(gx) | (spread3(gy) << 1) | (spread3(tz) << 2));
         if constexpr (SPLIT) {
-          double* pdst = a.m2l_part + ((int64_t)chunk * kM2l3SplitBoxes + tt.pbase[k] + bx) * cs;
+          double* pdst = a.m2l_part + (tt.pbase[k] + ((int64_t)chunk << (3 * k)) + bx) * cs;
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb) {
             const int j = 16 * nb + i;
@@ -352,7 +409,7 @@ __global__ __launch_bounds__(64 * NW) void k_m2l3d_mfma(FmmArgs a, M2l3Tiles tt,
     if (g == 0 && tx < n && ty < n && tz < n) {
       const int64_t bx = (int64_t)(spread3(tx) | (spread3(ty) << 1) | (spread3(tz) << 2));
       if constexpr (SPLIT)
-        a.m2l_part[((int64_t)chunk * kM2l3SplitBoxes + tt.pbase[k] + bx) * cs + i00] = b0;
+        a.m2l_part[(tt.pbase[k] + ((int64_t)chunk << (3 * k)) + bx) * cs + i00] = b0;
       else
         loc[bx * cs + i00] = (T)b0;
     }
@@ -368,7 +425,7 @@ __global__ void k_m2l3d_reduce(const double* part, T* loc, int64_t nbox, int cs,
   const int64_t b = g / nr;
   const int j = (int)(g - b * nr);
   double s = 0.0;
-  for (int c = 0; c < ns; ++c) s += part[((int64_t)c * kM2l3SplitBoxes + pbase + b) * cs + j];
+  for (int c = 0; c < ns; ++c) s += part[(pbase + c * nbox + b) * cs + j];
   loc[b * cs + j] = (T)s;
 }
 
@@ -391,21 +448,24 @@ static void m2l3_launch(const FmmArgs& a, const M2l3Tiles& tt, const M2lLayout& 
     }
 }
 
-// Tile variant mb: 4 mb layers of 16 targets per workgroup (mb = 4: eight
-// waves of two layers; FP32 only, the FP64 registers of two layers leave room
-// for one wave per SIMD).
+// Tile variant mb: 4 mb layers of 16 targets per workgroup (mb = 4, FP32 only:
+// eight waves of two layers).  FP64, mb = 1: eight waves of one layer where the
+// levels run unsplit: an operator pair of order 8 fills the LDS of a CU, and one
+// workgroup of four waves left each SIMD a single wave, which nothing overlaps
+// (300,007 particles, level 5, order 8: 2.17 -> 2.00 ms a step).
 template <typename T, int KS, int NB, bool SPLIT>
 static void m2l3_mb(const FmmArgs& a, const M2l3Tiles& tt, const M2lLayout& ly, hipStream_t st) {
   if constexpr (KS == 32) {  // K = N = 128: one layer per wave, one workgroup per CU
     m2l3_launch<T, KS, NB, 1, 4, SPLIT>(a, tt, ly, st);
-  } else {
-    if constexpr (sizeof(T) == 4) {
-      if (a.m2l_mb == 4) {
-        m2l3_launch<T, KS, NB, 2, 8, SPLIT>(a, tt, ly, st);
-        return;
-      }
-    }
+  } else if constexpr (sizeof(T) == 8) {
     if (a.m2l_mb == 2)
+      m2l3_launch<T, KS, NB, 2, 4, SPLIT>(a, tt, ly, st);
+    else
+      m2l3_launch<T, KS, NB, 1, SPLIT ? 4 : 8, SPLIT>(a, tt, ly, st);
+  } else {
+    if (a.m2l_mb == 4)
+      m2l3_launch<T, KS, NB, 2, 8, SPLIT>(a, tt, ly, st);
+    else if (a.m2l_mb == 2)
       m2l3_launch<T, KS, NB, 2, 4, SPLIT>(a, tt, ly, st);
     else
       m2l3_launch<T, KS, NB, 1, 4, SPLIT>(a, tt, ly, st);
@@ -427,14 +487,17 @@ void launch_m2l3d(const FmmArgs& a, bool fp64, hipStream_t st) {
   if (a.khi < a.klo) return;
   const M2lLayout ly = a.basis ? points3d_layout_n(a.p) : m2l3d_layout(order_bucket3(a.p));
   const int mb = ly.kpad == 128 ? 1 : m2l3d_variant_ok(a.m2l_mb, fp64) ? a.m2l_mb : 1;
-  const int zl = 4 * mb;  // same-parity z-layers per block
   FmmArgs am = a;
   am.m2l_mb = mb;
-  // levels 2 and 3 have 8 tiles each: their own launch splits each tile's
-  // offsets over kM2l3Split workgroups; the larger levels run unsplit
+  // Levels 2..4 have 8, 8 and (of four layers) 64 tiles: their own launch splits
+  // each tile's offsets over several workgroups; the finer levels, whose tiles
+  // are multiples of the 256 CUs, run unsplit (level 5 in FP64: two even rounds
+  // where its 512 and level 4's 64 tiles made three).
   const int ksplit = a.m2l_part ? std::min(a.khi, kM2l3SplitLevel) : a.klo - 1;
   for (int part = 0; part < 2; ++part) {
     const bool split = part == 0;
+    // same-parity z-layers per block (m2l3_mb)
+    const int zl = fp64 && mb == 1 && !split && ly.kpad < 128 ? 8 : 4 * mb;
     const int klo = split ? a.klo : std::max(a.klo, ksplit + 1);
     const int khi = split ? ksplit : a.khi;
     if (khi < klo) continue;
@@ -442,15 +505,16 @@ void launch_m2l3d(const FmmArgs& a, bool fp64, hipStream_t st) {
     tt.klo = klo;
     tt.khi = khi;
     int64_t t = 0;
-    for (int k = klo; k <= khi; ++k) {
+    for (int i = 0; i <= khi - klo; ++i) {
+      const int k = split ? khi - i : klo + i;
       tt.off[k] = t;
       const int n = 1 << k;
       const int64_t nxy = n >= 8 ? n / 8 : 1, nz = n >= 2 * zl ? n / (2 * zl) : 1;
-      tt.nsplit[k] = split ? kM2l3Split : 1;
-      tt.pbase[k] = k == 3 ? 64 : 0;
+      tt.nsplit[k] = split ? m2l3_split_of(k) : 1;
+      tt.pbase[k] = split ? m2l3_split_row(k) : 0;
       t += 8 * nxy * nxy * nz * tt.nsplit[k];
     }
-    tt.off[khi + 1] = t;
+    if (!split) tt.off[khi + 1] = t;
     tt.nblocks = t;
     if (a.basis && ly.kpad == 128) {  // 125 point charges: K = N = 128
       if (fp64)
