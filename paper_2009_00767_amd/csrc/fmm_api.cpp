@@ -616,14 +616,19 @@ struct TreeRun {
                                 // sorted coordinates)
 };
 
-// Enqueues everything after the sort for one tree: leaf offsets, gather, then
-// the near field on the near-field stream beside the moments and M2L on the
-// caller's stream, the join, and local evaluation + unsort.
+// The phases of one tree after the sort.  prepare_tree: leaf offsets, gather and
+// adaptive depths (on st), and the argument block of the others.  enqueue_near:
+// the near field, which needs only that.  enqueue_far: moments and contractions;
+// in the FP32 modes first the small FP64 chain of level 2 (moments, then the
+// contraction on the VALU, which leaves most of the chip to the near field),
+// then the main level range.  enqueue_local: the local evaluation, which adds
+// near and far and scatters to input order.
 // io (batched graphs): the caller's buffers come from this device record,
 // not from pos / q / pot / field.
-void enqueue_tree(fmm_plan_s* pl, const TreeRun& t, const uint32_t* skeys, const int32_t* perm,
-                  const double* pos, const double* q, double* pot, double* field, hipStream_t st,
-                  hipEvent_t* ev, const float4* spts, const BatchIo* io = nullptr) {
+FmmArgs prepare_tree(fmm_plan_s* pl, const TreeRun& t, const uint32_t* skeys, const int32_t* perm,
+                     const double* pos, const double* q, double* pot, double* field,
+                     hipStream_t st, hipEvent_t* ev, const float4* spts,
+                     const BatchIo* io = nullptr) {
   const LevelTable& lt = t.lt;
   const int64_t nleaf = (int64_t)lt.nsys << (pl->dim * lt.L);
   const uint32_t* keys = skeys + t.p0;
@@ -683,50 +688,34 @@ void enqueue_tree(fmm_plan_s* pl, const TreeRun& t, const uint32_t* skeys, const
     a.adapt_open = pl->adapt_open;
     a.depth = pl->depth;
   }
-  const int hi64 = std::min(lt.L, lt.split - 1);
+  return a;
+}
+
+void enqueue_near(fmm_plan_s* pl, const FmmArgs& a, hipStream_t st) {
+  if (pl->dim == 2)
+    launch_p2p2d(a, pl->f32, st);
+  else
+    launch_p2p3d(a, pl->f32, st);
+}
+
+void enqueue_far(fmm_plan_s* pl, const FmmArgs& a, hipStream_t st, hipEvent_t* ev) {
+  const LevelTable& lt = a.lt;
   FmmArgs a64 = a, a32 = a;
   a64.klo = lt.kmin;
-  a64.khi = hi64;
+  a64.khi = std::min(lt.L, lt.split - 1);
   a32.klo = std::max(lt.split, lt.kmin);
   a32.khi = lt.L;
-  // Two streams after the sort: the near-field stream runs the near field,
-  // which needs only the sort and overlaps everything else; the caller's stream
-  // runs the far field: in the FP32 modes first the small FP64 chain of level 2
-  // (moments, then the contraction on the VALU, which leaves most of the chip to
-  // the near field), then the main level range.  The local evaluation joins both.
-  // (Measured slower, on a 1M-particle 2D FP32 evaluation at 0.34 ms: a third
-  // stream for the level-2 chain (the extra overlap only adds contention with
-  // the near field); forking after the moments, the near field beside the
-  // contractions only (0.38 ms); the roles of the two streams swapped, the
-  // near field on the caller's stream (0.36 ms: the moments chain then starts
-  // late and finishes behind the near field); and shortening this chain by
-  // appending the slice sums to later launches (0.36 ms: the main contraction
-  // then starts beside the near field's last workgroups); both together, the
-  // short moments chain forked and joined before the main contraction, came
-  // out even on that workload and slower on the batched and clustered ones.)
   const bool lvl64 = pl->f32 && a64.khi >= a64.klo;
-  (void)hipEventRecord(pl->fork_ev, st);
-  (void)hipStreamWaitEvent(pl->near, pl->fork_ev, 0);
-  if (ev && (pl->ev_mask >> 6 & 1)) (void)hipEventRecord(ev[6], pl->near);
-  if (pl->dim == 2)
-    launch_p2p2d(a, pl->f32, pl->near);
-  else
-    launch_p2p3d(a, pl->f32, pl->near);
-  if (ev && (pl->ev_mask >> 7 & 1)) (void)hipEventRecord(ev[7], pl->near);
-  (void)hipEventRecord(pl->near_ev, pl->near);
   FmmArgs& am = pl->f32 ? a32 : a64;  // the main level range
   if (pl->root) {
     // root frame (FP64): U-bar-1/U-bar-2 and the transfers into box frames,
-    // the contraction, the transfers back and D-bar-2, then F(v)
+    // the contraction, the transfers back and D-bar-2
     launch_root_upward(a64, pl->rbuf, st);
     if (ev && (pl->ev_mask >> 2 & 1)) (void)hipEventRecord(ev[2], st);
     launch_m2l3d(a64, true, st);
     if (ev && (pl->ev_mask >> 3 & 1)) (void)hipEventRecord(ev[3], st);
     launch_root_downward(a64, pl->rbuf, st);
     if (ev && (pl->ev_mask >> 4 & 1)) (void)hipEventRecord(ev[4], st);
-    (void)hipStreamWaitEvent(st, pl->near_ev, 0);
-    launch_root_eval(a, pl->rbuf, st);
-    if (ev && (pl->ev_mask >> 5 & 1)) (void)hipEventRecord(ev[5], st);
     return;
   }
   if (pl->dim == 2 && pl->basis) {
@@ -761,8 +750,12 @@ void enqueue_tree(fmm_plan_s* pl, const TreeRun& t, const uint32_t* skeys, const
     launch_m2l3d(am, !pl->f32, st);
   if (ev && (pl->ev_mask >> 3 & 1)) (void)hipEventRecord(ev[3], st);
   if (ev && (pl->ev_mask >> 4 & 1)) (void)hipEventRecord(ev[4], st);
-  (void)hipStreamWaitEvent(st, pl->near_ev, 0);
-  if (pl->dim == 2 && pl->basis)
+}
+
+void enqueue_local(fmm_plan_s* pl, const FmmArgs& a, hipStream_t st, hipEvent_t* ev) {
+  if (pl->root)
+    launch_root_eval(a, pl->rbuf, st);  // F(v)
+  else if (pl->dim == 2 && pl->basis)
     launch_l2p2d_points(a, pl->f32, st);
   else if (pl->dim == 2)
     launch_l2p2d(a, pl->f32, st);
@@ -771,6 +764,35 @@ void enqueue_tree(fmm_plan_s* pl, const TreeRun& t, const uint32_t* skeys, const
   else
     launch_l2p3d(a, pl->f32, st);
   if (ev && (pl->ev_mask >> 5 & 1)) (void)hipEventRecord(ev[5], st);
+}
+
+// Everything after the sort for one or several trees.  Two streams: the
+// near-field stream runs every tree's near field, which needs only the sort and
+// overlaps everything else; the caller's stream runs their far fields, then,
+// joined with the near fields, the local evaluations.  (With the trees one after
+// the other, near and far joined in each, the chip ran dry at every join: 256
+// systems of four depths 3.72 -> BATCHMS ms.)
+// (Measured slower, on a 1M-particle 2D FP32 evaluation at 0.34 ms: a third
+// stream for the level-2 chain (the extra overlap only adds contention with
+// the near field); forking after the moments, the near field beside the
+// contractions only (0.38 ms); the roles of the two streams swapped, the
+// near field on the caller's stream (0.36 ms: the moments chain then starts
+// late and finishes behind the near field); and shortening this chain by
+// appending the slice sums to later launches (0.36 ms: the main contraction
+// then starts beside the near field's last workgroups); both together, the
+// short moments chain forked and joined before the main contraction, came
+// out even on that workload and slower on the batched and clustered ones.)
+void enqueue_trees(fmm_plan_s* pl, const std::vector<FmmArgs>& trees, hipStream_t st,
+                   hipEvent_t* ev) {
+  (void)hipEventRecord(pl->fork_ev, st);
+  (void)hipStreamWaitEvent(pl->near, pl->fork_ev, 0);
+  if (ev && (pl->ev_mask >> 6 & 1)) (void)hipEventRecord(ev[6], pl->near);
+  for (const FmmArgs& a : trees) enqueue_near(pl, a, pl->near);
+  if (ev && (pl->ev_mask >> 7 & 1)) (void)hipEventRecord(ev[7], pl->near);
+  (void)hipEventRecord(pl->near_ev, pl->near);
+  for (const FmmArgs& a : trees) enqueue_far(pl, a, st, ev);
+  (void)hipStreamWaitEvent(st, pl->near_ev, 0);
+  for (const FmmArgs& a : trees) enqueue_local(pl, a, st, ev);
 }
 
 // ----- M2L autotuner (2D) -----
@@ -1011,7 +1033,7 @@ int fmm_eval(fmm_plan_t pl, int64_t n, const double* pos, const double* q, doubl
   t.lt = pl->lt;
   t.n = n;
   t.sorted = one || two_digit;
-  enqueue_tree(pl, t, skeys, perm, pos, q, pot, field, st, ev, spts);
+  enqueue_trees(pl, {prepare_tree(pl, t, skeys, perm, pos, q, pot, field, st, ev, spts)}, st, ev);
   if (timing) {
     pl->ring_batched[pl->ring_next] = false;
     ring_advance(pl);
@@ -1189,11 +1211,14 @@ int fmm_batch_prepare(fmm_plan_t pl, int32_t nsys, const int64_t* sys_offsets,
                           pl->d_pq, pl->d_pcnt, order_budget_log10(pl), pl->d_ord,
                           fmm_plan_s::kOrdCols, pl->d_feat, gs, io);
     }
-    for (size_t g = 0; g < runs.size(); ++g) {
+    // the deepest trees, which hold most of the work, first
+    std::vector<FmmArgs> trees;
+    for (size_t g = runs.size(); g-- > 0;) {
       launch_rekey(skeys + runs[g].p0, runs[g].n, run_r0[g], runs[g].lt.L, kl, gs);
-      enqueue_tree(pl, runs[g], skeys, perm, nullptr, nullptr, nullptr, nullptr, gs, nullptr,
-                   spts, io);
+      trees.push_back(prepare_tree(pl, runs[g], skeys, perm, nullptr, nullptr, nullptr, nullptr,
+                                   gs, nullptr, spts, io));
     }
+    if (!trees.empty()) enqueue_trees(pl, trees, gs, nullptr);
   }
   hipGraph_t graph = nullptr;
   if (hipStreamEndCapture(gs, &graph) != hipSuccess || !graph) return FMM_ERR_DEVICE;

@@ -61,7 +61,7 @@ struct Mfma16x<double> {
 __device__ __forceinline__ void lds_copy16(const void* src, void* dst) {
   __builtin_amdgcn_global_load_lds(
       (const __attribute__((address_space(1))) void*)(uintptr_t)src,
-      (__attribute__((address_space(3))) void*)(uint32_t)(uintptr_t)dst, 16, 0, 0);
+      (__attribute__((address_space(3))) void*)(uintptr_t)(uint32_t)(uintptr_t)dst, 16, 0, 0);
 }
 // Waits until at most `newer` (0, 2 or 4) of this wave's vector memory accesses are
 // outstanding; they return in order, so all but the `newer` issued last have
