@@ -819,26 +819,39 @@ __global__ __launch_bounds__(256) void k_p2p2d_f32(FmmArgs a, int tiled,
 // only fall with k, so all particles of a level-k box agree on whether their
 // depth reaches k.
 // ---------------------------------------------------------------------------
-// Flags of level k, coarse to fine.  Bit 0 (open): k < L, the parent is open
-// (or k = kmin) and the 3 x 3 boxes around the box hold more than adapt_near
-// particles (a closed parent leaves no more than that around its children).
-// Bit 1 (k_adapt_near, once bit 0 of the level is complete): some box of the
+// Flags of levels kmin..L - 1, every level in one launch.  Bit 0 (open): the 3 x 3
+// boxes around the box hold more than adapt_near particles.  (Those around a
+// box lie within the children of those around its parent, so a box with a
+// closed ancestor is closed by its own count: no level waits for another, and
+// nine levels of a 2^21-particle tree take 2 launches and 56 us, not 18 and
+// 170.)
+// Bit 1 (k_adapt_near, once bit 0 of every level is complete): some box of the
 // 3 x 3 around it is open, i.e. its children are in the interaction list of an
 // open box's children and their moments are read.
-__global__ __launch_bounds__(256) void k_adapt_open(FmmArgs a, int k, uint8_t* open) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= ((int64_t)1 << (2 * k))) return;
-  uint8_t o = 0;
-  if (k == a.lt.kmin || (open[adapt_open_off(k - 1) + (b >> 2)] & 1))
-    o = around_count2(a.leaf_start, a.lt.L, k, (int)compact2((uint32_t)b),
-                      (int)compact2((uint32_t)b >> 1)) > a.adapt_near;
-  open[adapt_open_off(k) + b] = o;
+__device__ __forceinline__ int adapt_level(int kmin, int64_t t, int64_t& b) {
+  const int64_t e = adapt_open_off(kmin) + t;  // place in the flag array
+  int k = kmin;
+  while (adapt_open_off(k + 1) <= e) ++k;
+  b = e - adapt_open_off(k);
+  return k;
 }
 
-__global__ __launch_bounds__(256) void k_adapt_near(int k, uint8_t* open) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(256) void k_adapt_open(FmmArgs a, uint8_t* open) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= adapt_open_off(a.lt.L) - adapt_open_off(a.lt.kmin)) return;
+  int64_t b;
+  const int k = adapt_level(a.lt.kmin, t, b);
+  open[adapt_open_off(k) + b] =
+      around_count2(a.leaf_start, a.lt.L, k, (int)compact2((uint32_t)b),
+                    (int)compact2((uint32_t)b >> 1)) > a.adapt_near;
+}
+
+__global__ __launch_bounds__(256) void k_adapt_near(int kmin, int L, uint8_t* open) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= adapt_open_off(L) - adapt_open_off(kmin)) return;
+  int64_t b;
+  const int k = adapt_level(kmin, t, b);
   const int nb = 1 << k;
-  if (b >= (int64_t)nb * nb) return;
   const int bx = (int)compact2((uint32_t)b), by = (int)compact2((uint32_t)b >> 1);
   uint8_t* f = open + adapt_open_off(k);
   uint8_t any = 0;
@@ -861,11 +874,11 @@ __global__ __launch_bounds__(256) void k_adapt_depth(FmmArgs a, const uint8_t* o
 }
 
 void launch_adapt_depth(const FmmArgs& a, uint8_t* open, uint8_t* depth, hipStream_t st) {
-  for (int k = a.lt.kmin; k < a.lt.L; ++k) {
-    const int64_t nb = (int64_t)1 << (2 * k);
-    const dim3 grid((unsigned)((nb + 255) / 256));
-    hipLaunchKernelGGL(k_adapt_open, grid, dim3(256), 0, st, a, k, open);
-    hipLaunchKernelGGL(k_adapt_near, grid, dim3(256), 0, st, k, open);
+  const int64_t flags = adapt_open_off(a.lt.L) - adapt_open_off(a.lt.kmin);
+  if (flags > 0) {
+    const dim3 grid((unsigned)((flags + 255) / 256));
+    hipLaunchKernelGGL(k_adapt_open, grid, dim3(256), 0, st, a, open);
+    hipLaunchKernelGGL(k_adapt_near, grid, dim3(256), 0, st, a.lt.kmin, a.lt.L, open);
   }
   if (a.n > 0)
     hipLaunchKernelGGL(k_adapt_depth, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, st, a,
@@ -878,8 +891,11 @@ void launch_adapt_depth(const FmmArgs& a, uint8_t* open, uint8_t* depth, hipStre
 // formed from the leaf column and row the record carries (exact), as in the
 // tile kernel.  A wave whose targets share one level-d box reads the ranges
 // and records from wave-uniform addresses (scalar loads); any other wave takes
-// each lane's own box.
-__device__ __forceinline__ void shallow_sum(const FmmArgs& a, int L, int d, int bx, int by,
+// each lane's own box.  Bound by the latency of those loads: eight records are
+// loaded together (2^21 clustered particles, adapt_near 400: 606 -> 480 us).
+__device__ __forceinline__ void shallow_sum(const FmmArgs& a, const float4* __restrict__ pts,
+                                            const int32_t* __restrict__ leaf_start, int L, int d,
+                                            int bx, int by,
                                             int ltx, int lty, const float4& t, float sL,
                                             double& phi, double& ex, double& ey) {
   const int dl = L - d, nb = 1 << d;
@@ -888,12 +904,11 @@ __device__ __forceinline__ void shallow_sum(const FmmArgs& a, int L, int d, int 
     for (int nx = bx - 1; nx <= bx + 1; ++nx) {
       if (nx < 0 || nx >= nb) continue;
       const int64_t nk = (int64_t)(spread2(nx) | (spread2(ny) << 1));
-      const int32_t i1 = a.leaf_start[(nk + 1) << (2 * dl)];
-      for (int32_t c0 = a.leaf_start[nk << (2 * dl)]; c0 < i1; c0 += 32) {
+      const int32_t i1 = leaf_start[(nk + 1) << (2 * dl)];
+      for (int32_t c0 = leaf_start[nk << (2 * dl)]; c0 < i1; c0 += 32) {
         const int32_t c1 = c0 + 32 < i1 ? c0 + 32 : i1;
         float fp = 0.f, fx = 0.f, fy = 0.f;
-        for (int32_t i = c0; i < c1; ++i) {
-          const float4 sv = a.pts[i];
+        auto pair = [&](const float4& sv) {
           const uint32_t lb = __float_as_uint(sv.w);  // the source leaf's column | row << 16
           const float dx = (t.x - sv.x) + (float)(ltx - (int)(lb & 0xFFFFu)) * sL;
           const float dy = (t.y - sv.y) + (float)(lty - (int)(lb >> 16)) * sL;
@@ -902,7 +917,16 @@ __device__ __forceinline__ void shallow_sum(const FmmArgs& a, int L, int d, int 
           fp += sv.z * __builtin_amdgcn_logf(r2);
           fx -= w * dx;
           fy -= w * dy;
+        };
+        int32_t i = c0;
+        for (; i + 8 <= c1; i += 8) {  // eight loads issued together
+          float4 sb[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) sb[u] = pts[i + u];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) pair(sb[u]);
         }
+        for (; i < c1; ++i) pair(pts[i]);
         phi += (double)fp;
         ex += (double)fx;
         ey += (double)fy;
@@ -911,7 +935,8 @@ __device__ __forceinline__ void shallow_sum(const FmmArgs& a, int L, int d, int 
   }
 }
 
-__global__ __launch_bounds__(256) void k_p2p2d_f32_shallow(FmmArgs a) {
+__global__ __launch_bounds__(256) void k_p2p2d_f32_shallow(
+    FmmArgs a, const float4* __restrict__ pts, const int32_t* __restrict__ leaf_start) {
   const int64_t jt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t j = jt < a.n ? jt : a.n - 1;
   const int L = a.lt.L, d = a.depth[j];
@@ -928,9 +953,11 @@ __global__ __launch_bounds__(256) void k_p2p2d_f32_shallow(FmmArgs a) {
   const int d0 = __builtin_amdgcn_readlane(d, f);
   double phi = 0.0, ex = 0.0, ey = 0.0;
   if (__ballot(live && (bk != b0 || d != d0)) == 0) {
-    shallow_sum(a, L, d0, (int)compact2(b0), (int)compact2(b0 >> 1), ltx, lty, t, sL, phi, ex, ey);
+    shallow_sum(a, pts, leaf_start, L, d0, (int)compact2(b0), (int)compact2(b0 >> 1), ltx, lty, t,
+                sL, phi, ex, ey);
   } else if (live) {
-    shallow_sum(a, L, d, (int)compact2(bk), (int)compact2(bk >> 1), ltx, lty, t, sL, phi, ex, ey);
+    shallow_sum(a, pts, leaf_start, L, d, (int)compact2(bk), (int)compact2(bk >> 1), ltx, lty, t,
+                sL, phi, ex, ey);
   }
   if (!live) return;
   phi -= (double)t.z * (double)__builtin_amdgcn_logf(kP2pEps);  // the target's own term
@@ -951,7 +978,7 @@ void launch_p2p2d(const FmmArgs& a, bool leaf_local, hipStream_t st) {
     hipLaunchKernelGGL(k_p2p2d_f32, direct, dim3(256), 0, st, a, 0, a.pts, a.leaf_start, 0);
     if (a.lt.L > a.lt.kmin)
       hipLaunchKernelGGL(k_p2p2d_f32_shallow, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0,
-                         st, a);
+                         st, a, a.pts, a.leaf_start);
     return;
   }
   const int tiled = a.lt.L >= 2 && a.p2p_over ? 1 : 0;

@@ -621,7 +621,9 @@ struct TreeRun {
 // the near field, which needs only that.  enqueue_far: moments and contractions;
 // in the FP32 modes first the small FP64 chain of level 2 (moments, then the
 // contraction on the VALU, which leaves most of the chip to the near field),
-// then the main level range.  enqueue_local: the local evaluation, which adds
+// then the main level range (2^21 clustered particles with the adaptive depth:
+// 1.35 ms a step with the chain's contraction after the main moments, 1.26
+// before them).  enqueue_local: the local evaluation, which adds
 // near and far and scatters to input order.
 // io (batched graphs): the caller's buffers come from this device record,
 // not from pos / q / pot / field.
@@ -698,6 +700,23 @@ void enqueue_near(fmm_plan_s* pl, const FmmArgs& a, hipStream_t st) {
     launch_p2p3d(a, pl->f32, st);
 }
 
+// FP32 modes: level 2 in FP64, moments and contraction.
+void enqueue_level64(fmm_plan_s* pl, const FmmArgs& a64, hipStream_t st) {
+  if (pl->dim == 2 && pl->basis) {
+    launch_p2m2d_points(a64, true, true, st);
+    launch_m2l2d_points(a64, true, st);
+  } else if (pl->dim == 2) {
+    launch_p2m2d(a64, true, true, st);
+    launch_m2l2d(a64, true, st);
+  } else {
+    if (pl->basis && pl->p != 4)
+      launch_p2m3d_points(a64, true, true, st);
+    else
+      launch_p2m3d(a64, true, true, st);
+    launch_m2l3d(a64, true, st);
+  }
+}
+
 void enqueue_far(fmm_plan_s* pl, const FmmArgs& a, hipStream_t st, hipEvent_t* ev) {
   const LevelTable& lt = a.lt;
   FmmArgs a64 = a, a32 = a;
@@ -718,26 +737,15 @@ void enqueue_far(fmm_plan_s* pl, const FmmArgs& a, hipStream_t st, hipEvent_t* e
     if (ev && (pl->ev_mask >> 4 & 1)) (void)hipEventRecord(ev[4], st);
     return;
   }
+  if (lvl64) enqueue_level64(pl, a64, st);
   if (pl->dim == 2 && pl->basis) {
-    if (lvl64) launch_p2m2d_points(a64, true, true, st);
     launch_p2m2d_points(am, pl->f32, !pl->f32, st);
   } else if (pl->dim == 2) {
-    if (lvl64) launch_p2m2d(a64, true, true, st);
     launch_p2m2d(am, pl->f32, !pl->f32, st);
   } else if (pl->basis && pl->p != 4) {
-    if (lvl64) launch_p2m3d_points(a64, true, true, st);
     launch_p2m3d_points(am, pl->f32, !pl->f32, st);
   } else {
-    if (lvl64) launch_p2m3d(a64, true, true, st);
     launch_p2m3d(am, pl->f32, !pl->f32, st);
-  }
-  if (lvl64) {
-    if (pl->dim == 2 && pl->basis)
-      launch_m2l2d_points(a64, true, st);
-    else if (pl->dim == 2)
-      launch_m2l2d(a64, true, st);
-    else
-      launch_m2l3d(a64, true, st);
   }
   if (ev && (pl->ev_mask >> 2 & 1)) (void)hipEventRecord(ev[2], st);
   // the main M2L launch (all levels in FP64 mode, levels >= 3 in FP32 modes)
@@ -771,7 +779,7 @@ void enqueue_local(fmm_plan_s* pl, const FmmArgs& a, hipStream_t st, hipEvent_t*
 // overlaps everything else; the caller's stream runs their far fields, then,
 // joined with the near fields, the local evaluations.  (With the trees one after
 // the other, near and far joined in each, the chip ran dry at every join: 256
-// systems of four depths 3.72 -> BATCHMS ms.)
+// systems of four depths 3.65 -> 3.55 ms.)
 // (Measured slower, on a 1M-particle 2D FP32 evaluation at 0.34 ms: a third
 // stream for the level-2 chain (the extra overlap only adds contention with
 // the near field); forking after the moments, the near field beside the
