@@ -50,6 +50,7 @@ struct M2lTiles {
   int64_t off[kMaxLevels2D + 2];  // first tile of level k
   int64_t ntiles;
   int remap;  // deal tiles to the XCDs in contiguous ranges
+  int split;  // few tiles: a workgroup per parity class (m2l2d_split)
 };
 
 constexpr int kHalo = 14;  // 8 targets + 3 on each side (x); 8 MB + 6 rows (y)
@@ -91,7 +92,10 @@ struct HaloGeom {
 
 // FULL: every level of the launch runs at the layout order (pk = pb), so the
 // step and block counts are the compile-time KS, NB and no guard is emitted.
-template <typename T, int KS, int NB, int MB, bool FULL>
+//
+// SPLIT (MB = 1): a workgroup takes one parity class of its tile, its four waves
+// contiguous parts of the class's 27 offsets, added in order through LDS.
+template <typename T, int KS, int NB, int MB, bool FULL, bool SPLIT>
 __global__ __launch_bounds__(256) void k_m2l2d_mfma(FmmArgs a, M2lTiles tt, M2lLayout ly) {
   using G = HaloGeom<MB>;
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -99,7 +103,8 @@ __global__ __launch_bounds__(256) void k_m2l2d_mfma(FmmArgs a, M2lTiles tt, M2lL
   using acc_t = typename Mfma16<T>::acc_t;
   constexpr bool kF64 = sizeof(T) == 8;
 
-  const int64_t tile = tt.remap ? xcd_remap(blockIdx.x, tt.ntiles) : (int64_t)blockIdx.x;
+  const int64_t block = SPLIT ? blockIdx.x >> 2 : blockIdx.x;
+  const int64_t tile = tt.remap ? xcd_remap(block, tt.ntiles) : block;
   int k = tt.klo;
   while (k < tt.khi && tile >= tt.off[k + 1]) ++k;
   const int n = 1 << k;
@@ -171,7 +176,8 @@ __global__ __launch_bounds__(256) void k_m2l2d_mfma(FmmArgs a, M2lTiles tt, M2lL
   // the wave index is uniform: in a scalar register every offset slot and
   // operator address derived from it stays scalar
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int px = w & 1, py = w >> 1;
+  const int cls = SPLIT ? blockIdx.x & 3 : w;
+  const int px = cls & 1, py = cls >> 1;
   const int i = lane & 15, g = lane >> 4;
   const int ix = 2 * (i & 3) + px, iy = 2 * (i >> 2) + py;  // A-row target of this lane
   acc_t acc[MB][NB];
@@ -198,6 +204,13 @@ __global__ __launch_bounds__(256) void k_m2l2d_mfma(FmmArgs a, M2lTiles tt, M2lL
     const int nx0 = px ? 2 : 1, ny0 = py ? 2 : 1;
     for (int yy = 0; yy < 3; ++yy)
       for (int xx = 0; xx < 3; ++xx) todo &= ~(1ull << ((ny0 + yy) * 6 + nx0 + xx));
+  }
+  if constexpr (SPLIT) {  // the w-th quarter of them
+    const int c0 = 27 * w / 4, c1 = 27 * (w + 1) / 4;
+    for (int c = 0; c < c0; ++c) todo &= todo - 1;
+    uint64_t rest = todo;
+    for (int c = c0; c < c1; ++c) rest &= rest - 1;
+    todo ^= rest;
   }
 
   // Operator registers of one offset (the next offset's are loaded while the
@@ -287,6 +300,31 @@ __global__ __launch_bounds__(256) void k_m2l2d_mfma(FmmArgs a, M2lTiles tt, M2lL
   }
 #undef SFFMM_M2L_LOADW
 #undef SFFMM_M2L_STEP
+  if constexpr (SPLIT) {
+    constexpr int kVals = 4 * NB + 2;  // of a lane: accumulators, Re B_0, A_0 sum
+    __syncthreads();                   // every wave is done with the halo
+    if (w > 0) {
+      T* mine = halo + (w - 1) * kVals * 64 + lane;
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mine[(4 * nb + r) * 64] = acc[0][nb][r];
+      mine[4 * NB * 64] = b0p[0];
+      mine[(4 * NB + 1) * 64] = a0s[0];
+    }
+    __syncthreads();
+    if (w > 0) return;
+#pragma unroll
+    for (int o = 0; o < 3; ++o) {
+      const T* from = halo + o * kVals * 64 + lane;
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[0][nb][r] += from[(4 * nb + r) * 64];
+      b0p[0] += from[4 * NB * 64];
+      a0s[0] += from[(4 * NB + 1) * 64];
+    }
+  }
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
     T bp = b0p[mb], as = a0s[mb];
@@ -598,24 +636,24 @@ static size_t m2l2d_bf16_lds_kc(int kc, int mb) {
   return kc == 1 ? m2l2d_bf16_lds<1>(mb) : kc == 2 ? m2l2d_bf16_lds<2>(mb) : m2l2d_bf16_lds<3>(mb);
 }
 
-template <typename T, int KS, int NB, int MB, bool FULL>
+template <typename T, int KS, int NB, int MB, bool FULL, bool SPLIT>
 static void m2l_launch_f(const FmmArgs& a, const M2lTiles& tt, const M2lLayout& ly,
                          hipStream_t st) {
-  const size_t lds = m2l2d_lds(ly, MB, sizeof(T) == 8);
+  const size_t lds = m2l2d_lds(ly, MB, sizeof(T) == 8);  // SPLIT's 3 parts are smaller
   if (lds > 65536)
-    (void)hipFuncSetAttribute((const void*)k_m2l2d_mfma<T, KS, NB, MB, FULL>,
+    (void)hipFuncSetAttribute((const void*)k_m2l2d_mfma<T, KS, NB, MB, FULL, SPLIT>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL((k_m2l2d_mfma<T, KS, NB, MB, FULL>), dim3(tt.ntiles), dim3(256), lds, st, a,
-                     tt, ly);
+  hipLaunchKernelGGL((k_m2l2d_mfma<T, KS, NB, MB, FULL, SPLIT>),
+                     dim3(tt.ntiles * (SPLIT ? 4 : 1)), dim3(256), lds, st, a, tt, ly);
 }
 
-template <typename T, int KS, int NB, int MB>
+template <typename T, int KS, int NB, int MB, bool SPLIT = false>
 static void m2l_launch(const FmmArgs& a, const M2lTiles& tt, const M2lLayout& ly,
                        hipStream_t st) {
   if (a.ord_full)
-    m2l_launch_f<T, KS, NB, MB, true>(a, tt, ly, st);
+    m2l_launch_f<T, KS, NB, MB, true, SPLIT>(a, tt, ly, st);
   else
-    m2l_launch_f<T, KS, NB, MB, false>(a, tt, ly, st);
+    m2l_launch_f<T, KS, NB, MB, false, SPLIT>(a, tt, ly, st);
 }
 
 // Tile heights compiled per (precision, bucket): MB = 1 everywhere; 2, 3, 4 and
@@ -625,6 +663,12 @@ template <typename T, int KS, int NB>
 static void m2l_mb(const FmmArgs& a, const M2lTiles& tt, const M2lLayout& ly, hipStream_t st) {
   constexpr bool kF64 = sizeof(T) == 8;
   const int mb = a.m2l_mb;
+  if constexpr (kF64) {
+    if (tt.split) {
+      m2l_launch<T, KS, NB, 1, true>(a, tt, ly, st);
+      return;
+    }
+  }
   if (mb == 8 && !kF64 && KS <= 8) {
     m2l_launch<T, KS, NB, ((kF64 || KS > 8) ? 1 : 8)>(a, tt, ly, st);
   } else if (mb == 3 && (!kF64 || KS <= 8)) {
@@ -775,6 +819,24 @@ __global__ __launch_bounds__(256) void k_m2l2d_small(FmmArgs a, int k, M2lLayout
   }
 }
 
+constexpr int64_t kM2lSplitTiles = 128;
+// FP64 with at most 128 tiles: a workgroup per tile leaves half the CUs or more
+// without work and each wave 27 offsets in series; with one per parity class
+// and a quarter of the offsets per wave the chain is a quarter (levels 2-5, 22
+// tiles, order 16: 28 -> 14 us; 2-4, 6 tiles, order 12: 23 -> 11).  From there on
+// the three further stagings of each halo cost more than the chip was idle
+// (whole evaluations of order 16: level 6, 86 tiles,
+// 106 -> 100 us; level 7, 342 tiles, 177 unsplit, 180 split).  The rule counts tiles of 8 x 8, so every tile height a caller
+// sets gives the same sums.
+static bool m2l2d_split(const FmmArgs& a, bool fp64) {
+  int64_t t = 0;
+  for (int k = a.klo; k <= a.khi; ++k) {
+    const int64_t n = (((int64_t)1 << k) + 7) / 8;
+    t += n * n * a.lt.nsys;
+  }
+  return fp64 && t <= kM2lSplitTiles;
+}
+
 void launch_m2l2d(const FmmArgs& a, bool fp64, hipStream_t st, bool bf16) {
   if (a.khi < a.klo) return;
   if (fp64 && a.khi <= 2) {
@@ -787,8 +849,11 @@ void launch_m2l2d(const FmmArgs& a, bool fp64, hipStream_t st, bool bf16) {
   const M2lLayout ly = m2l2d_layout(order_bucket(a.p));
   FmmArgs b = a;
   if (!m2l2d_variant_ok(b.m2l_mb, fp64, ly.p, bf16 && !fp64)) b.m2l_mb = 1;
+  const bool split = m2l2d_split(a, fp64);
+  if (split) b.m2l_mb = 1;
   const int mb = b.m2l_mb;
   M2lTiles tt{};
+  tt.split = split;
   tt.klo = a.klo;
   tt.khi = a.khi;
   tt.remap = a.m2l_remap;
