@@ -77,44 +77,50 @@ struct Carve {
   }
 };
 
-__device__ double binom_d(int n, int k) {
-  if (k < 0 || k > n) return 0.0;
-  double c = 1.0;
-  for (int i = 1; i <= k; ++i) c *= double(n - k + i) / double(i);
-  return c;
-}
+// The powers and binomials of one offset slot's operator entries.
+struct OpTables {
+  double re[2 * kNoAllocMaxOrder + 1], im[2 * kNoAllocMaxOrder + 1];   // u^-e
+  double binom[kNoAllocMaxOrder + 1][kNoAllocMaxOrder];                // [l][m - 1]: C(l + m - 1, m - 1)
+};
 
-// u^-e for the Gaussian integer u = dx + i dy, by repeated multiplication with
-// 1/u (the product order the host builder uses).
-__device__ void uinv_pow(double dx, double dy, int e, double& re, double& im) {
-  const double d = dx * dx + dy * dy;
-  const double ir = dx / d, ii = -dy / d;
-  re = 1.0;
-  im = 0.0;
-  for (int k = 0; k < e; ++k) {
-    const double r = re * ir - im * ii;
-    im = re * ii + im * ir;
-    re = r;
+// u^-e for the Gaussian integer u = dx + i dy by repeated multiplication with
+// 1/u, C(l + m - 1, m - 1) by one factor a step in m (the product orders the
+// host builder uses): one thread the powers, one thread each row l.
+__device__ void build_tables(int p, int dx, int dy, OpTables& t) {
+  if (threadIdx.x == 0) {
+    const double x = dx, y = dy, d = x * x + y * y;
+    const double ir = x / d, ii = -y / d;
+    double re = 1.0, im = 0.0;
+    for (int e = 0; e <= 2 * p; ++e) {
+      t.re[e] = re;
+      t.im[e] = im;
+      const double r = re * ir - im * ii;
+      im = re * ii + im * ir;
+      re = r;
+    }
+  }
+  const int l = (int)threadIdx.x - 63;
+  if (l >= 1 && l <= p) {
+    double c = 1.0;
+    for (int m = 1; m <= p; ++m) {
+      if (m > 1) c *= double(l + m - 1) / double(m - 1);
+      t.binom[l][m - 1] = c;
+    }
   }
 }
 
-// Value `idx` of offset slot `slot` of the FP64 operator pack of order p in
-// layout ly (the multipole-to-local lemma in box-side-scaled variables, the
-// same entries as the host builder: Wb, c0, r0, t00; zero for adjacent slots
-// and padding).
-__device__ double pack_value(const M2lLayout& ly, int p, int slot, int idx) {
-  const int dx = slot % 7 - 3, dy = slot / 7 - 3;
-  if (abs(dx) <= 1 && abs(dy) <= 1) return 0.0;
+// Value `idx` of the FP64 operator pack of offset (dx, dy), order p, in layout
+// ly (the multipole-to-local lemma in box-side-scaled variables, the same
+// entries as the host builder: Wb, c0, r0, t00; zero for padding).
+__device__ double pack_value(const M2lLayout& ly, int p, int dx, int dy, const OpTables& t,
+                             int idx) {
   const int nk = ly.npad * ly.kpad;
-  double re, im;
   if (idx < nk) {
     const int j = idx / ly.kpad, k = idx % ly.kpad;
     const int l = j / 2 + 1, m = k / 2 + 1;
     if (l > p || m > p) return 0.0;
-    uinv_pow(dx, dy, l + m, re, im);
-    const double c = (m & 1 ? -1.0 : 1.0) * binom_d(l + m - 1, m - 1);
-    re *= c;
-    im *= c;
+    const double c = (m & 1 ? -1.0 : 1.0) * t.binom[l][m - 1];
+    const double re = t.re[l + m] * c, im = t.im[l + m] * c;
     const int a = j & 1, b = k & 1;
     return a == b ? re : (a == 0 ? -im : im);
   }
@@ -122,36 +128,61 @@ __device__ double pack_value(const M2lLayout& ly, int p, int slot, int idx) {
   if (idx < ly.npad) {  // c0: -1 / (l u^l)
     const int l = idx / 2 + 1;
     if (l > p) return 0.0;
-    uinv_pow(dx, dy, l, re, im);
-    return -(idx & 1 ? im : re) / double(l);
+    return -(idx & 1 ? t.im[l] : t.re[l]) / double(l);
   }
   idx -= ly.npad;
   if (idx < ly.kpad) {  // r0: Re((-1)^m u^-m A_m)
     const int m = idx / 2 + 1;
     if (m > p) return 0.0;
-    uinv_pow(dx, dy, m, re, im);
     const double s = m & 1 ? -1.0 : 1.0;
-    return idx & 1 ? -s * im : s * re;
+    return idx & 1 ? -s * t.im[m] : s * t.re[m];
   }
   idx -= ly.kpad;
   if (idx == 0) return 0.5 * log(double(dx * dx + dy * dy));  // Re log(-u)
   return 0.0;
 }
 
-// One workgroup per offset slot: the FP64 pack and its FP32 rounding, then the
-// lane-major FP64 / FP32 packs of the matrix-core kernel (the same mapping as
-// the host builder).
-__global__ __launch_bounds__(256) void k_build_ops2d(M2lLayout ly, int p, double* op64,
-                                                     float* op32, double* opl64, float* opl32) {
-  const int slot = blockIdx.x;
-  for (int i = threadIdx.x; i < ly.stride; i += blockDim.x) {
-    const double v = pack_value(ly, p, slot, i);
+// Everything a call starts from, in one launch.  Workgroups 0..48: the operators
+// of one offset slot, the FP64 pack and its FP32 rounding, then the lane-major
+// FP64 / FP32 packs of the matrix-core kernel (the same mapping as the host
+// builder; zero for adjacent slots).  The others: status words, orders and the
+// box vectors' zeros.  Bound by latency: an entry reads its power and binomial
+// from tables instead of multiplying them up (up to 32 products and 15
+// divisions each), and is formed once for the four packs (with the fills, order
+// 16: 26 -> 5 us).
+constexpr int kPrepThreads = 512;
+constexpr int kPackMax = 48 * 40 + 48 + 40 + 8;  // ly.stride at the largest order
+
+__global__ __launch_bounds__(kPrepThreads) void k_prepare2d(M2lLayout ly, int p, double* op64,
+                                                            float* op32, double* opl64,
+                                                            float* opl32, int32_t* flag,
+                                                            int32_t* ord, int4* zero,
+                                                            int64_t nzero) {
+  if (blockIdx.x >= 49) {
+    const int64_t t = (int64_t)(blockIdx.x - 49) * kPrepThreads + threadIdx.x;
+    if (t < nzero) zero[t] = int4{0, 0, 0, 0};
+    if (blockIdx.x == 49 && threadIdx.x < 16) {
+      ord[threadIdx.x] = p;
+      if (threadIdx.x < 4) flag[threadIdx.x] = 0;
+    }
+    return;
+  }
+  __shared__ OpTables tab;
+  __shared__ double pack[kPackMax];
+  const int slot = blockIdx.x, dx = slot % 7 - 3, dy = slot / 7 - 3;
+  const bool far = abs(dx) > 1 || abs(dy) > 1;
+  if (far) build_tables(p, dx, dy, tab);
+  __syncthreads();
+  for (int i = threadIdx.x; i < ly.stride; i += kPrepThreads) {
+    const double v = far ? pack_value(ly, p, dx, dy, tab, i) : 0.0;
+    pack[i] = v;
     op64[(size_t)slot * ly.stride + i] = v;
     op32[(size_t)slot * ly.stride + i] = (float)v;
   }
+  __syncthreads();
   const int ks = ly.kpad / 4, nbk = ly.npad / 16;
   const int nlane = nbk * (ks + 1) * 64, nr = ks * 64;
-  for (int i = threadIdx.x; i < ly.lstride; i += blockDim.x) {
+  for (int i = threadIdx.x; i < ly.lstride; i += kPrepThreads) {
     int src = -1;
     if (i < nlane) {
       const int l = i & 63, q = i >> 6, st = q % (ks + 1), nb = q / (ks + 1);
@@ -166,7 +197,7 @@ __global__ __launch_bounds__(256) void k_build_ops2d(M2lLayout ly, int p, double
     } else if (i == nlane + nr) {
       src = ly.npad * ly.kpad + ly.npad + ly.kpad;  // t00
     }
-    const double v = src >= 0 ? pack_value(ly, p, slot, src) : 0.0;
+    const double v = src >= 0 ? pack[src] : 0.0;
     opl64[(size_t)slot * ly.lstride + i] = v;
     opl32[(size_t)slot * ly.lstride + i] = (float)v;
   }
@@ -256,15 +287,14 @@ extern "C" int fmm_eval_noalloc(const fmm_options* opt, int64_t n, const double*
   if (c.over) return FMM_ERR_SCRATCH;
 
   // status words, orders and the box vectors (whose padding values no kernel
-  // writes, and which an earlier call may have left holding other data) start
-  // fresh in every call: fill kernels, no memset
-  launch_fill_i32(flag, 0, 4, st);
-  launch_fill_i32(ord, p, 16, st);
-  launch_fill_i32(reinterpret_cast<int32_t*>(mom64), 0, nbox64 * cs * 2, st);
-  launch_fill_i32(reinterpret_cast<int32_t*>(loc64), 0, nbox64 * cs * 2, st);
-  launch_fill_i32(reinterpret_cast<int32_t*>(mom32), 0, nbox32 * cs, st);
-  launch_fill_i32(reinterpret_cast<int32_t*>(loc32), 0, nbox32 * cs, st);
-  hipLaunchKernelGGL(k_build_ops2d, dim3(49), dim3(256), 0, st, ly, p, op64, op32, opl64, opl32);
+  // writes, and which an earlier call may have left holding other data; they lie
+  // one after the other from mom64 to part64) start fresh in every call, with
+  // the operators: a kernel, no memset
+  const int64_t nzero = (reinterpret_cast<unsigned char*>(part64) -
+                         reinterpret_cast<unsigned char*>(mom64)) / (int64_t)sizeof(int4);
+  hipLaunchKernelGGL(k_prepare2d, dim3((unsigned)(49 + (nzero + kPrepThreads - 1) / kPrepThreads)),
+                     dim3(kPrepThreads), 0, st, ly, p, op64, op32, opl64, opl32, flag, ord,
+                     reinterpret_cast<int4*>(mom64), nzero);
   const int32_t tag = 1;
   int which = 0;
   if (one) {
