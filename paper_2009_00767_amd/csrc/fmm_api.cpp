@@ -790,8 +790,23 @@ void enqueue_local(fmm_plan_s* pl, const FmmArgs& a, hipStream_t st, hipEvent_t*
 // then starts beside the near field's last workgroups); both together, the
 // short moments chain forked and joined before the main contraction, came
 // out even on that workload and slower on the batched and clustered ones.)
+// Small FP64 2D trees (near_moments2d_ok) run on the caller's stream alone, the
+// near field and the moments as one launch: the fork, the join and a launch
+// more cost the host 60 us a call, longer than the chip works for 4096 particles
+// (61 -> 45 us; 1000: 61 -> 31; 20,000: 84 -> 67; 40,000 and 65,536: even, at
+// 86 and 100).  Timed evaluations need the phases apart; the sums are the same.
 void enqueue_trees(fmm_plan_s* pl, const std::vector<FmmArgs>& trees, hipStream_t st,
                    hipEvent_t* ev) {
+  if (trees.size() == 1 && !ev && pl->dim == 2 && !pl->f32 && !pl->basis &&
+      near_moments2d_ok(trees[0])) {
+    FmmArgs a = trees[0];
+    a.klo = a.lt.kmin;
+    a.khi = a.lt.L;
+    launch_near_moments2d(a, st);
+    launch_m2l2d(a, true, st);
+    enqueue_local(pl, a, st, nullptr);
+    return;
+  }
   (void)hipEventRecord(pl->fork_ev, st);
   (void)hipStreamWaitEvent(pl->near, pl->fork_ev, 0);
   if (ev && (pl->ev_mask >> 6 & 1)) (void)hipEventRecord(ev[6], pl->near);

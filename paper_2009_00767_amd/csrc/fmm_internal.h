@@ -201,6 +201,10 @@ struct FmmArgs {
 __host__ __device__ constexpr int64_t adapt_open_off(int k) { return (((int64_t)1 << (2 * k)) - 1) / 3; }
 // P2M for levels a.klo..a.khi; leaf_local selects the FP32 leaf-local inputs,
 // fp64 the storage of that level range.
+// FP64, trees that near_moments2d_ok names (few particles, at least one level):
+// near field and moments (levels a.klo..a.khi) in one launch.
+bool near_moments2d_ok(const FmmArgs& a);
+void launch_near_moments2d(const FmmArgs& a, hipStream_t st);
 void launch_p2m2d(const FmmArgs& a, bool leaf_local, bool fp64, hipStream_t st);
 // partial rows for nsys stacked systems totalling at most maxn particles
 size_t p2m2d_partial_entries(const LevelTable& lt, int klo, int khi, int64_t maxn, int cs);

@@ -353,18 +353,20 @@ extern "C" int fmm_eval_noalloc(const fmm_options* opt, int64_t n, const double*
   a64.khi = hi64;
   a32.klo = std::max(lt.split, lt.kmin);
   a32.khi = lt.L;
-  // the same kernels as fmm_eval, in order on one stream
-  launch_p2p2d(a, f32, st);
+  // the kernels of fmm_eval, in order on one stream
   if (f32) {
+    launch_p2p2d(a, f32, st);
     if (a64.khi >= a64.klo) {
       launch_p2m2d(a64, true, true, st);
       launch_m2l2d(a64, true, st);
     }
     launch_p2m2d(a32, true, false, st);
     launch_m2l2d(a32, false, st);
-  } else {
-    launch_p2m2d(a64, false, true, st);
+  } else if (a64.khi >= a64.klo) {
+    launch_near_moments2d(a64, st);
     launch_m2l2d(a64, true, st);
+  } else {
+    launch_p2p2d(a, f32, st);
   }
   launch_l2p2d(a, f32, st);
   if (hipGetLastError() != hipSuccess) return FMM_ERR_DEVICE;

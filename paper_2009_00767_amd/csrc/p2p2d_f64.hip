@@ -13,10 +13,14 @@
 // particles at level 4 (sixteen lanes a target instead of one: 64 waves had
 // left the chip idle) 63 -> 12 us.
 #include "near2d.h"
+#include "p2m2d.h"
 
 namespace sffmm {
 
 namespace {
+
+// Targets up to which sixteen, and four, lanes share one (launch_p2p2d_f64).
+constexpr int64_t kLanes16 = 1 << 14, kLanes4 = 1 << 16;
 
 // log2 of a normal r2 > 0 is the exponent plus log2 of the mantissa m in [1/2,
 // 1), which is T_i + log2(1 + u) with u = m c_i - 1, c_i the reciprocal of the
@@ -170,14 +174,13 @@ __device__ __forceinline__ void range2_f64(const double* __restrict__ xs,
 // targets whose leaf lies at level d are taken.
 // over: only the targets of tiles the tile kernel left.
 template <int P>
-__global__ __launch_bounds__(256) void k_p2p2d_f64(FmmArgs a, int over,
-                                                   const double* __restrict__ xs,
-                                                   const double* __restrict__ ys,
-                                                   const double* __restrict__ qs,
-                                                   const int32_t* __restrict__ leaf_start,
-                                                   int lsh) {
-  __shared__ double2 tab[kLogTable];
-  const int64_t t = xcd_chunk_remap(blockIdx.x) * 256 + threadIdx.x;
+__device__ __forceinline__ void near_direct(const FmmArgs& a, int over,
+                                            const double* __restrict__ xs,
+                                            const double* __restrict__ ys,
+                                            const double* __restrict__ qs,
+                                            const int32_t* __restrict__ leaf_start, int lsh,
+                                            int64_t block, double2* tab) {
+  const int64_t t = xcd_chunk_remap(block) * 256 + threadIdx.x;
   const int64_t j = t / P;
   const LevelTable& lt = a.lt;
   bool mine = j < a.n && (!a.depth || a.depth[j] == lt.L);
@@ -225,6 +228,36 @@ __global__ __launch_bounds__(256) void k_p2p2d_f64(FmmArgs a, int over,
     if (t % P != 0) return;
   }
   store_near(a, j, s);
+}
+
+template <int P>
+__global__ __launch_bounds__(256) void k_p2p2d_f64(FmmArgs a, int over,
+                                                   const double* __restrict__ xs,
+                                                   const double* __restrict__ ys,
+                                                   const double* __restrict__ qs,
+                                                   const int32_t* __restrict__ leaf_start,
+                                                   int lsh) {
+  __shared__ double2 tab[kLogTable];
+  near_direct<P>(a, over, xs, ys, qs, leaf_start, lsh, blockIdx.x, tab);
+}
+
+// Few particles: the near field and the moments of every level, which both
+// need only the sort, as two kinds of workgroups of one launch: the moments'
+// few workgroups first, rounded up to whole rounds of the 8 XCDs.  Both are
+// bound by latency and leave most of the chip idle alone (20,011 particles,
+// order 16, 5 levels: 23 and 12 us one after the other; a call on one stream 85
+// -> 73 us).
+template <int P, int PB, bool FULL>
+__global__ __launch_bounds__(256) void k_near_moments2d(FmmArgs a, P2mPlan pl, int moments,
+                                                        const double* __restrict__ xs,
+                                                        const double* __restrict__ ys,
+                                                        const double* __restrict__ qs,
+                                                        const int32_t* __restrict__ leaf_start) {
+  __shared__ double2 tab[kLogTable];
+  if ((int)blockIdx.x < moments)
+    p2m_thread<double, PB, false, FULL>(a, pl, (int64_t)blockIdx.x * 256 + threadIdx.x);
+  else
+    near_direct<P>(a, 0, xs, ys, qs, leaf_start, 0, blockIdx.x - moments, tab);
 }
 
 // Tile form: a workgroup stages the sources of a 4 x 4-leaf tile's 6 x 6-leaf
@@ -307,7 +340,46 @@ void direct_f64(const FmmArgs& a, int over, int lsh, hipStream_t st) {
                      a.xs, a.ys, a.qs, a.leaf_start, lsh);
 }
 
+// Tiles from 1024 of them on (four workgroups a CU).  Below that the chip
+// wants more threads than targets: sixteen lanes a target up to 2^14 targets
+// and four up to 2^16 give it at least one wave a SIMD (4096 targets: 63 us
+// with one lane, 12 with sixteen; 20,011: 76 and 18).
+int64_t near_tiles(const FmmArgs& a) {  // 0: the direct form
+  const int64_t tiles = a.lt.L >= 2 && a.p2p_over ? (int64_t)a.lt.nsys << (2 * (a.lt.L - 2)) : 0;
+  return tiles >= 1024 ? tiles : 0;
+}
+
+template <int P, int PB>
+void near_moments(const FmmArgs& a, hipStream_t st) {
+  const P2mPlan pl = make_p2m_plan(2, a.klo, a.khi, a.n, a.lt.nsys, p2m_lane_particles(true, a.n));
+  const int moments = (int)((pl.thr_off[a.khi + 1] + 256 * 8 - 1) / (256 * 8) * 8);
+  const dim3 grid(chunked_grid((a.n * P + 255) / 256).x + moments);
+  if (a.ord_full)
+    hipLaunchKernelGGL((k_near_moments2d<P, PB, true>), grid, dim3(256), 0, st, a, pl, moments,
+                       a.xs, a.ys, a.qs, a.leaf_start);
+  else
+    hipLaunchKernelGGL((k_near_moments2d<P, PB, false>), grid, dim3(256), 0, st, a, pl, moments,
+                       a.xs, a.ys, a.qs, a.leaf_start);
+  launch_p2m2d_slices(a, pl, PB, true, st);
+}
+
+template <int PB>
+void near_moments_pb(const FmmArgs& a, hipStream_t st) {
+  if (a.n <= kLanes16)
+    near_moments<16, PB>(a, st);
+  else
+    near_moments<4, PB>(a, st);
+}
+
 }  // namespace
+
+bool near_moments2d_ok(const FmmArgs& a) {
+  return !a.depth && a.n > 0 && a.n <= kLanes4 && a.lt.L >= a.lt.kmin && !near_tiles(a);
+}
+
+void launch_near_moments2d(const FmmArgs& a, hipStream_t st) {
+  SFFMM_PB_DISPATCH(near_moments_pb, a.p, a, st);
+}
 
 void launch_p2p2d_f64(const FmmArgs& a, hipStream_t st) {
   if (a.n <= 0) return;
@@ -321,19 +393,14 @@ void launch_p2p2d_f64(const FmmArgs& a, hipStream_t st) {
     }
     return;
   }
-  // Tiles from 1024 of them on (four workgroups a CU).  Below that the chip
-  // wants more threads than targets: sixteen lanes a target up to 2^14 targets
-  // and four up to 2^16 give it at least one wave a SIMD (4096 targets: 63 us
-  // with one lane, 12 with sixteen; 20,011: 76 and 18).
-  const int64_t tiles = a.lt.L >= 2 && a.p2p_over ? (int64_t)a.lt.nsys << (2 * (a.lt.L - 2)) : 0;
-  if (tiles >= 1024) {
+  if (const int64_t tiles = near_tiles(a)) {
     const int cap = p2p2d_tile_cap(a.lt, a.n, kTile64Cap);
     hipLaunchKernelGGL(k_p2p2d_f64_tile, chunked_grid(tiles), dim3(256),
                        (size_t)cap * 3 * sizeof(double), st, a, cap);
     direct_f64<1>(a, 1, 0, st);
-  } else if (a.n * 16 <= (1 << 18)) {
+  } else if (a.n <= kLanes16) {
     direct_f64<16>(a, 0, 0, st);
-  } else if (a.n * 4 <= (1 << 18)) {
+  } else if (a.n <= kLanes4) {
     direct_f64<4>(a, 0, 0, st);
   } else {
     direct_f64<1>(a, 0, 0, st);
