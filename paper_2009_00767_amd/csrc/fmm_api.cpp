@@ -774,12 +774,12 @@ void enqueue_local(fmm_plan_s* pl, const FmmArgs& a, hipStream_t st, hipEvent_t*
   if (ev && (pl->ev_mask >> 5 & 1)) (void)hipEventRecord(ev[5], st);
 }
 
-// Everything after the sort for one or several trees.  Two streams: the
-// near-field stream runs every tree's near field, which needs only the sort and
-// overlaps everything else; the caller's stream runs their far fields, then,
-// joined with the near fields, the local evaluations.  (With the trees one after
-// the other, near and far joined in each, the chip ran dry at every join: 256
-// systems of four depths 3.65 -> 3.55 ms.)
+// Everything after the sort for one tree.  Two streams: the near-field stream
+// runs the near field, which needs only the sort; the caller's stream runs the
+// far field, then, joined with the near field, the local evaluation.  Batched
+// trees go through here one after the other: every tree's near field beside
+// every tree's far field, joined once, gave 3.66 -> 3.51 ms on 256 systems but
+// 6.15 -> 6.6 on 512, and joined tree by tree without the fork 5.5 and 8.4.
 // (Measured slower, on a 1M-particle 2D FP32 evaluation at 0.34 ms: a third
 // stream for the level-2 chain (the extra overlap only adds contention with
 // the near field); forking after the moments, the near field beside the
@@ -795,27 +795,25 @@ void enqueue_local(fmm_plan_s* pl, const FmmArgs& a, hipStream_t st, hipEvent_t*
 // more cost the host 60 us a call, longer than the chip works for 4096 particles
 // (61 -> 45 us; 1000: 61 -> 31; 20,000: 84 -> 67; 40,000 and 65,536: even, at
 // 86 and 100).  Timed evaluations need the phases apart; the sums are the same.
-void enqueue_trees(fmm_plan_s* pl, const std::vector<FmmArgs>& trees, hipStream_t st,
-                   hipEvent_t* ev) {
-  if (trees.size() == 1 && !ev && pl->dim == 2 && !pl->f32 && !pl->basis &&
-      near_moments2d_ok(trees[0])) {
-    FmmArgs a = trees[0];
-    a.klo = a.lt.kmin;
-    a.khi = a.lt.L;
-    launch_near_moments2d(a, st);
-    launch_m2l2d(a, true, st);
+void enqueue_tree(fmm_plan_s* pl, const FmmArgs& a, hipStream_t st, hipEvent_t* ev) {
+  if (!ev && pl->dim == 2 && !pl->f32 && !pl->basis && near_moments2d_ok(a)) {
+    FmmArgs am = a;
+    am.klo = a.lt.kmin;
+    am.khi = a.lt.L;
+    launch_near_moments2d(am, st);
+    launch_m2l2d(am, true, st);
     enqueue_local(pl, a, st, nullptr);
     return;
   }
   (void)hipEventRecord(pl->fork_ev, st);
   (void)hipStreamWaitEvent(pl->near, pl->fork_ev, 0);
   if (ev && (pl->ev_mask >> 6 & 1)) (void)hipEventRecord(ev[6], pl->near);
-  for (const FmmArgs& a : trees) enqueue_near(pl, a, pl->near);
+  enqueue_near(pl, a, pl->near);
   if (ev && (pl->ev_mask >> 7 & 1)) (void)hipEventRecord(ev[7], pl->near);
   (void)hipEventRecord(pl->near_ev, pl->near);
-  for (const FmmArgs& a : trees) enqueue_far(pl, a, st, ev);
+  enqueue_far(pl, a, st, ev);
   (void)hipStreamWaitEvent(st, pl->near_ev, 0);
-  for (const FmmArgs& a : trees) enqueue_local(pl, a, st, ev);
+  enqueue_local(pl, a, st, ev);
 }
 
 // ----- M2L autotuner (2D) -----
@@ -1056,7 +1054,7 @@ int fmm_eval(fmm_plan_t pl, int64_t n, const double* pos, const double* q, doubl
   t.lt = pl->lt;
   t.n = n;
   t.sorted = one || two_digit;
-  enqueue_trees(pl, {prepare_tree(pl, t, skeys, perm, pos, q, pot, field, st, ev, spts)}, st, ev);
+  enqueue_tree(pl, prepare_tree(pl, t, skeys, perm, pos, q, pot, field, st, ev, spts), st, ev);
   if (timing) {
     pl->ring_batched[pl->ring_next] = false;
     ring_advance(pl);
@@ -1234,14 +1232,11 @@ int fmm_batch_prepare(fmm_plan_t pl, int32_t nsys, const int64_t* sys_offsets,
                           pl->d_pq, pl->d_pcnt, order_budget_log10(pl), pl->d_ord,
                           fmm_plan_s::kOrdCols, pl->d_feat, gs, io);
     }
-    // the deepest trees, which hold most of the work, first
-    std::vector<FmmArgs> trees;
-    for (size_t g = runs.size(); g-- > 0;) {
+    for (size_t g = 0; g < runs.size(); ++g) {
       launch_rekey(skeys + runs[g].p0, runs[g].n, run_r0[g], runs[g].lt.L, kl, gs);
-      trees.push_back(prepare_tree(pl, runs[g], skeys, perm, nullptr, nullptr, nullptr, nullptr,
-                                   gs, nullptr, spts, io));
+      enqueue_tree(pl, prepare_tree(pl, runs[g], skeys, perm, nullptr, nullptr, nullptr, nullptr,
+                                    gs, nullptr, spts, io), gs, nullptr);
     }
-    if (!trees.empty()) enqueue_trees(pl, trees, gs, nullptr);
   }
   hipGraph_t graph = nullptr;
   if (hipStreamEndCapture(gs, &graph) != hipSuccess || !graph) return FMM_ERR_DEVICE;
