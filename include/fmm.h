@@ -325,8 +325,8 @@ int fmm_mlp_forward(const float* w, const float* x, int64_t m, float* y, void* s
 /* Mean squared error over all outputs, loss = sum (y - t)^2 / (21 m), and its
  * gradient with respect to the parameters (backpropagation).  Device arrays:
  * w, grad [FMM_MLP_NPARAM], x [m][3], t [m][21], loss [1].  Deterministic (the
- * per-workgroup partial gradients are summed in a fixed order in FP64).
- * Synchronises (calls that overlap in time on several threads allocate and
+ * gradients of every 16 samples, formed in FP32, are summed in a fixed order in
+ * FP64).  Synchronises (calls that overlap in time on several threads allocate and
  * free their partial-sum scratch, all but one). */
 int fmm_mlp_loss_grad(const float* w, const float* x, const float* t, int64_t m, float* grad,
                       float* loss, void* stream);

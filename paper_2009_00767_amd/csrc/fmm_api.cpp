@@ -1355,11 +1355,11 @@ namespace {
 std::mutex g_mlp_mu;  // the order network's partial-sum array of every device
 
 struct MlpScratch {
-  float* part = nullptr;
+  double* part = nullptr;
   double* part_loss = nullptr;
   int alloc(int64_t m) {
     const size_t nb = (size_t)std::max<int64_t>(mlp_grad_blocks(m), 1);
-    if (hipMalloc(&part, sizeof(float) * nb * FMM_MLP_NPARAM) != hipSuccess ||
+    if (hipMalloc(&part, sizeof(double) * nb * FMM_MLP_NPARAM) != hipSuccess ||
         hipMalloc(&part_loss, sizeof(double) * nb) != hipSuccess) {
       (void)hipGetLastError();
       return FMM_ERR_NOMEM;

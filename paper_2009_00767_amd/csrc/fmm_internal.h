@@ -282,7 +282,7 @@ int64_t mlp_grad_blocks(int64_t m);
 void launch_mlp_forward(const float* w, const float* x, int64_t m, float* y, hipStream_t st);
 // part: [mlp_grad_blocks(m)][FMM_MLP_NPARAM], part_loss the same count; part NULL:
 // the device's own array of that size, which serves one gradient at a time
-void launch_mlp_grad(const float* w, const float* x, const float* t, int64_t m, float* part,
+void launch_mlp_grad(const float* w, const float* x, const float* t, int64_t m, double* part,
                      double* part_loss, float* grad, float* loss, hipStream_t st);
 void launch_mlp_adam(float* w, const float* g, float* m1, float* m2, int step, float lr,
                      hipStream_t st);
