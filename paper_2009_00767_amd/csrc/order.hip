@@ -136,8 +136,10 @@ __device__ __forceinline__ mlpx4 mlp_product(mlpx4 c, FA&& a, FB&& b) {
   return c;
 }
 
-// Hidden layers of the tile's samples s0.. (zeros past m) into h1 and h2, then
-// the outputs: result rows of output block `wave` (waves 0 and 1 only).
+// Hidden layers of the tile's samples s0.. into h1 and h2, then the outputs:
+// result rows of output block `wave` (waves 0 and 1 only).  Past m the first
+// hidden layer is zero, so that no padding sample overflows where the samples do
+// not (its zero output error times infinity would reach the gradient).
 // Ends with the tile's h1 and h2 visible to the workgroup.
 __device__ __forceinline__ mlpx4 tile_forward(const float* __restrict__ x, int64_t m, int64_t s0,
                                               MlpTile& s) {
@@ -152,7 +154,7 @@ __device__ __forceinline__ mlpx4 tile_forward(const float* __restrict__ x, int64
     const int i = 4 * u + wave;
     const float z = s.b1[lane] + s.w1[lane * 3] * s.x[i][0] + s.w1[lane * 3 + 1] * s.x[i][1] +
                     s.w1[lane * 3 + 2] * s.x[i][2];
-    s.h1[i * kStride + lane] = z > 0.f ? z : 0.f;
+    s.h1[i * kStride + lane] = z > 0.f && s0 + i < m ? z : 0.f;
   }
   __syncthreads();
   {
