@@ -22,16 +22,26 @@ namespace {
 // Targets up to which sixteen, and four, lanes share one (launch_p2p2d_f64).
 constexpr int64_t kLanes16 = 1 << 14, kLanes4 = 1 << 16;
 
-// log2 of a normal r2 > 0 is the exponent plus log2 of the mantissa m in [1/2,
-// 1), which is T_i + log2(1 + u) with u = m c_i - 1, c_i the reciprocal of the
-// middle of m's interval of width 2^-8 and T_i = -log2 c_i.  |u| <= 2^-8, so
-// the series of log2(1 + u) ends after u^6 (the next term is below 3e-18).
+// log2 of a normal r2 > 0 is an exponent plus log2 of a mantissa in [1/s, s), s =
+// 1 + kLogLow / 128 (about the square root of 2), so that both parts vanish
+// together at r2 = 1 and a logarithm near zero keeps its digits.  In terms of the
+// hardware's mantissa m in [1/2, 1): log2(m) or log2(2 m) is T_i + log2(1 + u)
+// with u = m c_i - 1, c_i the reciprocal of the middle of m's interval of width
+// 2^-8 and T_i = -log2 c_i or -log2(c_i / 2).  The intervals at m = 1/2 and below
+// 1 take c = 2 and 1 instead, for which u is exact and T = 0.  |u| <= 2^-7
+// there, 2^-8 elsewhere: the series of log2(1 + u) up to u^7, its u^8 term folded
+// into the lower ones over |u| <= 2^-7 by Chebyshev's T_7 (economisation; what
+// is left is below 4e-18 of the logarithm).
 constexpr int kLogBits = 7;
 constexpr int kLogTable = 1 << kLogBits;
+constexpr int kLogLow = 53;  // intervals whose mantissas count twice: 2 m < s
+constexpr uint32_t kLogBase = (1022u << 20) + ((uint32_t)kLogLow << (20 - kLogBits));
 __device__ __forceinline__ void fill_log_table(double2* tab) {
   for (int i = threadIdx.x; i < kLogTable; i += blockDim.x) {
-    const double c = 1.0 / (0.5 + ((double)i + 0.5) * (0.5 / kLogTable));
-    tab[i] = make_double2(c, -log2(c));
+    const double c = i == 0               ? 2.0
+                     : i == kLogTable - 1 ? 1.0
+                                          : 1.0 / (0.5 + ((double)i + 0.5) * (0.5 / kLogTable));
+    tab[i] = make_double2(c, 0.0 - log2(i < kLogLow ? 0.5 * c : c));
   }
 }
 
@@ -57,16 +67,17 @@ __device__ __forceinline__ void add_pairs2(const double (&dx)[U], const double (
     const uint32_t hi = (uint32_t)__double2hiint(r2[u]);
     const double2 t = tab[(hi >> (20 - kLogBits)) & (kLogTable - 1)];
     const double m = __builtin_amdgcn_frexp_mant(r2[u]);
-    const double ef = (double)__builtin_amdgcn_frexp_exp(r2[u]);
+    const double ef = (double)((int32_t)(hi - kLogBase) >> 20);
     double y0 = __builtin_amdgcn_rcp(r2[u]);  // relative error e at most 2^-24.3 (measured)
     const double e = fma(-r2[u], y0, 1.0);
     y0 = fma(y0, fma(e, e, e), y0);  // 1 / r2 = y0 / (1 - e) = y0 (1 + e + e^2 + ...)
     const double w = q[u] * y0;
     const double v = fma(m, t.x, -1.0);
-    double p = fma(v, -0.24044917348149390, 0.28853900817779268);  // (-1)^(k+1) / (k ln 2)
-    p = fma(p, v, -0.36067376022224085);
-    p = fma(p, v, 0.48089834696298780);
-    p = fma(p, v, -0.72134752044448170);
+    double p = fma(v, 0.2060992915555662, -0.24046843553839053);  // (-1)^k / ((k + 1) ln 2)
+    p = fma(p, v, 0.28853900817779266);
+    p = fma(p, v, -0.3606737596344095);
+    p = fma(p, v, 0.4808983469629878);
+    p = fma(p, v, -0.7213475204444861);
     p = fma(p, v, 1.4426950408889634);
     a.fr = fma(q[u], fma(p, v, t.y), a.fr);
     a.ex2 = fma(q[u], ef, a.ex2);
