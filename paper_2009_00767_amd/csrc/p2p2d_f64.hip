@@ -137,8 +137,48 @@ __device__ __forceinline__ void pairs2_f64(double x, double y, const double (&sx
   add_pairs2<U>(dx, dy, r2, q, tab, a);
 }
 
-__device__ __forceinline__ void store_near(const FmmArgs& a, int64_t j, const NearSum& s) {
-  a.near_pot[j] = (s.fr + s.ex2) * 0.34657359027997264;  // (ln 2) / 2: log r = log2(r^2) ln2 / 2
+// The potential of a target in leaf `key` by the library's logarithm, one term at a
+// time (in units of log2 r^2; lsh: see walk_near2d).
+__device__ __forceinline__ double near_by_terms(const LevelTable& lt, uint32_t key,
+                                                const double* __restrict__ xs,
+                                                const double* __restrict__ ys,
+                                                const double* __restrict__ qs,
+                                                const int32_t* __restrict__ leaf_start, int lsh,
+                                                double x, double y) {
+  const uint32_t lmask = local2(0xFFFFFFFFu, lt.L), sysbits = key & ~lmask;
+  const int lx = (int)compact2(key & lmask), ly = (int)compact2((key & lmask) >> 1);
+  const int nl = 1 << lt.L;
+  double sum = 0.0;
+#pragma unroll 1
+  for (int b = 0; b < 9; ++b) {
+    const int nx = lx - 1 + b % 3, ny = ly - 1 + b / 3;
+    if (nx < 0 || nx >= nl || ny < 0 || ny >= nl) continue;
+    const int64_t nk = (int64_t)(sysbits | spread2(nx) | (spread2(ny) << 1));
+    const int32_t i1 = leaf_start[(nk + 1) << lsh];
+#pragma unroll 1
+    for (int32_t i = leaf_start[nk << lsh]; i < i1; ++i) {
+      const double dx = x - xs[i], dy = y - ys[i], r2 = fma(dx, dx, dy * dy);
+      if (r2 != 0.0) sum += qs[i] * log2(r2);
+    }
+  }
+  return sum;
+}
+
+// The two parts of a logarithm may differ in sign, and either may be zero: with
+// infinite charges, or charges near the end of the range, their sums can be inf -
+// inf, inf * 0 or beyond the range where the terms' own sum is not.  Such a target
+// is done again (a sum of whole terms in the loops cost the clustered case 3 %
+// more).
+__device__ __forceinline__ void store_near(const FmmArgs& a, int64_t j, const NearSum& s,
+                                           uint32_t key, const double* __restrict__ xs,
+                                           const double* __restrict__ ys,
+                                           const double* __restrict__ qs,
+                                           const int32_t* __restrict__ leaf_start, int lsh,
+                                           double x, double y) {
+  double lg = s.fr + s.ex2;
+  if (!(fabs(lg) < __builtin_inf()))
+    lg = near_by_terms(a.lt, key, xs, ys, qs, leaf_start, lsh, x, y);
+  a.near_pot[j] = lg * 0.34657359027997264;  // (ln 2) / 2: log r = log2(r^2) ln2 / 2
   a.near_ex[j] = s.ex;
   a.near_ey[j] = s.ey;
 }
@@ -238,7 +278,7 @@ __device__ __forceinline__ void near_direct(const FmmArgs& a, int over,
     }
     if (t % P != 0) return;
   }
-  store_near(a, j, s);
+  store_near(a, j, s, key, xs, ys, qs, leaf_start, lsh, x, y);
 }
 
 template <int P>
@@ -341,7 +381,7 @@ __global__ __launch_bounds__(256) void k_p2p2d_f64_tile(FmmArgs a, int cap) {
       s.ex += __shfl_xor(s.ex, d, 64);
       s.ey += __shfl_xor(s.ey, d, 64);
     }
-    if (part == 0) store_near(a, j, s);
+    if (part == 0) store_near(a, j, s, a.keys[j], a.xs, a.ys, a.qs, a.leaf_start, 0, x, y);
   }
 }
 

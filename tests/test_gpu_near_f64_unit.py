@@ -1,6 +1,6 @@
 """The FP64 near field of the 2D log kernel for pairs about one unit apart, where
-log r^2 vanishes, in every form of the kernel (sixteen, four and one lane a
-target, tiles, the plan-free evaluation).
+log r^2 vanishes, and for infinite charges, in every form of the kernel (sixteen,
+four and one lane a target, tiles, the plan-free evaluation).
 
 Every charge is zero but one, so a target's potential is one pair's term.  The
 distances are exact in FP64 and so is r^2; relative tolerance 8 * 2^-53: the
@@ -57,3 +57,12 @@ def test_unit_distance(n, L, side, noalloc):
     pot = potentials(n, L, side, noalloc, (c, c), np.array(off), 1.0)
     assert pot[0] == 0.0
     np.testing.assert_allclose(pot, want, rtol=8 * 2.0 ** -53, atol=0.0)
+
+
+@pytest.mark.parametrize("charge", [np.inf, -np.inf])
+@pytest.mark.parametrize("n,L,side,noalloc", FORMS)
+def test_infinite_charge(n, L, side, noalloc, charge):
+    r = np.array([0.25, 0.6, 0.8, 0.9, 1.1, 1.3, 1.75])
+    c = 0.5 * side + 0.25
+    pot = potentials(n, L, side, noalloc, (c, c), np.stack([r, 0.0 * r], axis=1), charge)
+    np.testing.assert_array_equal(pot, np.where(r < 1.0, -charge, charge))
