@@ -253,7 +253,7 @@ extern "C" int fmm_eval_noalloc(const fmm_options* opt, int64_t n, const double*
   int32_t* vals_alt = c.take<int32_t>(n);
   int32_t* hist = c.take<int32_t>(radix_hist_entries(n));
   int32_t* tot = c.take<int32_t>(256);
-  const bool one = sort_in_one(n, bits);
+  const bool one = sort_in_one(n, bits, false);
   const bool two_digit = !one && radix_two_digit(n, bits);
   int32_t* parts = two_digit ? c.take<int32_t>(radix_two_digit_parts()) : nullptr;
   int32_t* leaf_start = c.take<int32_t>(nleaf + 1);

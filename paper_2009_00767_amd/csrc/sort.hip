@@ -659,8 +659,17 @@ void radix_sort_two_digit(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int
 // launch instead of five or six: they are bound by latency, not by work.
 // ---------------------------------------------------------------------------
 constexpr int kOneThreads = 1024, kOneWaves = kOneThreads / 64;
-constexpr int kOneMax = 8192;   // particles
-constexpr int kOneBits = 12;    // key bits
+constexpr int kOneBits = 12;  // key bits
+// Particles: one workgroup's chain grows with them and the launches' latency does
+// not.  Whole evaluations against the launches (two digits or radix passes), FP64
+// at levels 3 to 6: 3000 particles 42.6, 41.8, 51.6, 84.3 us against 49.1, 48.2,
+// 57.2, 87.2; 4096: 46.6, 44.7, 54.9, 82.1 against 50.2, 49.1, 57.3, 82.5; 5000:
+// 56.5, 51.4, 62.0, 85.7 against 56.1, 50.7, 57.1, 78.6.  An evaluation on two
+// streams (FP32 modes) also waits for the host, which the launches keep longer:
+// 6000 particles 91.0, 77.3, 90.2, 103.7 against 95.6, 83.0, 93.5, 105.2; 7000: 99.9,
+// 77.3, 89.2, 101.5 against 103.8, 82.0, 90.4, 101.1; 8192: 117.5, 80.6, 91.8, 102.5
+// against 115.6, 82.6, 90.7, 100.0.
+constexpr int kOneMax = 4096, kOneMaxForked = 6144;
 
 template <int D, int PER>  // PER: particles per thread
 __global__ __launch_bounds__(kOneThreads) void k_sort_one(
@@ -769,7 +778,9 @@ __global__ __launch_bounds__(kOneThreads) void k_sort_one(
   }
 }
 
-bool sort_in_one(int64_t n, int bits) { return n <= kOneMax && bits <= kOneBits; }
+bool sort_in_one(int64_t n, int bits, bool forked) {
+  return n <= (forked ? kOneMaxForked : kOneMax) && bits <= kOneBits;
+}
 
 void launch_sort_one(int dim, const double* pos, const double* q, int64_t n, const LevelTable& lt,
                      int bits, uint32_t* keys, int32_t* vals, int32_t* flag, int32_t tag,
@@ -783,11 +794,11 @@ void launch_sort_one(int dim, const double* pos, const double* q, int64_t n, con
   if (dim == 2) {
     if (n <= 2 * kOneThreads) SFFMM_ONE(2, 2);
     else if (n <= 4 * kOneThreads) SFFMM_ONE(2, 4);
-    else SFFMM_ONE(2, 8);
+    else SFFMM_ONE(2, 6);
   } else {
     if (n <= 2 * kOneThreads) SFFMM_ONE(3, 2);
     else if (n <= 4 * kOneThreads) SFFMM_ONE(3, 4);
-    else SFFMM_ONE(3, 8);
+    else SFFMM_ONE(3, 6);
   }
 #undef SFFMM_ONE
 }

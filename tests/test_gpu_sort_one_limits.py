@@ -1,0 +1,42 @@
+"""The particle sort on both sides of the one-workgroup form's limits (4096
+particles, 6144 in the FP32 modes, 12 key bits): permutation, keys and leaf offsets
+bit-exact, the permutation being the stable argsort of the leaf keys."""
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+F = pytest.importorskip("paper_2009_00767_amd")
+
+
+def morton(c):
+    key = np.zeros(len(c), np.int64)
+    for b in range(7):
+        for d in range(c.shape[1]):
+            key |= ((c[:, d] >> b) & 1) << (b * c.shape[1] + d)
+    return key
+
+
+@pytest.mark.parametrize("n", [4095, 4096, 4097, 5119, 6143, 6144, 6145])
+@pytest.mark.parametrize("dim,L", [(2, 0), (2, 4), (2, 5), (2, 6), (2, 7), (3, 2), (3, 4)])
+@pytest.mark.parametrize("prec", [F.FMM_FP64, F.FMM_FP32])
+def test_both_sides(n, dim, L, prec):
+    make = workloads.uniform if n % 2 else workloads.gaussian_mixture
+    pos, q = make(n, dim, seed=n)
+    f = F.FMM(F.FMM_LOG2D if dim == 2 else F.FMM_COULOMB3D, levels=L, order=4, precision=prec,
+              max_particles=n, flags=F.FMM_SYNC_CHECK)
+    f.evaluate(torch.from_numpy(pos).cuda(), torch.from_numpy(q).cuda())
+    nleaf = 2 ** (dim * L)
+    perm = np.frombuffer(F.fmm_debug_level_data(f.plan, 0, F.FMM_DBG_PERM, 4 * n), np.int32)
+    keys = np.frombuffer(F.fmm_debug_level_data(f.plan, 0, F.FMM_DBG_SORTED_KEYS, 4 * n), np.uint32)
+    start = np.frombuffer(F.fmm_debug_level_data(f.plan, 0, F.FMM_DBG_LEAF_START, 4 * (nleaf + 1)),
+                          np.int32)
+    f.close()
+    k = morton(np.minimum(np.floor(pos * (2 ** L / 5.0)).astype(np.int64), 2 ** L - 1))
+    want = np.argsort(k, kind="stable")
+    np.testing.assert_array_equal(perm, want)
+    np.testing.assert_array_equal(keys.astype(np.int64), k[want])
+    np.testing.assert_array_equal(start, np.searchsorted(k[want], np.arange(nleaf + 1), "left"))
