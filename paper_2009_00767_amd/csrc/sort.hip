@@ -365,21 +365,34 @@ int radix_sort(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_
 // bucket is sorted stably by its low lb bits and the leaf offsets of its 2^lb
 // keys are written from the same counts, which replaces the second pass's
 // count, scan and scatter and the leaf-offset search.  Two launches share the
-// buckets.  The first has one workgroup per bucket: a bucket that fits the LDS
-// stage is placed there at its final order and written out in one coalesced
-// sweep; for a larger one (clustered inputs) it counts the digits of each of
-// the bucket's kBucketSplit parts into a table.  In the second (left out when n
-// itself fits a stage), the kBucketSplit workgroups of such a bucket each place
-// one part, their digit offsets taken from the table, straight to the final
-// places (the workgroups of the other buckets leave at once).  Inside a
-// workgroup every wave takes a contiguous piece: after one count of each wave's
-// digits and one scan, the waves rank and place their pieces 64 keys at a time
-// with no further barrier (a wave's running digit offsets in LDS, read and
+// buckets.  The first has one workgroup per bucket, which places a bucket that
+// fits the LDS stage there at its final order and writes it out in one coalesced
+// sweep, and one per part of the larger buckets (clustered inputs), which counts
+// the part's digits into a table.  In the second (left out when n itself fits a
+// stage), a workgroup per part places it, its digit offsets taken from the
+// table, straight to the final places.  Parts have a fixed size and are numbered
+// over all larger buckets, so both launches hold workgroups for the most parts n
+// can make, and the work of a dense bucket is spread over the chip (10^6 particles
+// in one bucket: 44 us; with eight parts a bucket, counted by one workgroup, 949).
+// Inside a workgroup every wave takes a contiguous piece: after one count of each
+// wave's digits and one scan, the waves rank and place their pieces 64 keys at a
+// time with no further barrier (a wave's running digit offsets in LDS, read and
 // advanced in program order).  In FP64 mode the sorted coordinates and charges
 // are gathered in the same sweep.
 constexpr int kBucketCap = 5120;       // elements of a bucket the LDS stage holds
 constexpr int kBucketCapSmall = 1280;  // the same for small n (four waves a bucket)
-constexpr int kBucketSplit = 8;        // parts of a bucket beyond the stage
+constexpr int kBucketParts = 512;      // rows of the parts' table
+// Elements of a part: a few 64-key chunks a wave (the launches' quick exits cost
+// more with smaller ones).
+constexpr int bucket_part(int cap) { return cap * 8 / 5; }
+// The most parts that n elements make: every larger bucket holds more than cap.
+constexpr int64_t bucket_parts(int64_t n, int cap) {
+  return n > cap ? n / bucket_part(cap) + n / cap : 0;
+}
+constexpr int64_t two_digit_max(int cap) { return 256 * (cap * 9 / 10); }
+static_assert(bucket_parts(two_digit_max(kBucketCap), kBucketCap) <= kBucketParts &&
+                  bucket_parts(two_digit_max(kBucketCapSmall), kBucketCapSmall) <= kBucketParts,
+              "the parts' table holds every part");
 
 // Sorted FP64 coordinates and charges of the particle of sorted place `dst`.
 struct GatherOut {
@@ -418,12 +431,33 @@ __device__ __forceinline__ void bucket_range(const int32_t* __restrict__ tot, in
   __syncthreads();
 }
 
-// Part s of a bucket of m elements: [s per, min(m, (s + 1) per)).
-__device__ __forceinline__ int bucket_part_size(int m) {
-  return (m + kBucketSplit - 1) / kBucketSplit;
+struct BucketPart {
+  int64_t b0;  // the bucket's first place
+  int32_t b, m, part, parts, row0;  // bucket, its size, part, its parts and their first row
+};
+// Part p of those of all buckets beyond the stage (every thread of the workgroup
+// calls it); false if there is none.
+template <int NT, int CAP>
+__device__ __forceinline__ bool find_part(const int32_t* __restrict__ tot, int64_t n, int p,
+                                          int32_t* wt, BucketPart* out) {
+  constexpr int kPart = bucket_part(CAP);
+  const int t = threadIdx.x;
+  const int32_t m = t < 256 ? tot[t] : 0;
+  const int32_t pc = m > CAP ? (m + kPart - 1) / kPart : 0;
+  if (!__syncthreads_or(pc != 0)) return false;
+  int32_t all;
+  const int32_t ex = block_exclusive_scan<NT>(m, wt, &all);
+  const int32_t row0 = block_exclusive_scan<NT>(pc, wt, &all);
+  if (p >= all || all > kBucketParts) return false;  // (the latter: inconsistent counts only)
+  if (p >= row0 && p < row0 + pc)
+    *out = BucketPart{ex, t, (int32_t)(ex + (int64_t)m <= n ? m : (n > ex ? n - ex : 0)), p - row0,
+                      pc, row0};
+  __syncthreads();
+  return true;
 }
 
-// CAP: the stage of the launch with STAGED set.
+// STAGED: workgroups 0..255 the buckets, the others the counts of the parts; else
+// a part a workgroup.  CAP: the stage of the launch with STAGED set.
 template <int NT, bool STAGED, int CAP>
 __global__ __launch_bounds__(NT) void k_bucket_sort(
     const uint32_t* __restrict__ kin, const int32_t* __restrict__ vin,
@@ -442,38 +476,45 @@ __global__ __launch_bounds__(NT) void k_bucket_sort(
   __shared__ int32_t wt[NW];
   __shared__ int64_t s_b0;
   __shared__ int32_t s_m;
+  __shared__ BucketPart s_at;
+  constexpr int kPart = bucket_part(CAP);
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int b = STAGED ? (int)blockIdx.x : (int)blockIdx.x / kBucketSplit;
-  const int part = STAGED ? 0 : (int)blockIdx.x % kBucketSplit;
-  bucket_range<NT>(tot, n, b, wt, &s_b0, &s_m);
-  const int64_t b0 = s_b0;
-  const int m = s_m;
-  const bool fits = m <= CAP;
-  if (!STAGED && fits) return;  // sorted by the first launch (workgroup-uniform)
-  const int per = bucket_part_size(m);
-  if (STAGED && !fits) {
-    // count the digits of each part of this bucket into parts[b][s][256]
-    for (int s = 0; s < kBucketSplit; ++s) {
-      if (t < 256) all_cnt[t] = 0;
-      __syncthreads();
-      const int plo = min(m, s * per), phi = min(m, plo + per);
-      for (int g0 = plo + wave * 64 * G; g0 < phi; g0 += NT * G) {
-        uint32_t k2[G];
+  if (STAGED && blockIdx.x >= 256) {  // count the digits of a part
+    if (!find_part<NT, CAP>(tot, n, (int)blockIdx.x - 256, wt, &s_at)) return;
+    const int64_t b0 = s_at.b0;
+    const int plo = min(s_at.m, s_at.part * kPart), phi = min(s_at.m, plo + kPart);
+    if (t < 256) all_cnt[t] = 0;
+    __syncthreads();
+    for (int g0 = plo + wave * 64 * G; g0 < phi; g0 += NT * G) {
+      uint32_t k2[G];
 #pragma unroll
-        for (int c = 0; c < G; ++c) {
-          const int e = g0 + 64 * c + lane;
-          k2[c] = e < phi ? kin[b0 + e] : 0u;
-        }
-#pragma unroll
-        for (int c = 0; c < G; ++c)
-          if (g0 + 64 * c < phi) count_digits(all_cnt, k2[c] & low, g0 + 64 * c + lane < phi);
+      for (int c = 0; c < G; ++c) {
+        const int e = g0 + 64 * c + lane;
+        k2[c] = e < phi ? kin[b0 + e] : 0u;
       }
-      __syncthreads();
-      if (t < 256) parts[((int64_t)b * kBucketSplit + s) * 256 + t] = all_cnt[t];
+#pragma unroll
+      for (int c = 0; c < G; ++c)
+        if (g0 + 64 * c < phi) count_digits(all_cnt, k2[c] & low, g0 + 64 * c + lane < phi);
     }
+    __syncthreads();
+    if (t < 256) parts[(int64_t)(s_at.row0 + s_at.part) * 256 + t] = all_cnt[t];
     return;
   }
-  const int lo = STAGED ? 0 : min(m, part * per), hi = STAGED ? m : min(m, lo + per);
+  int b, part = 0, lo = 0;
+  if (STAGED) {
+    b = (int)blockIdx.x;
+    bucket_range<NT>(tot, n, b, wt, &s_b0, &s_m);
+    if (s_m > CAP) return;  // in parts (workgroup-uniform)
+  } else {
+    if (!find_part<NT, CAP>(tot, n, (int)blockIdx.x, wt, &s_at)) return;
+    b = s_at.b;
+    part = s_at.part;
+    lo = part * kPart;
+  }
+  const int64_t b0 = STAGED ? s_b0 : s_at.b0;
+  const int m = STAGED ? s_m : s_at.m;
+  const int hi = STAGED ? m : min(m, lo + kPart);
+  lo = min(lo, hi);
   const int wper = (hi - lo + NW - 1) / NW;  // STAGED: at most 64 G
   const int wlo = min(hi, lo + wave * wper), whi = min(hi, wlo + wper);  // this wave's piece
   if (t < 256) {
@@ -484,8 +525,9 @@ __global__ __launch_bounds__(NT) void k_bucket_sort(
     } else {
       // the bucket's digit counts and those of the parts before this one
       int32_t a = 0, p = 0;
-      for (int s = 0; s < kBucketSplit; ++s) {
-        const int32_t c = parts[((int64_t)b * kBucketSplit + s) * 256 + t];
+#pragma unroll 8
+      for (int s = 0; s < s_at.parts; ++s) {
+        const int32_t c = parts[(int64_t)(s_at.row0 + s) * 256 + t];
         a += c;
         if (s < part) p += c;
       }
@@ -604,10 +646,10 @@ __global__ __launch_bounds__(NT) void k_bucket_sort(
 
 bool radix_two_digit(int64_t n, int bits) {
   if (bits <= 8 || bits > 16 || n <= 0) return false;
-  return n <= 256 * (kBucketCap * 9 / 10);  // the mean bucket well inside the stage
+  return n <= two_digit_max(kBucketCap);  // the mean bucket well inside the stage
 }
 
-size_t radix_two_digit_parts() { return (size_t)256 * kBucketSplit * 256; }
+size_t radix_two_digit_parts() { return (size_t)kBucketParts * 256; }
 
 template <int NT, int CAP>
 static void bucket_sorts(uint32_t* keys, int32_t* vals, const uint32_t* keys_alt,
@@ -619,13 +661,14 @@ static void bucket_sorts(uint32_t* keys, int32_t* vals, const uint32_t* keys_alt
   if (lds > 65536)
     (void)hipFuncSetAttribute((const void*)k_bucket_sort<NT, true, CAP>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL((k_bucket_sort<NT, true, CAP>), dim3(256), dim3(NT), lds, st, keys_alt,
+  const unsigned np = (unsigned)bucket_parts(n, CAP);
+  hipLaunchKernelGGL((k_bucket_sort<NT, true, CAP>), dim3(256 + np), dim3(NT), lds, st, keys_alt,
                      vals_alt, recs_alt, keys, vals, recs, n, lb, tot, leaf_start, nleaf, parts,
                      go);
-  if (n > CAP)  // (else no bucket outgrows the stage)
-    hipLaunchKernelGGL((k_bucket_sort<512, false, CAP>), dim3(256 * kBucketSplit), dim3(512), 0,
-                       st, keys_alt, vals_alt, recs_alt, keys, vals, recs, n, lb, tot, leaf_start,
-                       nleaf, parts, go);
+  if (np > 0)  // (else no bucket outgrows the stage)
+    hipLaunchKernelGGL((k_bucket_sort<512, false, CAP>), dim3(np), dim3(512), 0, st, keys_alt,
+                       vals_alt, recs_alt, keys, vals, recs, n, lb, tot, leaf_start, nleaf, parts,
+                       go);
 }
 
 // Four waves a bucket while the mean bucket lies well inside their stage (20,011
@@ -643,7 +686,7 @@ void radix_sort_two_digit(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int
   hipLaunchKernelGGL(k_scan_rows, dim3(256), dim3(256), 0, st, hist, ntiles, tot);
   hipLaunchKernelGGL(k_rs_scatter, dim3(ntiles), dim3(kScatterThreads), lds, st, keys, vals,
                      keys_alt, vals_alt, n, lb, hist, tot, ntiles, recs, recs_alt);
-  if (n <= 256 * (kBucketCapSmall * 9 / 10))
+  if (n <= two_digit_max(kBucketCapSmall))
     bucket_sorts<256, kBucketCapSmall>(keys, vals, keys_alt, vals_alt, n, lb, tot, leaf_start,
                                        nleaf, parts, st, recs, recs_alt, go);
   else
