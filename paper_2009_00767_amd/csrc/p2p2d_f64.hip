@@ -22,28 +22,40 @@ namespace {
 // Targets up to which sixteen, and four, lanes share one (launch_p2p2d_f64).
 constexpr int64_t kLanes16 = 1 << 14, kLanes4 = 1 << 16;
 
-// log2 of a normal r2 > 0 is an exponent plus log2 of a mantissa in [1/s, s), s =
-// 1 + kLogLow / 128 (about the square root of 2), so that both parts vanish
-// together at r2 = 1 and a logarithm near zero keeps its digits.  In terms of the
-// hardware's mantissa m in [1/2, 1): log2(m) or log2(2 m) is T_i + log2(1 + u)
-// with u = m c_i - 1, c_i the reciprocal of the middle of m's interval of width
-// 2^-8 and T_i = -log2 c_i or -log2(c_i / 2).  The intervals at m = 1/2 and below
-// 1 take c = 2 and 1 instead, for which u is exact and T = 0.  |u| <= 2^-7
-// there, 2^-8 elsewhere: the series of log2(1 + u) up to u^7, its u^8 term folded
-// into the lower ones over |u| <= 2^-7 by Chebyshev's T_7 (economisation; what
-// is left is below 4e-18 of the logarithm).
+// log2 of a normal r2 > 0 from the hardware's mantissa m in [1/2, 1) and exponent:
+// log2(m) is T_i + log2(1 + u) with u = m c_i - 1, c_i the reciprocal of the middle
+// of m's interval of width 2^-8 and T_i = -log2 c_i.  |u| <= 2^-8, so the series of
+// log2(1 + u) ends after u^6 (the next term is below 3e-18).
+//
+// UNIT (pairs can be about one unit apart, near_unit): exponent and mantissa
+// parts must vanish together at r2 = 1, or a logarithm near zero loses its
+// digits to their cancellation.  The mantissa then runs over [1/s, s), s = 1 +
+// kLogLow / 128 (about the square root of 2): intervals below kLogLow stand for 2 m, T_i
+// = -log2(c_i / 2), and the exponent is one less.  The intervals at m = 1/2 and
+// below 1 take c = 2 and 1, for which u is exact and T = 0; |u| <= 2^-7 there,
+// so the series goes up to u^7, its u^8 term folded into the lower ones over |u|
+// <= 2^-7 by Chebyshev's T_7 (economisation; what is left is below 4e-18 of the
+// logarithm).  Two instructions a pair more, so only where it matters: 500,009
+// clustered particles (level 8 of a box of side 5) 1502 us a call, with it 1554.
 constexpr int kLogBits = 7;
 constexpr int kLogTable = 1 << kLogBits;
-constexpr int kLogLow = 53;  // intervals whose mantissas count twice: 2 m < s
+constexpr int kLogLow = 53;
 constexpr uint32_t kLogBase = (1022u << 20) + ((uint32_t)kLogLow << (20 - kLogBits));
+template <bool UNIT>
 __device__ __forceinline__ void fill_log_table(double2* tab) {
   for (int i = threadIdx.x; i < kLogTable; i += blockDim.x) {
-    const double c = i == 0               ? 2.0
-                     : i == kLogTable - 1 ? 1.0
-                                          : 1.0 / (0.5 + ((double)i + 0.5) * (0.5 / kLogTable));
-    tab[i] = make_double2(c, 0.0 - log2(i < kLogLow ? 0.5 * c : c));
+    double c = 1.0 / (0.5 + ((double)i + 0.5) * (0.5 / kLogTable));
+    if (UNIT) c = i == 0 ? 2.0 : i == kLogTable - 1 ? 1.0 : c;
+    tab[i] = make_double2(c, 0.0 - log2(UNIT && i < kLogLow ? 0.5 * c : c));
   }
 }
+
+// Whether sources of the leaves around a target (at most two leaf sides away in
+// each direction) can reach r2 = 1: below, r2 lies in intervals where exponent and
+// mantissa parts do not cancel.
+bool near_unit(const LevelTable& lt) { return !(8.0 * lt.s[lt.L] * lt.s[lt.L] < 0.98); }
+
+constexpr double kHalfLn2 = 0.34657359027997264;  // log r = log2(r^2) (ln 2) / 2
 
 // Running sums of a target: log2(r^2) in two parts (the exponents' share is
 // kept apart, so that neither part rounds at the other's magnitude), and the field.
@@ -58,7 +70,7 @@ __device__ __forceinline__ double near_threshold(double side) {
 }
 
 // The sums of U pairs at dx, dy, r2 (a normal number of FP64's range).
-template <int U>
+template <int U, bool UNIT>
 __device__ __forceinline__ void add_pairs2(const double (&dx)[U], const double (&dy)[U],
                                            const double (&r2)[U], const double (&q)[U],
                                            const double2* tab, NearSum& a) {
@@ -67,17 +79,26 @@ __device__ __forceinline__ void add_pairs2(const double (&dx)[U], const double (
     const uint32_t hi = (uint32_t)__double2hiint(r2[u]);
     const double2 t = tab[(hi >> (20 - kLogBits)) & (kLogTable - 1)];
     const double m = __builtin_amdgcn_frexp_mant(r2[u]);
-    const double ef = (double)((int32_t)(hi - kLogBase) >> 20);
+    const double ef = UNIT ? (double)((int32_t)(hi - kLogBase) >> 20)
+                           : (double)__builtin_amdgcn_frexp_exp(r2[u]);
     double y0 = __builtin_amdgcn_rcp(r2[u]);  // relative error e at most 2^-24.3 (measured)
     const double e = fma(-r2[u], y0, 1.0);
     y0 = fma(y0, fma(e, e, e), y0);  // 1 / r2 = y0 / (1 - e) = y0 (1 + e + e^2 + ...)
     const double w = q[u] * y0;
     const double v = fma(m, t.x, -1.0);
-    double p = fma(v, 0.2060992915555662, -0.24046843553839053);  // (-1)^k / ((k + 1) ln 2)
-    p = fma(p, v, 0.28853900817779266);
-    p = fma(p, v, -0.3606737596344095);
-    p = fma(p, v, 0.4808983469629878);
-    p = fma(p, v, -0.7213475204444861);
+    double p;
+    if constexpr (UNIT) {
+      p = fma(v, 0.2060992915555662, -0.24046843553839053);  // (-1)^k / ((k + 1) ln 2), folded
+      p = fma(p, v, 0.28853900817779266);
+      p = fma(p, v, -0.3606737596344095);
+      p = fma(p, v, 0.4808983469629878);
+      p = fma(p, v, -0.7213475204444861);
+    } else {
+      p = fma(v, -0.24044917348149390, 0.28853900817779268);  // (-1)^k / ((k + 1) ln 2)
+      p = fma(p, v, -0.36067376022224085);
+      p = fma(p, v, 0.48089834696298780);
+      p = fma(p, v, -0.72134752044448170);
+    }
     p = fma(p, v, 1.4426950408889634);
     a.fr = fma(q[u], fma(p, v, t.y), a.fr);
     a.ex2 = fma(q[u], ef, a.ex2);
@@ -89,7 +110,7 @@ __device__ __forceinline__ void add_pairs2(const double (&dx)[U], const double (
 // U sources at once.  Whether some lane has a pair at r = 0 or below thr is one
 // compare a pair (its mask is joined in scalar registers); the batch then takes
 // a path of its own, so that the others carry nothing of it.
-template <int U>
+template <int U, bool UNIT>
 __device__ __forceinline__ void pairs2_f64(double x, double y, const double (&sx)[U],
                                            const double (&sy)[U], const double (&q)[U],
                                            double thr, const double2* tab, NearSum& a) {
@@ -131,23 +152,30 @@ __device__ __forceinline__ void pairs2_f64(double x, double y, const double (&sx
       }
       return;
     }
-    add_pairs2<U>(dx, dy, r, c, tab, a);
+    add_pairs2<U, UNIT>(dx, dy, r, c, tab, a);
     return;
   }
-  add_pairs2<U>(dx, dy, r2, q, tab, a);
+  add_pairs2<U, UNIT>(dx, dy, r2, q, tab, a);
 }
 
-// The potential of a target in leaf `key` by the library's logarithm, one term at a
-// time (in units of log2 r^2; lsh: see walk_near2d).
-__device__ __forceinline__ double near_by_terms(const LevelTable& lt, uint32_t key,
-                                                const double* __restrict__ xs,
-                                                const double* __restrict__ ys,
-                                                const double* __restrict__ qs,
-                                                const int32_t* __restrict__ leaf_start, int lsh,
-                                                double x, double y) {
+// The potential of target j again, by the library's logarithm and one term at a
+// time.  The two parts of a logarithm may differ in sign, and either may be zero:
+// with infinite charges, or charges near the end of the range, their sums can be
+// inf - inf, inf * 0 or beyond the range where the terms' own sum is not, so a
+// target whose sum is not finite comes here (a sum of whole terms in the loops cost
+// the clustered case 3 % more).  Everything is read again, so that the loops hold
+// no register for it.  lsh: see walk_near2d.
+__device__ __forceinline__ void near_by_terms(const FmmArgs& a, int64_t j,
+                                              const double* __restrict__ xs,
+                                              const double* __restrict__ ys,
+                                              const double* __restrict__ qs,
+                                              const int32_t* __restrict__ leaf_start, int lsh) {
+  const LevelTable& lt = a.lt;
+  const uint32_t key = a.keys[j] >> lsh;
   const uint32_t lmask = local2(0xFFFFFFFFu, lt.L), sysbits = key & ~lmask;
   const int lx = (int)compact2(key & lmask), ly = (int)compact2((key & lmask) >> 1);
   const int nl = 1 << lt.L;
+  const double x = xs[j], y = ys[j];
   double sum = 0.0;
 #pragma unroll 1
   for (int b = 0; b < 9; ++b) {
@@ -161,31 +189,21 @@ __device__ __forceinline__ double near_by_terms(const LevelTable& lt, uint32_t k
       if (r2 != 0.0) sum += qs[i] * log2(r2);
     }
   }
-  return sum;
+  a.near_pot[j] = sum * kHalfLn2;
 }
 
-// The two parts of a logarithm may differ in sign, and either may be zero: with
-// infinite charges, or charges near the end of the range, their sums can be inf -
-// inf, inf * 0 or beyond the range where the terms' own sum is not.  Such a target
-// is done again (a sum of whole terms in the loops cost the clustered case 3 %
-// more).
-__device__ __forceinline__ void store_near(const FmmArgs& a, int64_t j, const NearSum& s,
-                                           uint32_t key, const double* __restrict__ xs,
-                                           const double* __restrict__ ys,
-                                           const double* __restrict__ qs,
-                                           const int32_t* __restrict__ leaf_start, int lsh,
-                                           double x, double y) {
-  double lg = s.fr + s.ex2;
-  if (!(fabs(lg) < __builtin_inf()))
-    lg = near_by_terms(a.lt, key, xs, ys, qs, leaf_start, lsh, x, y);
-  a.near_pot[j] = lg * 0.34657359027997264;  // (ln 2) / 2: log r = log2(r^2) ln2 / 2
+// Whether the potential is finite (else near_by_terms has to follow).
+__device__ __forceinline__ bool store_near(const FmmArgs& a, int64_t j, const NearSum& s) {
+  const double lg = s.fr + s.ex2;
+  a.near_pot[j] = lg * kHalfLn2;
   a.near_ex[j] = s.ex;
   a.near_ey[j] = s.ey;
+  return fabs(lg) < __builtin_inf();
 }
 
 // Sources i0 + P k (k = 0, 1, ...) below i1 in batches of four; the last batch
 // repeats its first source with no charge.
-template <int P>
+template <int P, bool UNIT>
 __device__ __forceinline__ void range2_f64(const double* __restrict__ xs,
                                            const double* __restrict__ ys,
                                            const double* __restrict__ qs, int32_t i0, int32_t i1,
@@ -200,7 +218,7 @@ __device__ __forceinline__ void range2_f64(const double* __restrict__ xs,
       sy[u] = ys[i + u * P];
       q[u] = qs[i + u * P];
     }
-    pairs2_f64<4>(x, y, sx, sy, q, thr, tab, s);
+    pairs2_f64<4, UNIT>(x, y, sx, sy, q, thr, tab, s);
   }
   if (i < i1) {
     double sx[4], sy[4], q[4];
@@ -212,7 +230,7 @@ __device__ __forceinline__ void range2_f64(const double* __restrict__ xs,
       sy[u] = ys[iu];
       q[u] = in ? qs[iu] : 0.0;
     }
-    pairs2_f64<4>(x, y, sx, sy, q, thr, tab, s);
+    pairs2_f64<4, UNIT>(x, y, sx, sy, q, thr, tab, s);
   }
 }
 
@@ -224,7 +242,7 @@ __device__ __forceinline__ void range2_f64(const double* __restrict__ xs,
 // of depth L: leaf keys and leaf offsets are those of level d, and only the
 // targets whose leaf lies at level d are taken.
 // over: only the targets of tiles the tile kernel left.
-template <int P>
+template <int P, bool UNIT>
 __device__ __forceinline__ void near_direct(const FmmArgs& a, int over,
                                             const double* __restrict__ xs,
                                             const double* __restrict__ ys,
@@ -238,7 +256,7 @@ __device__ __forceinline__ void near_direct(const FmmArgs& a, int over,
   const uint32_t key = mine ? a.keys[j] >> lsh : 0u;
   if (over) mine = mine && a.p2p_over[key >> 4];
   if (!__syncthreads_or(mine)) return;
-  fill_log_table(tab);
+  fill_log_table<UNIT>(tab);
   __syncthreads();
   if (!mine) return;
   const double thr = near_threshold(lt.side);
@@ -246,7 +264,7 @@ __device__ __forceinline__ void near_direct(const FmmArgs& a, int over,
   NearSum s;
   if constexpr (P == 1) {
     walk_near2d(lt, key, leaf_start, lsh, [&](int32_t i0, int32_t i1, int, int) {
-      range2_f64<1>(xs, ys, qs, i0, i1, x, y, thr, tab, s);
+      range2_f64<1, UNIT>(xs, ys, qs, i0, i1, x, y, thr, tab, s);
     });
   } else {
     const uint32_t lmask = local2(0xFFFFFFFFu, lt.L), sysbits = key & ~lmask;
@@ -265,7 +283,7 @@ __device__ __forceinline__ void near_direct(const FmmArgs& a, int over,
 #pragma unroll
     for (int b = 0; b < 9; ++b) {
       const int32_t len = i1[b] - i0[b];
-      range2_f64<P>(xs, ys, qs, i0[b] + off, i1[b], x, y, thr, tab, s);
+      range2_f64<P, UNIT>(xs, ys, qs, i0[b] + off, i1[b], x, y, thr, tab, s);
       const int32_t left = len - off;  // sources from this lane's first one on
       off = left > 0 ? (P - left % P) % P : -left;
     }
@@ -278,10 +296,10 @@ __device__ __forceinline__ void near_direct(const FmmArgs& a, int over,
     }
     if (t % P != 0) return;
   }
-  store_near(a, j, s, key, xs, ys, qs, leaf_start, lsh, x, y);
+  if (!store_near(a, j, s)) near_by_terms(a, j, xs, ys, qs, leaf_start, lsh);
 }
 
-template <int P>
+template <int P, bool UNIT>
 __global__ __launch_bounds__(256) void k_p2p2d_f64(FmmArgs a, int over,
                                                    const double* __restrict__ xs,
                                                    const double* __restrict__ ys,
@@ -289,7 +307,7 @@ __global__ __launch_bounds__(256) void k_p2p2d_f64(FmmArgs a, int over,
                                                    const int32_t* __restrict__ leaf_start,
                                                    int lsh) {
   __shared__ double2 tab[kLogTable];
-  near_direct<P>(a, over, xs, ys, qs, leaf_start, lsh, blockIdx.x, tab);
+  near_direct<P, UNIT>(a, over, xs, ys, qs, leaf_start, lsh, blockIdx.x, tab);
 }
 
 // Few particles: the near field and the moments of every level, which both
@@ -298,7 +316,7 @@ __global__ __launch_bounds__(256) void k_p2p2d_f64(FmmArgs a, int over,
 // bound by latency and leave most of the chip idle alone (20,011 particles,
 // order 16, 5 levels: 23 and 12 us one after the other; a call on one stream 85
 // -> 73 us).
-template <int P, int PB, bool FULL>
+template <int P, int PB, bool FULL, bool UNIT>
 __global__ __launch_bounds__(256) void k_near_moments2d(FmmArgs a, P2mPlan pl, int moments,
                                                         const double* __restrict__ xs,
                                                         const double* __restrict__ ys,
@@ -308,7 +326,7 @@ __global__ __launch_bounds__(256) void k_near_moments2d(FmmArgs a, P2mPlan pl, i
   if ((int)blockIdx.x < moments)
     p2m_thread<double, PB, false, FULL>(a, pl, (int64_t)blockIdx.x * 256 + threadIdx.x);
   else
-    near_direct<P>(a, 0, xs, ys, qs, leaf_start, 0, blockIdx.x - moments, tab);
+    near_direct<P, UNIT>(a, 0, xs, ys, qs, leaf_start, 0, blockIdx.x - moments, tab);
 }
 
 // Tile form: a workgroup stages the sources of a 4 x 4-leaf tile's 6 x 6-leaf
@@ -321,6 +339,7 @@ __global__ __launch_bounds__(256) void k_near_moments2d(FmmArgs a, P2mPlan pl, i
 constexpr int kTile64P = 2;
 constexpr int kTile64Cap = 1536;  // records of 24 bytes
 
+template <bool UNIT>
 __global__ __launch_bounds__(256) void k_p2p2d_f64_tile(FmmArgs a, int cap) {
   constexpr int P = kTile64P;
   extern __shared__ double2 sxy[];  // cap positions, then as many charges
@@ -335,7 +354,7 @@ __global__ __launch_bounds__(256) void k_p2p2d_f64_tile(FmmArgs a, int cap) {
   const uint32_t tile = (uint32_t)tl, k0 = tile << 4;
   const uint32_t tm = local2(k0, L);
   const int bx0 = (int)compact2(tm), by0 = (int)compact2(tm >> 1);
-  fill_log_table(tab);
+  fill_log_table<UNIT>(tab);
   tile_halo(lt, a.leaf_start, tile, hstart, hoff);
   const int total = hoff[kP2pHaloLeaves];
   if (tid == 0) a.p2p_over[tile] = total > cap ? 1 : 0;
@@ -348,6 +367,7 @@ __global__ __launch_bounds__(256) void k_p2p2d_f64_tile(FmmArgs a, int cap) {
   const int32_t t0 = a.leaf_start[k0], t1 = a.leaf_start[k0 + 16];
   const double thr = near_threshold(lt.side);
   const int part = tid % P;
+  bool again = false;
   for (int32_t j = t0 + tid / P; j < t1; j += 256 / P) {
     const uint32_t key = local2(a.keys[j], L);
     const int tx = (int)compact2(key) - bx0, ty = (int)compact2(key >> 1) - by0;
@@ -367,11 +387,11 @@ __global__ __launch_bounds__(256) void k_p2p2d_f64_tile(FmmArgs a, int cap) {
           sy[u] = p.y;
           q[u] = sq[c + u * P];
         }
-        pairs2_f64<4>(x, y, sx, sy, q, thr, tab, s);
+        pairs2_f64<4, UNIT>(x, y, sx, sy, q, thr, tab, s);
       }
       for (; c < c1; c += P) {
         double sx[1] = {sxy[c].x}, sy[1] = {sxy[c].y}, q[1] = {sq[c]};
-        pairs2_f64<1>(x, y, sx, sy, q, thr, tab, s);
+        pairs2_f64<1, UNIT>(x, y, sx, sy, q, thr, tab, s);
       }
     }
 #pragma unroll
@@ -381,14 +401,24 @@ __global__ __launch_bounds__(256) void k_p2p2d_f64_tile(FmmArgs a, int cap) {
       s.ex += __shfl_xor(s.ex, d, 64);
       s.ey += __shfl_xor(s.ey, d, 64);
     }
-    if (part == 0) store_near(a, j, s, a.keys[j], a.xs, a.ys, a.qs, a.leaf_start, 0, x, y);
+    if (part == 0 && !store_near(a, j, s)) again = true;
   }
+  if (!again) return;
+#pragma unroll 1
+  for (int j = t0 + tid / P; j < t1; j += 256 / P)
+    if (!(fabs(a.near_pot[j]) < __builtin_inf()))
+      near_by_terms(a, j, a.xs, a.ys, a.qs, a.leaf_start, 0);
 }
 
 template <int P>
 void direct_f64(const FmmArgs& a, int over, int lsh, hipStream_t st) {
-  hipLaunchKernelGGL(k_p2p2d_f64<P>, chunked_grid((a.n * P + 255) / 256), dim3(256), 0, st, a, over,
-                     a.xs, a.ys, a.qs, a.leaf_start, lsh);
+  const dim3 grid = chunked_grid((a.n * P + 255) / 256);
+  if (near_unit(a.lt))
+    hipLaunchKernelGGL((k_p2p2d_f64<P, true>), grid, dim3(256), 0, st, a, over, a.xs, a.ys, a.qs,
+                       a.leaf_start, lsh);
+  else
+    hipLaunchKernelGGL((k_p2p2d_f64<P, false>), grid, dim3(256), 0, st, a, over, a.xs, a.ys, a.qs,
+                       a.leaf_start, lsh);
 }
 
 // Tiles from 1024 of them on (four workgroups a CU).  Below that the chip
@@ -400,26 +430,26 @@ int64_t near_tiles(const FmmArgs& a) {  // 0: the direct form
   return tiles >= 1024 ? tiles : 0;
 }
 
-template <int P, int PB>
+template <int P, int PB, bool FULL>
 void near_moments(const FmmArgs& a, hipStream_t st) {
   const P2mPlan pl = make_p2m_plan(2, a.klo, a.khi, a.n, a.lt.nsys, p2m_lane_particles(true, a.n));
   const int moments = (int)((pl.thr_off[a.khi + 1] + 256 * 8 - 1) / (256 * 8) * 8);
   const dim3 grid(chunked_grid((a.n * P + 255) / 256).x + moments);
-  if (a.ord_full)
-    hipLaunchKernelGGL((k_near_moments2d<P, PB, true>), grid, dim3(256), 0, st, a, pl, moments,
-                       a.xs, a.ys, a.qs, a.leaf_start);
+  if (near_unit(a.lt))
+    hipLaunchKernelGGL((k_near_moments2d<P, PB, FULL, true>), grid, dim3(256), 0, st, a, pl,
+                       moments, a.xs, a.ys, a.qs, a.leaf_start);
   else
-    hipLaunchKernelGGL((k_near_moments2d<P, PB, false>), grid, dim3(256), 0, st, a, pl, moments,
-                       a.xs, a.ys, a.qs, a.leaf_start);
+    hipLaunchKernelGGL((k_near_moments2d<P, PB, FULL, false>), grid, dim3(256), 0, st, a, pl,
+                       moments, a.xs, a.ys, a.qs, a.leaf_start);
   launch_p2m2d_slices(a, pl, PB, true, st);
 }
 
 template <int PB>
 void near_moments_pb(const FmmArgs& a, hipStream_t st) {
   if (a.n <= kLanes16)
-    near_moments<16, PB>(a, st);
+    a.ord_full ? near_moments<16, PB, true>(a, st) : near_moments<16, PB, false>(a, st);
   else
-    near_moments<4, PB>(a, st);
+    a.ord_full ? near_moments<4, PB, true>(a, st) : near_moments<4, PB, false>(a, st);
 }
 
 }  // namespace
@@ -446,8 +476,11 @@ void launch_p2p2d_f64(const FmmArgs& a, hipStream_t st) {
   }
   if (const int64_t tiles = near_tiles(a)) {
     const int cap = p2p2d_tile_cap(a.lt, a.n, kTile64Cap);
-    hipLaunchKernelGGL(k_p2p2d_f64_tile, chunked_grid(tiles), dim3(256),
-                       (size_t)cap * 3 * sizeof(double), st, a, cap);
+    const size_t lds = (size_t)cap * 3 * sizeof(double);
+    if (near_unit(a.lt))
+      hipLaunchKernelGGL(k_p2p2d_f64_tile<true>, chunked_grid(tiles), dim3(256), lds, st, a, cap);
+    else
+      hipLaunchKernelGGL(k_p2p2d_f64_tile<false>, chunked_grid(tiles), dim3(256), lds, st, a, cap);
     direct_f64<1>(a, 1, 0, st);
   } else if (a.n <= kLanes16) {
     direct_f64<16>(a, 0, 0, st);

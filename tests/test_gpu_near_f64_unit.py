@@ -66,3 +66,15 @@ def test_infinite_charge(n, L, side, noalloc, charge):
     c = 0.5 * side + 0.25
     pot = potentials(n, L, side, noalloc, (c, c), np.stack([r, 0.0 * r], axis=1), charge)
     np.testing.assert_array_equal(pot, np.where(r < 1.0, -charge, charge))
+
+
+# Leaves too small for unit distances (side 11/32) take the shorter logarithm.
+@pytest.mark.parametrize("charge", [np.inf, -np.inf])
+@pytest.mark.parametrize("n,L,side,noalloc", [(300, 1, 0.6875, False), (20000, 1, 0.6875, False),
+                                              (66000, 1, 0.6875, False),
+                                              (300000, 7, 44.0, False), (300, 1, 0.6875, True)])
+def test_infinite_charge_small_leaves(n, L, side, noalloc, charge):
+    off = np.array([(0.02, 0.3), (0.3, 0.3), (0.5, 0.5), (0.6, 0.4), (0.6, 0.6), (0.62, 0.62)])
+    c = (0.5 * side if L > 1 else 0.0) + 0.02  # just inside a leaf's lower corner
+    pot = potentials(n, L, side, noalloc, (c, c), off, charge)
+    np.testing.assert_array_equal(pot, np.full(len(off), -charge))
