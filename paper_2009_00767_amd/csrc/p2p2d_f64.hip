@@ -421,13 +421,21 @@ void direct_f64(const FmmArgs& a, int over, int lsh, hipStream_t st) {
                        a.leaf_start, lsh);
 }
 
-// Tiles from 1024 of them on (four workgroups a CU).  Below that the chip
-// wants more threads than targets: sixteen lanes a target up to 2^14 targets
-// and four up to 2^16 give it at least one wave a SIMD (4096 targets: 63 us
-// with one lane, 12 with sixteen; 20,011: 76 and 18).
+// Tiles from 1024 of them on (four workgroups a CU) and for 6 to 40 particles a
+// leaf.  Below, a tile's staging costs more than its sources' second reads (uniform
+// particles at levels 7, 8 and 9, whole calls with tiles and without: 5 a leaf
+// 121, 241 and 824 us against 112, 235 and 832; 7: 128, 275, 969 against 127,
+// 284, 1012; 0.1 a leaf 193, 281, 589 against 176, 266, 549).  Above, many a halo
+// (36 leaves) outgrows the stage and the direct kernel does it again (39 a leaf at
+// levels 7 and 8: 458 and 1580 against 453 and 1661; 45: 737 and 2260 against 534
+// and 2022).
+// Without tiles the chip wants more threads than targets: sixteen lanes a target
+// up to 2^14 targets and four up to 2^16 give it at least one wave a SIMD (4096
+// targets: 63 us with one lane, 12 with sixteen; 20,011: 76 and 18).
 int64_t near_tiles(const FmmArgs& a) {  // 0: the direct form
   const int64_t tiles = a.lt.L >= 2 && a.p2p_over ? (int64_t)a.lt.nsys << (2 * (a.lt.L - 2)) : 0;
-  return tiles >= 1024 ? tiles : 0;
+  const bool dense = a.n >= 6 * 16 * tiles && a.n <= 40 * 16 * tiles;
+  return tiles >= 1024 && dense ? tiles : 0;
 }
 
 template <int P, int PB, bool FULL>
