@@ -86,8 +86,10 @@ __host__ __device__ constexpr int m2l3_lds_slots() {
 }
 
 // The row of a source outside the grid (a select on the values would wait for
-// their loads where they are issued).
-static __device__ const double g_zero_row[128] = {0};
+// their loads where they are issued): read like a box row, up to value 4 KS (the
+// degree-0 value's index is at most that) and 16 bytes at a time.
+constexpr int kZeroRow = 132;
+alignas(16) static __device__ const double g_zero_row[kZeroRow] = {0};
 
 struct M2l3Tiles {
   int klo, khi;
@@ -161,7 +163,13 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 && KS < 32 ? 2 : 1) void k_
   T* loc = (kF64 ? (T*)a.loc64 : (T*)a.loc32) + a.lt.off[k] * cs;
   const T* ops = kF64 ? (const T*)a.opl64 : (const T*)a.opl32;
   const int i00 = ly.nr - 1;  // index of the degree-0 value
-  const int64_t zoff = reinterpret_cast<const T*>(g_zero_row) - mom;
+  static_assert(4 * KS + 1 <= kZeroRow, "the zero row is as long as a box row");
+  static_assert(sizeof(vec_t) <= 16, "the zero row's alignment");
+  // (global address space: a generic pointer chosen between the two would make
+  // the loads flat ones)
+  typedef const __attribute__((address_space(1))) T* row_t;
+  typedef const __attribute__((address_space(1))) vec_t* row_vec_t;
+  const row_t mom_rows = (row_t)mom, zero_row = (row_t)(const T*)g_zero_row;
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, g = lane >> 4;
@@ -225,7 +233,11 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 && KS < 32 ? 2 : 1) void k_
       }
     }
   };
-  // `newer`: loads issued after the copies that need not have arrived.
+  // `newer`: loads issued after the copies that need not have arrived.  Right only
+  // while at least that many loads stay behind the copies in issue order: fetch,
+  // which issues the copies, stands before contract, whose scheduling barriers
+  // keep each reload in its step, and every layer's last part and degree-0
+  // value are reloaded there; neither may be moved across a barrier.
   auto settle = [&](T* buf, int newer) {
     if constexpr (kDB) {
       lds_copy_wait(newer);
@@ -242,7 +254,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 && KS < 32 ? 2 : 1) void k_
   uint32_t yz[MB];
   bool yzok[MB];
   int qyz = -1;
-  auto find_rows = [&](int qq, const T* (&row)[MB]) {
+  auto find_rows = [&](int qq, row_t (&row)[MB]) {
     if (qq / 6 != qyz) {  // (uniform)
       qyz = qq / 6;
       const int sy = ty + ylo + qyz % 6, dz = zlo + qyz / 6;
@@ -258,17 +270,17 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 && KS < 32 ? 2 : 1) void k_
     const uint32_t xs = spread3((uint32_t)sx);
 #pragma unroll
     for (int m = 0; m < MB; ++m)
-      row[m] = mom + (xok && yzok[m] ? (int64_t)(xs | yz[m]) * cs : zoff);
+      row[m] = xok && yzok[m] ? mom_rows + (int64_t)(xs | yz[m]) * cs : zero_row;
   };
   // Values s0 .. s0 + RW - 1 of this lane's part of a row (one load).
   constexpr int RW = (KS * sizeof(T)) % 16 == 0 ? VW : 1;
-  auto load_part = [&](const T* (&row)[MB], int s0, T (&av)[MB][KS]) {
+  auto load_part = [&](const row_t (&row)[MB], int s0, T (&av)[MB][KS]) {
 #pragma unroll
     for (int m = 0; m < MB; ++m) {
       if constexpr (RW == 1) {
         av[m][s0] = row[m][g * KS + s0];
       } else {
-        const vec_t v = *reinterpret_cast<const vec_t*>(row[m] + g * KS + s0);
+        const vec_t v = *(row_vec_t)(row[m] + g * KS + s0);
 #pragma unroll
         for (int c = 0; c < RW; ++c) av[m][s0 + c] = v[c];
       }
@@ -281,7 +293,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 && KS < 32 ? 2 : 1) void k_
   // the matrix cores' time).  RELOAD: a part of the rows is dead after its last
   // step, and the next offset's takes its registers.
   auto contract = [&](auto reload, const T* Wl, T (&av)[MB][KS], T (&a0)[MB],
-                      const T* (&row)[MB]) {
+                      const row_t (&row)[MB]) {
     constexpr bool kReload = decltype(reload)::value;
     constexpr acc_t zero = {0, 0, 0, 0};
     const T* R = Wl + (size_t)NB * (KS + 1) * 64;
@@ -332,7 +344,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 && KS < 32 ? 2 : 1) void k_
   };
 
   int q = SPLIT ? nth_q(chunk * 189 / ns) : next_q(-1);
-  const T* row[MB];
+  row_t row[MB];
   T av[MB][KS], a0[MB];
   fetch(q, wb0);
   find_rows(q, row);
@@ -353,6 +365,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 && KS < 32 ? 2 : 1) void k_
       fetch(more ? qn : q, nxt);
       find_rows(more ? qn : q, row);
       contract(std::true_type{}, cur, av, a0, row);
+      static_assert(KS / RW + 1 >= 2, "two reloads a layer behind the copies");
       settle(nxt, 2 * MB);
       __syncthreads();
       if (!more) break;
