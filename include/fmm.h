@@ -353,7 +353,10 @@ int fmm_mlp_train(float* w, const float* x, const float* t, int64_t m, int32_t s
  * (eight waves of two layers; FP64, tile_mb 1, levels from 5 on: eight waves of
  * one layer); each operator value read from LDS serves the products of a wave's
  * layers; xcd_remap = 1 only.  Anything else: FMM_ERR_INVALID_ARG.  Every
- * variant forms the same sums in the same order: results are bit-identical. */
+ * variant forms the same sums in the same order: results are bit-identical.
+ * (2D FP64 launches of at most 128 tiles of 8 x 8 targets, all levels and stacked
+ * systems of a depth together, run in a form of their own whatever tile_mb is;
+ * FMM_AUTOTUNE leaves it at 1 where the plan's own tree is such a launch.) */
 int fmm_set_m2l_variant(fmm_plan_t plan, int32_t tile_mb, int32_t xcd_remap);
 
 /* Device-detected status of the last fmm_eval on this plan.  Synchronises with

@@ -937,6 +937,8 @@ int autotune_m2l(fmm_plan_s* pl) {
   for (int mb : {1, 2, 3, 4, 8}) {
     if (pl->dim == 2 ? !m2l2d_variant_ok(mb, fp64, pl->pb, bf16) : !m2l3d_variant_ok(mb, fp64))
       continue;
+    // launches of few tiles have one height: timing the others would pick by noise
+    if (pl->dim == 2 && mb > 1 && m2l2d_split(a, fp64)) continue;
     for (int rm : {1, 0}) {
       if (pl->dim == 3 && rm == 0) continue;  // 3D tiles are always dealt per XCD
       a.m2l_mb = mb;

@@ -213,6 +213,8 @@ size_t p2m2d_partial_entries(const LevelTable& lt, int klo, int khi, int64_t max
 void launch_m2l2d(const FmmArgs& a, bool fp64, hipStream_t st, bool bf16 = false);
 // Whether tile height mb is compiled and fits the LDS for this precision and bucket.
 bool m2l2d_variant_ok(int mb, bool fp64, int pb, bool bf16);
+// Whether levels a.klo..a.khi run in the form for few tiles, which has one height.
+bool m2l2d_split(const FmmArgs& a, bool fp64);
 void launch_l2p2d(const FmmArgs& a, bool leaf_local, hipStream_t st);
 void launch_p2p2d(const FmmArgs& a, bool leaf_local, hipStream_t st);
 // Adaptive depth: the open flags of levels kmin..L - 1 (one launch per level,

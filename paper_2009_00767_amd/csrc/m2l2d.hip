@@ -828,7 +828,7 @@ constexpr int64_t kM2lSplitTiles = 128;
 // (whole evaluations of order 16: level 6, 86 tiles,
 // 106 -> 100 us; level 7, 342 tiles, 177 unsplit, 180 split).  The rule counts tiles of 8 x 8, so every tile height a caller
 // sets gives the same sums.
-static bool m2l2d_split(const FmmArgs& a, bool fp64) {
+bool m2l2d_split(const FmmArgs& a, bool fp64) {
   int64_t t = 0;
   for (int k = a.klo; k <= a.khi; ++k) {
     const int64_t n = (((int64_t)1 << k) + 7) / 8;
