@@ -90,13 +90,18 @@ inline P2mPlan make_p2m_plan(int dim, int klo, int khi, int64_t n, int nsys = 1,
   return pl;
 }
 
-// Particles per lane: FP32 sums keep 16, which their rounding follows; FP64 sums
-// take 8 from 2^19 particles on and 4 below, where the waves of a level would
-// not fill the chip and a launch lasts as long as one lane's chain (whole
-// evaluation of 4096 particles: 67 us with 16, 61 with 8, 60 with 4; of 2^20:
-// 547, 545 and 555).
-inline int p2m_lane_particles(bool f64, int64_t n) {
-  return !f64 ? 16 : n >= ((int64_t)1 << 19) ? 8 : 4;
+// Particles per lane.  FP32 sums keep 16, which their rounding follows.  FP64 sums
+// take 4 up to 2^16 particles, where the waves of a level would not fill the chip
+// and a launch lasts as long as one lane's chain (whole evaluations with 16, 8 and
+// 4: 4096 particles 50.8, 48.5, 47.1 us, 65,536 103, 100, 98; 20,000 in 3D 251,
+// 240, 238; 8192 with 8 x 8 Chebyshev points 116, 108, 107).  Beyond, shorter
+// chains help dense boxes (2D log, `beyond` 8: 262,144 and 1,048,576 clustered 1944,
+// 1884, 1872 and 1833, 1784, 1826), but the further waves take their places from
+// the near field beside them (150,000 clustered 2022, 2043, 2312; 400,000 uniform
+// 254, 261, 273), and elsewhere only that is left (`beyond` 16: 300,000 with 4 x 4
+// and 8 x 8 points 167, 171, 176 and 392, 452, 459; 600,000 in 3D 2309, 2327, 2339).
+inline int p2m_lane_particles(bool f64, int64_t n, int beyond) {
+  return !f64 ? 16 : n > ((int64_t)1 << 16) ? beyond : 4;
 }
 
 // The work item of thread t of level k: box b, slice j, lane r of its group, and

@@ -101,7 +101,7 @@ void launch_p2m2d_slices(const FmmArgs& a, const P2mPlan& pl, int pb, bool f64, 
 template <int PB>
 static void p2m_dispatch(const FmmArgs& a, bool ll, bool f64, hipStream_t st) {
   const P2mPlan pl = make_p2m_plan(2, a.klo, a.khi, a.n, a.lt.nsys,
-                                   p2m_lane_particles(f64, a.n));
+                                   p2m_lane_particles(f64, a.n, 8));
   const int64_t thr = pl.thr_off[a.khi + 1];
   const dim3 grid((unsigned)((thr + 255) / 256));
   const bool full = a.ord_full != 0;

@@ -440,7 +440,7 @@ int64_t near_tiles(const FmmArgs& a) {  // 0: the direct form
 
 template <int P, int PB, bool FULL>
 void near_moments(const FmmArgs& a, hipStream_t st) {
-  const P2mPlan pl = make_p2m_plan(2, a.klo, a.khi, a.n, a.lt.nsys, p2m_lane_particles(true, a.n));
+  const P2mPlan pl = make_p2m_plan(2, a.klo, a.khi, a.n, a.lt.nsys, p2m_lane_particles(true, a.n, 8));
   const int moments = (int)((pl.thr_off[a.khi + 1] + 256 * 8 - 1) / (256 * 8) * 8);
   const dim3 grid(chunked_grid((a.n * P + 255) / 256).x + moments);
   if (near_unit(a.lt))
