@@ -94,12 +94,13 @@ inline P2mPlan make_p2m_plan(int dim, int klo, int khi, int64_t n, int nsys = 1,
 // take 4 up to 2^16 particles, where the waves of a level would not fill the chip
 // and a launch lasts as long as one lane's chain (whole evaluations with 16, 8 and
 // 4: 4096 particles 50.8, 48.5, 47.1 us, 65,536 103, 100, 98; 20,000 in 3D 251,
-// 240, 238; 8192 with 8 x 8 Chebyshev points 116, 108, 107).  Beyond, shorter
-// chains help dense boxes (2D log, `beyond` 8: 262,144 and 1,048,576 clustered 1944,
-// 1884, 1872 and 1833, 1784, 1826), but the further waves take their places from
-// the near field beside them (150,000 clustered 2022, 2043, 2312; 400,000 uniform
-// 254, 261, 273), and elsewhere only that is left (`beyond` 16: 300,000 with 4 x 4
-// and 8 x 8 points 167, 171, 176 and 392, 452, 459; 600,000 in 3D 2309, 2327, 2339).
+// 240, 238; 8192 with 8 x 8 Chebyshev points 116, 108, 107).  Beyond, shorter chains
+// are what dense boxes need, most of all in 3D, whose boxes hold few particles on
+// average (clustered: 100,000 at level 4 13.4, 4.0, 2.2 ms, 300,000 at level 5 13.2,
+// 13.4, 10.8; uniform: 600,000 2.31, 2.33, 2.34); in 2D the further waves also take
+// their places from the near field beside them (clustered: 150,000 at level 6 2022,
+// 2043, 2312 us, 262,144 at level 7 1944, 1884, 1872, 100,000 with 8 x 8 points 1457,
+// 1305, 1655; uniform: 400,000 254, 261, 273, 300,000 with 8 x 8 points 392, 452, 459).
 inline int p2m_lane_particles(bool f64, int64_t n, int beyond) {
   return !f64 ? 16 : n > ((int64_t)1 << 16) ? beyond : 4;
 }

@@ -161,7 +161,7 @@ __global__ void k_p2m3d_slices(FmmArgs a, P2mPlan pl, int k, int nc) {
 
 template <int PB, int BASIS = 0>
 static void p2m3d_dispatch(const FmmArgs& a, bool ll, bool f64, hipStream_t st) {
-  const P2mPlan pl = make_p2m_plan(3, a.klo, a.khi, a.n, 1, p2m_lane_particles(f64, a.n, 16));
+  const P2mPlan pl = make_p2m_plan(3, a.klo, a.khi, a.n, 1, p2m_lane_particles(f64, a.n, 4));
   const int64_t thr = pl.thr_off[a.khi + 1];
   const dim3 grid((unsigned)((thr + 255) / 256));
   if (f64) {

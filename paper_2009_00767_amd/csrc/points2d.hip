@@ -395,7 +395,7 @@ __global__ __launch_bounds__(256) void k_l2p2d_points(FmmArgs a, PtsNodes nd) {
 template <int N>
 void p2m_points_n(const FmmArgs& a, bool ll, bool f64, hipStream_t st) {
   const PtsNodes nd = make_nodes(a.basis, N);
-  const P2mPlan pl = make_p2m_plan(2, a.klo, a.khi, a.n, 1, p2m_lane_particles(f64, a.n, 16));
+  const P2mPlan pl = make_p2m_plan(2, a.klo, a.khi, a.n, 1, p2m_lane_particles(f64, a.n, 8));
   const int64_t thr = pl.thr_off[a.khi + 1];
   const dim3 grid((unsigned)((thr + 255) / 256));
   if (f64) {
