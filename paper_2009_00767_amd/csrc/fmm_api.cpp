@@ -1017,7 +1017,7 @@ int fmm_eval(fmm_plan_t pl, int64_t n, const double* pos, const double* q, doubl
   if (timing && (pl->ev_mask & 1)) (void)hipEventRecord(ev[0], st);
 
   const int bits = pl->dim * pl->L;
-  const bool one = sort_in_one(n, bits, pl->f32);
+  const bool one = sort_in_one(n, bits, pl->f32 || (pl->dim == 2 && pl->basis));
   const bool two_digit = !one && pl->radix_parts && radix_two_digit(n, bits);
   int which = 0;
   if (one) {

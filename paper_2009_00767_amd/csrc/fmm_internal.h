@@ -122,7 +122,7 @@ void radix_sort_two_digit(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int
                           double* qs);
 // Few particles and keys of few bits: binning, sort, leaf offsets and the
 // sorted records (rec) or coordinates and charges (xs .. qs) in one launch.
-// forked: the evaluation's other launches run on two streams.
+// forked: the evaluation is one on two streams that waits for the host (sort.hip).
 bool sort_in_one(int64_t n, int bits, bool forked);
 void launch_sort_one(int dim, const double* pos, const double* q, int64_t n, const LevelTable& lt,
                      int bits, uint32_t* keys, int32_t* vals, int32_t* flag, int32_t tag,

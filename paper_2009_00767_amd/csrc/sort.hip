@@ -708,11 +708,12 @@ constexpr int kOneBits = 12;  // key bits
 // at levels 3 to 6: 3000 particles 42.6, 41.8, 51.6, 84.3 us against 49.1, 48.2,
 // 57.2, 87.2; 4096: 46.6, 44.7, 54.9, 82.1 against 50.2, 49.1, 57.3, 82.5; 5000:
 // 56.5, 51.4, 62.0, 85.7 against 56.1, 50.7, 57.1, 78.6.  An evaluation on two
-// streams (FP32 modes) also waits for the host, which the launches keep longer:
-// 6000 particles 91.0, 77.3, 90.2, 103.7 against 95.6, 83.0, 93.5, 105.2; 7000: 99.9,
-// 77.3, 89.2, 101.5 against 103.8, 82.0, 90.4, 101.1; 8192: 117.5, 80.6, 91.8, 102.5
-// against 115.6, 82.6, 90.7, 100.0.
-constexpr int kOneMax = 4096, kOneMaxForked = 6144;
+// streams that keep the chip for less than the host needs to fill them (FP32
+// modes, 2D point charges) waits for the host, which the launches keep longer: FP32,
+// 6000 particles 91.0, 77.3, 90.2, 103.7 against 95.6, 83.0, 93.5, 105.2; 8192:
+// 117.5, 80.6, 91.8, 102.5 against 115.6, 82.6, 90.7, 100.0; 4 x 4 points in FP64 at
+// level 4, 4500, 6000 and 8192: 52, 57, 63 against 69, 70, 67.
+constexpr int kOneMax = 4096, kOneMaxForked = 8192;
 
 template <int D, int PER>  // PER: particles per thread
 __global__ __launch_bounds__(kOneThreads) void k_sort_one(
@@ -837,11 +838,11 @@ void launch_sort_one(int dim, const double* pos, const double* q, int64_t n, con
   if (dim == 2) {
     if (n <= 2 * kOneThreads) SFFMM_ONE(2, 2);
     else if (n <= 4 * kOneThreads) SFFMM_ONE(2, 4);
-    else SFFMM_ONE(2, 6);
+    else SFFMM_ONE(2, 8);
   } else {
     if (n <= 2 * kOneThreads) SFFMM_ONE(3, 2);
     else if (n <= 4 * kOneThreads) SFFMM_ONE(3, 4);
-    else SFFMM_ONE(3, 6);
+    else SFFMM_ONE(3, 8);
   }
 #undef SFFMM_ONE
 }

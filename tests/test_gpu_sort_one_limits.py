@@ -1,6 +1,7 @@
 """The particle sort on both sides of the one-workgroup form's limits (4096
-particles, 6144 in the FP32 modes, 12 key bits): permutation, keys and leaf offsets
-bit-exact, the permutation being the stable argsort of the leaf keys."""
+particles, 8192 in the FP32 modes and with 2D point charges, 12 key bits):
+permutation, keys and leaf offsets bit-exact, the permutation being the stable
+argsort of the leaf keys."""
 import numpy as np
 import pytest
 
@@ -20,14 +21,16 @@ def morton(c):
     return key
 
 
-@pytest.mark.parametrize("n", [4095, 4096, 4097, 5119, 6143, 6144, 6145])
+@pytest.mark.parametrize("n", [4095, 4096, 4097, 5119, 6145, 8192, 8193])
 @pytest.mark.parametrize("dim,L", [(2, 0), (2, 4), (2, 5), (2, 6), (2, 7), (3, 2), (3, 4)])
-@pytest.mark.parametrize("prec", [F.FMM_FP64, F.FMM_FP32])
+@pytest.mark.parametrize("prec", [F.FMM_FP64, F.FMM_FP32, "points"])
 def test_both_sides(n, dim, L, prec):
     make = workloads.uniform if n % 2 else workloads.gaussian_mixture
     pos, q = make(n, dim, seed=n)
-    f = F.FMM(F.FMM_LOG2D if dim == 2 else F.FMM_COULOMB3D, levels=L, order=4, precision=prec,
-              max_particles=n, flags=F.FMM_SYNC_CHECK)
+    kernel = F.FMM_LOG2D if dim == 2 else F.FMM_COULOMB3D
+    if prec == "points":
+        kernel, prec = (F.FMM_LOG2D_POINTS if dim == 2 else F.FMM_COULOMB3D_POINTS), F.FMM_FP64
+    f = F.FMM(kernel, levels=L, order=4, precision=prec, max_particles=n, flags=F.FMM_SYNC_CHECK)
     f.evaluate(torch.from_numpy(pos).cuda(), torch.from_numpy(q).cuda())
     nleaf = 2 ** (dim * L)
     perm = np.frombuffer(F.fmm_debug_level_data(f.plan, 0, F.FMM_DBG_PERM, 4 * n), np.int32)
