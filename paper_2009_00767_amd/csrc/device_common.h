@@ -105,6 +105,11 @@ inline int p2m_lane_particles(bool f64, int64_t n, int beyond) {
   return !f64 ? 16 : n > ((int64_t)1 << 16) ? beyond : 4;
 }
 
+// A particle's sorted place where lanes step through a range: unsigned, since a
+// plan may hold up to 2^31 - 2 particles, and a lane's first place, or the one past
+// its last, lies up to a step (at most 64 + 63) beyond the range's end.
+typedef uint32_t place_t;
+
 // The work item of thread t of level k: box b, slice j, lane r of its group, and
 // (inside the box range) its particles lo + r, lo + r + G, ... below hi.
 struct P2mItem {
@@ -117,11 +122,16 @@ __device__ __forceinline__ P2mItem p2m_item_of(const P2mPlan& pl, int k, int64_t
   return P2mItem{local >> (lg + ls), (int)(local >> lg) & ((1 << ls) - 1),
                  (int)local & ((1 << lg) - 1)};
 }
-__device__ __forceinline__ void p2m_slice(const P2mPlan& pl, int k, int j, int32_t s0, int32_t s1,
-                                          int32_t& lo, int32_t& hi) {
+__host__ __device__ inline void p2m_slice(const P2mPlan& pl, int k, int j, int32_t s0, int32_t s1,
+                                          place_t& lo, place_t& hi) {
   const int64_t len = s1 - s0;
-  lo = s0 + (int32_t)(len * j >> pl.lgS[k]);
-  hi = s0 + (int32_t)(len * (j + 1) >> pl.lgS[k]);
+  lo = (place_t)(s0 + (len * j >> pl.lgS[k]));
+  hi = (place_t)(s0 + (len * (j + 1) >> pl.lgS[k]));
+}
+
+// Distance between the 64 probes of a search over n >= 1 places.
+__host__ __device__ constexpr int32_t probe_step(int32_t n) {
+  return (int32_t)(((place_t)n + 63) >> 6);
 }
 
 // Sums v[0..N) over the 2^lg lanes of each group (neighbouring lanes, lg uniform

@@ -96,7 +96,7 @@ __global__ __launch_bounds__(256) void k_p2m3d(FmmArgs a, P2mPlan pl) {
 #pragma unroll
   for (int i = 0; i < NR; ++i) acc[i] = (T)0;
   if (valid) {
-    int32_t lo, hi;
+    place_t lo, hi;
     p2m_slice(pl, k, j, a.leaf_start[b << (3 * sh)], a.leaf_start[(b + 1) << (3 * sh)], lo, hi);
     const T is = (T)lt.inv_s[k], sL = (T)lt.s[lt.L];
     T cx = 0, cy = 0, cz = 0;
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(256) void k_p2m3d(FmmArgs a, P2mPlan pl) {
       cy = (T)(lt.origin[1] + lt.s[k] * ((double)compact3(ub >> 1) + 0.5));
       cz = (T)(lt.origin[2] + lt.s[k] * ((double)compact3(ub >> 2) + 0.5));
     }
-    for (int32_t i = lo + r; i < hi; i += G) {
+    for (place_t i = lo + r; i < hi; i += G) {
       T q, wx, wy, wz;
       if (LL) {
         const float4 pt = a.pts[i];

@@ -84,7 +84,7 @@ __device__ __forceinline__ void p2m_item(const FmmArgs& a, const P2mPlan& pl, in
   if (valid && a.adapt_open && k > lt.kmin)
     valid = (a.adapt_open[adapt_open_off(k - 1) + (b >> 2)] & 2) != 0;
   if (valid) {
-    int32_t lo, hi;
+    place_t lo, hi;
     p2m_slice(pl, k, it.j, a.leaf_start[b << (2 * sh)], a.leaf_start[(b + 1) << (2 * sh)], lo, hi);
     const T is = (T)lt.inv_s[k];
     T cx = 0, cy = 0, sL = (T)lt.s[lt.L];
@@ -105,7 +105,7 @@ __device__ __forceinline__ void p2m_item(const FmmArgs& a, const P2mPlan& pl, in
         nq = a.qs[lo + it.r];
       }
     }
-    for (int32_t i = lo + it.r; i < hi; i += G) {
+    for (place_t i = lo + it.r; i < hi; i += G) {
       T q, wr, wi;
       const float4 pt = npt;
       const double px = nx, py = ny, pq = nq;

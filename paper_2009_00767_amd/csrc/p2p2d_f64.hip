@@ -202,7 +202,10 @@ __device__ __forceinline__ bool store_near(const FmmArgs& a, int64_t j, const Ne
 }
 
 // Sources i0 + P k (k = 0, 1, ...) below i1 in batches of four; the last batch
-// repeats its first source with no charge.
+// repeats its first source with no charge.  (Places are compared by their distance:
+// a plan may hold up to 2^31 - 2 particles, though few with P > 1.  Unsigned ones,
+// which may wrap, keep a batch's loads from being joined: 500,009 clustered
+// particles 1650 -> 1774 us.)
 template <int P, bool UNIT>
 __device__ __forceinline__ void range2_f64(const double* __restrict__ xs,
                                            const double* __restrict__ ys,
@@ -210,7 +213,7 @@ __device__ __forceinline__ void range2_f64(const double* __restrict__ xs,
                                            double x, double y, double thr, const double2* tab,
                                            NearSum& s) {
   int32_t i = i0;
-  for (; i + 3 * P < i1; i += 4 * P) {
+  for (; i1 - i > 3 * P; i += 4 * P) {
     double sx[4], sy[4], q[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -224,7 +227,7 @@ __device__ __forceinline__ void range2_f64(const double* __restrict__ xs,
     double sx[4], sy[4], q[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const bool in = i + u * P < i1;
+      const bool in = u * P < i1 - i;
       const int32_t iu = in ? i + u * P : i;
       sx[u] = xs[iu];
       sy[u] = ys[iu];

@@ -149,7 +149,7 @@ __global__ __launch_bounds__(256) void k_p2m2d_points(FmmArgs a, P2mPlan pl, Pts
 #pragma unroll
   for (int i = 0; i < D; ++i) acc[i] = (T)0;
   if (valid) {
-    int32_t lo, hi;
+    place_t lo, hi;
     p2m_slice(pl, k, j, a.leaf_start[b << (2 * sh)], a.leaf_start[(b + 1) << (2 * sh)], lo, hi);
     const T is = (T)lt.inv_s[k], sL = (T)lt.s[lt.L];
     T cx = 0, cy = 0;
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(256) void k_p2m2d_points(FmmArgs a, P2mPlan pl, Pts
       cx = (T)(lt.origin[0] + lt.s[k] * ((double)compact2((uint32_t)b) + 0.5));
       cy = (T)(lt.origin[1] + lt.s[k] * ((double)compact2((uint32_t)b >> 1) + 0.5));
     }
-    for (int32_t i = lo + r; i < hi; i += G) {
+    for (place_t i = lo + r; i < hi; i += G) {
       T q, wx, wy;
       if (LL) {
         const float4 pt = a.pts[i];

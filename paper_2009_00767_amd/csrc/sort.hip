@@ -860,7 +860,7 @@ __device__ __forceinline__ int32_t wave_first_at_least(const uint32_t* __restric
   const int lane = threadIdx.x & 63;
   int32_t lo = 0, hi = n;
   while (lo < hi) {
-    const int32_t step = (hi - lo + 63) >> 6;
+    const int32_t step = probe_step(hi - lo);
     const int64_t i = lo + (int64_t)lane * step;
     const int m = __popcll(__ballot(i < hi && (int64_t)keys[i < hi ? i : lo] < l));
     if (m == 0) return lo;  // the keys ascend: the first m probes are below l
