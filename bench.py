@@ -42,10 +42,11 @@ CU, LANES, CLOCK_GHZ = 256, 64, 2.4
 # instructions dearer than one slot, see the roofline note).  2D FP32: 10 in the
 # direct kernel (80 in the body of its loop over eight sources), 12 in the
 # LDS-tile kernel (whose per-source leaf offset costs two more); the lower
-# count, i.e. the higher peak, is the one used.  2D FP64: 85 in the body of
-# the tile kernel's loop over four sources; 3D FP32: 70 in the body of the loop
-# over four sources; 3D FP64: 77 in its loop over four sources of another leaf.
-P2P_SLOTS = {(2, "fp32"): 10.0, (2, "fp64"): 21.25, (3, "fp32"): 17.5, (3, "fp64"): 19.25}
+# count, i.e. the higher peak, is the one used.  2D FP64: 111 in the tile
+# kernel's loop over four sources (26 form the differences and r^2 and compare,
+# 85 the sums); 3D FP32: 70 in the body of the loop over four sources; 3D FP64:
+# 77 in its loop over four sources of another leaf.
+P2P_SLOTS = {(2, "fp32"): 10.0, (2, "fp64"): 27.75, (3, "fp32"): 17.5, (3, "fp64"): 19.25}
 
 
 PHASE_STEPS = 5

@@ -3,15 +3,25 @@
 // back to input order).  Sources of a target: its leaf and the adjacent ones;
 // pairs with r = 0 (the target itself, coincident points) contribute nothing.
 //
-// What bounds it: vector issue.  A pair needs log r^2 and 1 / r^2 in FP64;
-// with the library's log and a correctly rounded division it took about 117
-// issue slots.  Here it takes about 30: the reciprocal is the hardware
-// estimate with one third-order step, and the logarithm comes from a table in
-// LDS.  Measured (MI355X): 1.8e9 pairs of a 500,009-particle mixture (level 8,
-// dense leaves, direct form) 4.5 -> 1.45 ms, 1.27e12 pairs/s; 2^20 uniform
-// particles at level 8 (tile form, beside the moments) 0.90 -> 0.35 ms; 4096
-// particles at level 4 (sixteen lanes a target instead of one: 64 waves had
-// left the chip idle) 63 -> 12 us.
+// A pair needs log r^2 and 1 / r^2 in FP64; with the library's log and a correctly
+// rounded division it took about 117 vector instructions.  Here the loop over four
+// sources holds 111: the reciprocal is the hardware estimate with one third-order
+// step, and the logarithm comes from a table in LDS.  Whole evaluations, before and
+// now: 500,009 clustered particles at level 8 (8.5e8 to 9.8e8 pairs) 4.53 -> 1.62
+// ms, 2^20 uniform at level 8 (1.5e8) 0.95 -> 0.52, 4096 at level 4 (sixteen lanes a
+// target instead of one: 64 waves had left the chip idle) 112 -> 44 us.
+//
+// What bounds it, by counters of each kernel alone (vector instructions take 4
+// cycles of a SIMD and more for the reciprocal, exponent and conversion):
+//   direct form, the clustered case: 1.27 ms, 6.9e11 pairs/s, 29.4 instructions a
+//     pair, the vector unit at work for 0.62 of the cycles.  Waves are 0.42 of their
+//     time ready without a turn and 0.22 waiting for data, and 2.2 of them are on a
+//     SIMD on average: those of the densest leaves outlast the others.  The LDS is
+//     busy for 0.22 of the cycles, two thirds of that bank conflicts of the table.
+//   tile form, the uniform case: 0.24 ms, 6.2e11 pairs/s, 39.8 instructions a pair
+//     (lanes whose spans have ended, remainders taken one by one, staging), the vector
+//     unit at work for 0.77 of the cycles, the LDS for 0.41, a third of that
+//     conflicts; 2.8 waves on a SIMD.
 #include "near2d.h"
 #include "p2m2d.h"
 
@@ -432,9 +442,17 @@ void direct_f64(const FmmArgs& a, int over, int lsh, hipStream_t st) {
 // (36 leaves) outgrows the stage and the direct kernel does it again (39 a leaf at
 // levels 7 and 8: 458 and 1580 against 453 and 1661; 45: 737 and 2260 against 534
 // and 2022).
-// Without tiles the chip wants more threads than targets: sixteen lanes a target
-// up to 2^14 targets and four up to 2^16 give it at least one wave a SIMD (4096
-// targets: 63 us with one lane, 12 with sixteen; 20,011: 76 and 18).
+// Without tiles the chip wants more threads than targets.  Whole calls, order 12,
+// with sixteen, four and one lane a target, uniform | clustered particles:
+//      4096, level 4   44.8  48.7  64.2 |  60.7 103.9 259.4 us
+//    16,384, level 5   62.3  58.2  75.3 | 118.7 167.1 377.8
+//    24,000, level 5   69.5  64.0  84.1 | 172.2 236.7 523.9
+//    32,768, level 6   85.9  68.4  75.6 | 178.8 188.3 376.6
+//    65,536, level 6  121.4  94.0  93.3 | 398.5 474.1 671.6
+//   100,000, level 6  157.3 120.9 122.7 (131,072: 187.3 151.2 135.9)
+// Uniform particles turn from sixteen lanes to four near 12,000, clustered ones
+// beyond 65,536; sixteen up to 2^14 lies between.  From four to one uniform ones
+// turn at 65,536 to 100,000.
 int64_t near_tiles(const FmmArgs& a) {  // 0: the direct form
   const int64_t tiles = a.lt.L >= 2 && a.p2p_over ? (int64_t)a.lt.nsys << (2 * (a.lt.L - 2)) : 0;
   const bool dense = a.n >= 6 * 16 * tiles && a.n <= 40 * 16 * tiles;
